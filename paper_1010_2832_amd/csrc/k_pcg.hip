@@ -299,6 +299,7 @@ __global__ __launch_bounds__(NT) void k_cg_init(long long n, const T* bsrc, T* _
         sc->max_iter = max_iter;
         sc->alpha = sc->beta = sc->pq = 0.0;
         sc->fallbacks = 0;
+        sc->aborted = 0;
     }
     double vv[2] = {rz, rr};
     block_partial<2, NT>(vv, part_out, gridDim.x, blockIdx.x);
@@ -324,6 +325,7 @@ __global__ __launch_bounds__(NT) void k_cg_restart(long long n, const T* __restr
         sc->done = 0;
         sc->iter = 0;
         sc->max_iter = max_iter;
+        sc->aborted = 0;
     }
     double vv[2] = {rz, rr};
     block_partial<2, NT>(vv, part_out, gridDim.x, blockIdx.x);

@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <utility>
 
@@ -175,6 +176,77 @@ int run_chunks(vfs_ctx* ctx, Vecs<T>& v, bool set_bb, Scalars* out) {
         if (out->done) return VFS_OK;
         chunk = std::min(chunk * 2, 256);
     }
+}
+
+// Most workgroups a resident solve may have: they wait for each other, so all
+// of them must fit on the chip at once, one per compute unit.
+int res_most() {
+    static int cache[16] = {};
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+    int& c = cache[dev & 15];
+    if (c == 0) {
+        if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            ncu < 1)
+            ncu = 1;
+        c = std::min(ncu, kResMost);
+    }
+    return c;
+}
+
+// One resident solve at a time on a device: two of them could each hold half
+// of the chip and wait for the other half.
+std::mutex& res_mutex() {
+    static std::mutex m[16];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+    return m[dev & 15];
+}
+
+// Tile shape of the resident 2D solve, or -1 for the launched iteration.  The
+// smallest tile whose list fits wins: it leaves each workgroup the least work,
+// and what more workgroups cost the exchange (1.4 us a round for 32 of them,
+// 2.3 us for 256) is less than a doubled tile does.
+int res2d_shape(const vfs_ctx* ctx, int word) {
+    if (!ctx->res_part || ctx->res_off) return -1;
+    const int most = res_most();
+    for (int q = 0; q < (word == 4 ? kResShapes : kResShapes - 1); ++q)
+        if (ctx->res_count[q] > 0 && ctx->res_count[q] <= most) return q;
+    return -1;
+}
+
+// A whole Jacobi-PCG run on the residual in v.r, added to v.x, in one resident
+// kernel.  VFS_OK with *gave_up set when its workgroups could not all run (the
+// context then keeps to the launched iteration; v.r is untouched, v.x void).
+template <typename T>
+int run_resident2d(vfs_ctx* ctx, int shape, Vecs<T>& v, bool set_bb, int max_iter, Scalars* out,
+                   bool* gave_up) {
+    hipStream_t s = ctx->stream;
+    if (ctx->res_stamp > 0xfffffff0u - (unsigned)max_iter - 8u) {   // stamps would wrap
+        HIPCHK(hipMemsetAsync(ctx->res_part, 0, 2 * kResMost * 16 * sizeof(*ctx->res_part), s));
+        HIPCHK(hipMemsetAsync(ctx->res_msg, 0, ctx->res_msg_words * sizeof(*ctx->res_msg), s));
+        ctx->res_stamp = 0;
+    }
+    std::lock_guard<std::mutex> one(res_mutex());
+    if (ctx->prof) HIPCHK(hipEventRecord(ctx->pev[0], s));
+    launch_resident2d<T>(ctx->g, shape, ctx->res_lists + shape * kResMost, ctx->res_count[shape], v.r,
+                         v.x, v.dinv, v.a, v.c, v.K, ctx->res_part, ctx->res_msg, ctx->res_stamp,
+                         set_bb, ctx->sc, s);
+    if (ctx->prof) HIPCHK(hipEventRecord(ctx->pev[1], s));
+    HIPCHK(hipGetLastError());
+    int rc = read_scalars(ctx, 0, out);
+    if (rc) return rc;
+    *gave_up = out->aborted != 0 || out->done == 0;
+    if (*gave_up) {
+        ctx->res_off = true;
+        return VFS_OK;
+    }
+    ctx->res_stamp += (unsigned)out->iter + 4u;
+    if (ctx->prof) {   // average over the iterations of the run
+        ctx->prof_apply_ms += elapsed(ctx->pev[0], ctx->pev[1]) / std::max(1, out->iter + 1);
+        ++ctx->prof_apply_n;
+    }
+    return VFS_OK;
 }
 
 // 2D PCG with one fused launch per iteration (k_fused2d.hip) in FP32 over the
@@ -354,16 +426,25 @@ int zero_dirs(vfs_ctx* ctx, bool f32) {
 // FP64 solve of A x = b (padded device vectors); fills stats.
 int solve_fp64(vfs_ctx* ctx, const double* b, double* x) {
     const Geo& g = ctx->g;
-    if (int rc0 = zero_dirs(ctx, false)) return rc0;
     const Parts P = parts(ctx);
     Vecs<double> v{x, ctx->r, ctx->p0, ctx->p1, ctx->q, nullptr, ctx->a, ctx->c, ctx->K,
                    ctx->dinv};
+    const int shape = g.dim == 2 ? res2d_shape(ctx, 8) : -1;
+    if (shape < 0)
+        if (int rc0 = zero_dirs(ctx, false)) return rc0;
+    auto run = [&](bool set_bb, int most, Scalars* out, bool* gave_up) {
+        *gave_up = false;
+        return shape < 0 ? run_chunks<double>(ctx, v, set_bb, out)
+                         : run_resident2d<double>(ctx, shape, v, set_bb, most, out, gave_up);
+    };
     launch_cg_init<double>(g, b, x, ctx->r, ctx->dinv, nullptr, ctx->tol, ctx->max_iter, ctx->sc,
                            P.B, ctx->stream);
     HIPCHK(hipGetLastError());
     Scalars s{};
-    int rc = run_chunks<double>(ctx, v, true, &s);
+    bool gave_up = false;
+    int rc = run(true, ctx->max_iter, &s, &gave_up);
     if (rc) return rc;
+    if (gave_up) return solve_fp64(ctx, b, x);   // from the start, by launches
     int total = s.iter, outer = 0, status = VFS_OK;
     const double bb = s.bb;
     ctx->stats.rel_residual_start = bb > 0.0 ? 1.0 : 0.0;
@@ -386,8 +467,9 @@ int solve_fp64(vfs_ctx* ctx, const double* b, double* x) {
         launch_cg_restart<double>(g, ctx->r, ctx->dinv, nullptr, ctx->sc, P.B,
                                   ctx->max_iter - total, ctx->stream);
         HIPCHK(hipGetLastError());
-        rc = run_chunks<double>(ctx, v, false, &s);
+        rc = run(false, ctx->max_iter - total, &s, &gave_up);
         if (rc) return rc;
+        if (gave_up) return solve_fp64(ctx, b, x);
         total += s.iter;
     }
     ctx->stats.iterations = total;
@@ -453,11 +535,20 @@ int solve_mixed(vfs_ctx* ctx, const double* b, double* x) {
                               ctx->max_iter - total, ctx->sc, P.B, ctx->stream);
         HIPCHK(hipGetLastError());
         Scalars s{};
-        if (learned)
+        bool gave_up = false;
+        if (learned) {
             rc = run_chunks_fcg(ctx, v, true, &s);
-        else if (g.dim == 2)
-            rc = run_chunks_fused(ctx, true, &s);
-        else
+        } else if (g.dim == 2) {
+            const int shape = res2d_shape(ctx, 4);
+            if (shape >= 0)
+                rc = run_resident2d<float>(ctx, shape, v, true, ctx->max_iter - total, &s, &gave_up);
+            if (!rc && gave_up) {   // again by launches, from the same residual
+                launch_cg_init<float>(g, ctx->r32, ctx->x32, ctx->r32, ctx->dinv32, nullptr, tol_in,
+                                      ctx->max_iter - total, ctx->sc, P.B, ctx->stream);
+                HIPCHK(hipGetLastError());
+            }
+            if (!rc && (shape < 0 || gave_up)) rc = run_chunks_fused(ctx, true, &s);
+        } else
             rc = run_chunks_fused3d(ctx, true, &s);
         if (rc) return rc;
         total += s.iter;
@@ -662,10 +753,14 @@ int assemble_internal(vfs_ctx* ctx, double dt) {
     }
     if (g.dim == 2) {
         launch_tiles2d(g, ctx->a, ctx->tile_flags, ctx->tile_list, ctx->tile_count, s);
-        HIPCHK(hipMemcpyAsync(ctx->tile_count_host, ctx->tile_count, sizeof(int),
+        if (ctx->res_part)
+            launch_res2d_lists(g, ctx->a, ctx->res_flags, ctx->res_lists, kResMost,
+                               ctx->tile_count + 1, s);
+        HIPCHK(hipMemcpyAsync(ctx->tile_count_host, ctx->tile_count, (1 + kResShapes) * sizeof(int),
                               hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         ctx->tiles2d = *ctx->tile_count_host;
+        for (int q = 0; q < kResShapes; ++q) ctx->res_count[q] = ctx->tile_count_host[1 + q];
         ctx->stats.n_tile_samples = (int64_t)ctx->tiles2d * tile2d_anchors() * g.nsamp();
     }
     if (g.dim == 3) {
@@ -826,7 +921,8 @@ int vfs_destroy(vfs_ctx* ctx) {
                     ctx->p032,  ctx->p132,  ctx->q32,  ctx->z32,    ctx->partials, ctx->counter,
                     ctx->sc,    ctx->flag,  ctx->stage, ctx->netvec, ctx->netpart, ctx->netcoef,
                     ctx->f32b,  ctx->fpart, ctx->ybc, ctx->adv_a, ctx->adv_b, ctx->adv_ka,
-                    ctx->adv_kb, ctx->phi_tmp, ctx->ead32};
+                    ctx->adv_kb, ctx->phi_tmp, ctx->ead32, ctx->res_part, ctx->res_msg,
+                    ctx->res_flags, ctx->res_lists};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
     if (ctx->net_owned) (void)vfs_unet_destroy(ctx->net_owned);
@@ -927,7 +1023,7 @@ int vfs_create(vfs_ctx** out, int dim, int nx, int ny, int nz, double h, const d
         const long long nt = (long long)ctx->tiles.ntx * ctx->tiles.nty * ctx->tiles.ntz;
         ALLOC(ctx->tile_flags, nt);
         ALLOC(ctx->tile_list, nt);
-        ALLOC(ctx->tile_count, 4);
+        ALLOC(ctx->tile_count, 8);
         fused_tile_dims(g, ctx->ftiles.ntx, ctx->ftiles.nty, ctx->ftiles.ntz);
         const long long nf = (long long)ctx->ftiles.ntx * ctx->ftiles.nty * ctx->ftiles.ntz;
         ALLOC(ctx->ftile_flags, nf);
@@ -936,14 +1032,26 @@ int vfs_create(vfs_ctx** out, int dim, int nx, int ny, int nz, double h, const d
     } else {
         ALLOC(ctx->tile_flags, nt2);
         ALLOC(ctx->tile_list, nt2);
-        ALLOC(ctx->tile_count, 4);
+        ALLOC(ctx->tile_count, 8);
+        // the resident solve holds at most 256 tiles of 62 x 64 anchors, all of
+        // them active; a grid of more than twice as many is not expected to fit
+        if (NP <= 2LL * kResMost * 62 * 64) {
+            int ltx, lty;
+            res2d_lattice(g, ltx, lty);
+            for (int q = 0; q < kResShapes; ++q)
+                ctx->res_msg_words = std::max(ctx->res_msg_words, res2d_words(g, q));
+            ALLOC(ctx->res_part, 2 * kResMost * 16);
+            ALLOC(ctx->res_msg, ctx->res_msg_words);
+            ALLOC(ctx->res_flags, (long long)ltx * lty);
+            ALLOC(ctx->res_lists, kResShapes * kResMost);
+        }
     }
 #undef ALLOC
     if (hipHostMalloc((void**)&ctx->sc_host, 4 * sizeof(Scalars), hipHostMallocDefault) !=
             hipSuccess ||
         hipHostMalloc((void**)&ctx->flag_host, 4 * sizeof(int), hipHostMallocDefault) !=
             hipSuccess ||
-        hipHostMalloc((void**)&ctx->tile_count_host, 4 * sizeof(int), hipHostMallocDefault) !=
+        hipHostMalloc((void**)&ctx->tile_count_host, 8 * sizeof(int), hipHostMallocDefault) !=
             hipSuccess) {
         vfs_destroy(ctx);
         return fail(nullptr, VFS_ENOMEM, "hipHostMalloc failed");

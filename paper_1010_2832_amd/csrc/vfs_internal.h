@@ -25,6 +25,12 @@
 
 namespace vfs {
 
+// Words through which the workgroups of a resident solve exchange values
+// (vfs_resident.h), and its tile shapes and largest number of workgroups.
+using LLWordBuf = unsigned long long*;
+constexpr int kResShapes = 4;
+constexpr int kResMost = 256;
+
 constexpr int kFront = 32;   // elements before the body (128-byte rows, see make_geo)
 // 3D kernels run at most this many workgroups, each looping over tiles, so
 // that the partial sums a consumer must read stay few.
@@ -105,7 +111,8 @@ struct Scalars {
     int flexible;
     long long n_active;
     int fallbacks;      // flexible CG: iterations that used the Jacobi direction
-    int pad[3];
+    int aborted;        // resident solve: a wait was given up (the result is void)
+    int pad[2];
     double pqh[8];      // p.Ap of iteration k in slot k & 7 (truncated flexible CG)
 };
 
@@ -264,6 +271,17 @@ struct vfs_ctx {
     int* tile_count_host = nullptr;  // pinned
     vfs::Tiles tiles{nullptr, 0, 0, 0, 0};
     int tiles2d = 0;                 // 2D: active tiles of the fused CG (in tile_list)
+    // resident CG: exchange buffers, tile lists by shape and the stamp the next
+    // solve starts from (null buffers: the grid is too large for it); res_off
+    // is set when a wait was given up and keeps this context to the launched
+    // iteration
+    vfs::LLWordBuf res_part = nullptr, res_msg = nullptr;
+    long long res_msg_words = 0;
+    int* res_flags = nullptr;
+    int* res_lists = nullptr;
+    int res_count[vfs::kResShapes] = {};
+    unsigned res_stamp = 0;
+    bool res_off = false;
     // 3D: work tiles of the fused iteration holding an active tile, and one
     // byte per kRow3X-anchor row (x part, y, z) with bit s set if sample slice
     // s has an active sample in the row
@@ -444,6 +462,17 @@ template <typename T>
 void launch_fused2d(const Geo& g, bool init, const FusedVecs& v, const T* dinv, const T* a,
                     const T* c, const T* K, const int* tiles, int count, const RedArgs& ra,
                     hipStream_t s);
+// resident 2D CG (k_resident2d.hip): a whole solve in one launch.  Tile shape
+// q < kResShapes has 62 x 8 2^q anchors (FP64: q <= 2); lists holds one list
+// of `cap` tiles per shape
+void res2d_lattice(const Geo& g, int& ntx, int& nty);
+long long res2d_words(const Geo& g, int shape);
+void launch_res2d_lists(const Geo& g, const double* a, int* flags, int* lists, int cap, int* counts,
+                        hipStream_t s);
+template <typename T>
+void launch_resident2d(const Geo& g, int shape, const int* tiles, int count, const T* r, T* x,
+                       const T* dinv, const T* a, const T* c, const T* K, LLWordBuf part,
+                       LLWordBuf msg, unsigned stamp, bool set_bb, Scalars* sc, hipStream_t s);
 int update_blocks(const Geo& g, const Tiles& tl);
 template <typename T>
 void launch_apply(const Geo& g, const Tiles& tl, int mode, bool zin, const T* r, const T* zsrc,
