@@ -14,6 +14,35 @@
 
 using namespace vfs;
 
+namespace vfs {
+
+// Most workgroups a resident solve may have: they wait for each other, so all
+// of them must fit on the chip at once, one per compute unit.
+int res_most() {
+    static int cache[16] = {};
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+    int& c = cache[dev & 15];
+    if (c == 0) {
+        if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            ncu < 1)
+            ncu = 1;
+        c = std::min(ncu, kResMost);
+    }
+    return c;
+}
+
+// One resident solve at a time on a device: two of them could each hold half
+// of the chip and wait for the other half.
+std::mutex& res_mutex() {
+    static std::mutex m[16];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+    return m[dev & 15];
+}
+
+}  // namespace vfs
+
 namespace {
 
 thread_local std::string g_create_err;
@@ -176,31 +205,6 @@ int run_chunks(vfs_ctx* ctx, Vecs<T>& v, bool set_bb, Scalars* out) {
         if (out->done) return VFS_OK;
         chunk = std::min(chunk * 2, 256);
     }
-}
-
-// Most workgroups a resident solve may have: they wait for each other, so all
-// of them must fit on the chip at once, one per compute unit.
-int res_most() {
-    static int cache[16] = {};
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    int& c = cache[dev & 15];
-    if (c == 0) {
-        if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            ncu < 1)
-            ncu = 1;
-        c = std::min(ncu, kResMost);
-    }
-    return c;
-}
-
-// One resident solve at a time on a device: two of them could each hold half
-// of the chip and wait for the other half.
-std::mutex& res_mutex() {
-    static std::mutex m[16];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    return m[dev & 15];
 }
 
 // Tile shape of the resident 2D solve, or -1 for the launched iteration.  The
@@ -754,13 +758,14 @@ int assemble_internal(vfs_ctx* ctx, double dt) {
     if (g.dim == 2) {
         launch_tiles2d(g, ctx->a, ctx->tile_flags, ctx->tile_list, ctx->tile_count, s);
         if (ctx->res_part)
-            launch_res2d_lists(g, ctx->a, ctx->res_flags, ctx->res_lists, kResMost,
+            launch_res2d_lists(g, ctx->a, ctx->res_flags, ctx->res_lists, ctx->res_list64,
                                ctx->tile_count + 1, s);
-        HIPCHK(hipMemcpyAsync(ctx->tile_count_host, ctx->tile_count, (1 + kResShapes) * sizeof(int),
+        HIPCHK(hipMemcpyAsync(ctx->tile_count_host, ctx->tile_count, (2 + kResShapes) * sizeof(int),
                               hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         ctx->tiles2d = *ctx->tile_count_host;
         for (int q = 0; q < kResShapes; ++q) ctx->res_count[q] = ctx->tile_count_host[1 + q];
+        ctx->res_count64 = ctx->tile_count_host[1 + kResShapes];
         ctx->stats.n_tile_samples = (int64_t)ctx->tiles2d * tile2d_anchors() * g.nsamp();
     }
     if (g.dim == 3) {
@@ -921,8 +926,7 @@ int vfs_destroy(vfs_ctx* ctx) {
                     ctx->p032,  ctx->p132,  ctx->q32,  ctx->z32,    ctx->partials, ctx->counter,
                     ctx->sc,    ctx->flag,  ctx->stage, ctx->netvec, ctx->netpart, ctx->netcoef,
                     ctx->f32b,  ctx->fpart, ctx->ybc, ctx->adv_a, ctx->adv_b, ctx->adv_ka,
-                    ctx->adv_kb, ctx->phi_tmp, ctx->ead32, ctx->res_part, ctx->res_msg,
-                    ctx->res_flags, ctx->res_lists};
+                    ctx->adv_kb, ctx->phi_tmp, ctx->ead32, ctx->res_part};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
     if (ctx->net_owned) (void)vfs_unet_destroy(ctx->net_owned);
@@ -1040,10 +1044,15 @@ int vfs_create(vfs_ctx** out, int dim, int nx, int ny, int nz, double h, const d
             res2d_lattice(g, ltx, lty);
             for (int q = 0; q < kResShapes; ++q)
                 ctx->res_msg_words = std::max(ctx->res_msg_words, res2d_words(g, q));
-            ALLOC(ctx->res_part, 2 * kResMost * 16);
-            ALLOC(ctx->res_msg, ctx->res_msg_words);
-            ALLOC(ctx->res_flags, (long long)ltx * lty);
-            ALLOC(ctx->res_lists, kResShapes * kResMost);
+            // one allocation: words, messages, partial sums, then lists and flags
+            const long long part = 2 * kResMost * 16, lists = kResShapes * kResMost;
+            const long long t64 = res2d_tiles64(g), tl = (long long)ltx * lty;
+            ALLOC(ctx->res_part, part + ctx->res_msg_words + t64 + (lists + t64 + tl + t64 + 1) / 2);
+            ctx->res_msg = ctx->res_part + part;
+            ctx->res_part64 = (double*)(ctx->res_msg + ctx->res_msg_words);
+            ctx->res_lists = (int*)(ctx->res_part64 + t64);
+            ctx->res_list64 = ctx->res_lists + lists;
+            ctx->res_flags = ctx->res_list64 + t64;
         }
     }
 #undef ALLOC

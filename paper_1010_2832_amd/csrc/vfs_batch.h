@@ -46,7 +46,29 @@ struct BState {
     int iters_total;  // iterations over all passes
     int passes;
     unsigned long long t_start, t_done;   // device wall clock
+    unsigned stamp;   // resident solve: last stamp used
+    int pad;
 };
+
+// Resident solve of a batch (k_resident2d.hip).  Workgroups form groups of
+// consecutive numbers; a group takes the problems of its list one after the
+// other, a problem using as many of its workgroups as it has tiles.
+struct BResProb {
+    const int* tiles;
+    int ntx, W;
+    LLWordBuf part, msg;
+    long long slot;
+    unsigned stamp;
+    int ntx64, nt64;   // 64 x 8 tiles of the FP64 residual and its partial sums
+    const int* tiles64;
+    double* part64;
+};
+struct BResWg {
+    int group0;        // first workgroup of this one's group
+    int list0, nlist;  // the group's problems
+    int group;
+};
+constexpr int kBResShapes = 3;   // 62 x 8, 62 x 16, 62 x 32 anchors a workgroup
 
 // Grid barrier: workgroup b arrives at group counter b % kBarGroups, the last
 // arrival of each group at the top counter, the last of those advances the
@@ -93,6 +115,12 @@ void launch_batch_zero(const BatchArgs& A, hipStream_t s);
 void launch_batch_tile_flags(const BProb* prob, const int* full_prob, int nfull, int bx, int by,
                              int* flags, hipStream_t s);
 void launch_batch_reset_ctl(BatchCtl* ctl, hipStream_t s);
+// zero solution, fresh state and start time of every problem, abort flag and
+// beats cleared
+void launch_batch_resident_start(const BatchArgs& A, unsigned* beats, hipStream_t s);
+// every problem's whole mixed solve (A.prob, A.state, A.ctl, tolerance and limits)
+void launch_batch_resident(int shape, const BatchArgs& A, const BResProb* rp, const BResWg* wg,
+                           const int* list, unsigned* beats, int grid, hipStream_t s);
 
 // single-problem pieces reused by the batch (vfs_api.hip)
 int ctx_assemble(vfs_ctx* ctx, double dt);

@@ -1,9 +1,11 @@
 // C ABI of the batched 2D solver: many independent steps of different grid
-// sizes whose CG solves run in one persistent launch per refinement pass.
-// Each pass (reset, persistent FP32 PCG over all problems, x64 update, FP64
-// residual, per-problem decision) is captured once in a hipGraph and
-// replayed.  Assembly and velocity recovery reuse the single-problem
-// kernels on each problem's own context.
+// sizes whose mixed solves, refinement included, run in one launch that is
+// captured once in a hipGraph and replayed.  Where every problem fits on the
+// chip (at most one tile a compute unit) groups of workgroups keep one problem
+// each in their registers until it is solved (k_batch_resident); otherwise one
+// persistent kernel walks all tiles of all problems (k_batch_pcg).  Assembly
+// and velocity recovery reuse the single-problem kernels on each problem's own
+// context.
 #include <algorithm>
 #include <cmath>
 #include <string>
@@ -47,7 +49,15 @@ struct vfs_batch {
     std::vector<BProb> h_prob;
     BState* h_state = nullptr;   // pinned
     BatchCtl* h_ctl = nullptr;   // pinned
-    // graph of one refinement pass
+    // resident solve: device arrays (problems, workgroups, lists), their staging
+    // copy, the tile shape of this step (-1: the persistent kernel) and the one
+    // the captured graph has; res_off: a resident solve was given up
+    char* d_res = nullptr;
+    char* h_res = nullptr;
+    unsigned* d_beats = nullptr;
+    int res_shape = -1, graph_shape = -1, res_groups = 0;
+    bool res_off = false;
+    // graph of the whole solve
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     bool graph_ok = false;
@@ -237,9 +247,148 @@ int build_items(vfs_batch* b) {
     return VFS_OK;
 }
 
-// the whole solve: x64 = 0, r64 = b, |b|, then the persistent kernel
-// (inner FP32 CG, FP64 residual and refinement for every problem)
+size_t res_bytes(int n) {
+    return sizeof(BResProb) * n + sizeof(BResWg) * kResMost + sizeof(int) * n;
+}
+BResWg* res_wgs(char* base, int n) { return (BResWg*)(base + sizeof(BResProb) * n); }
+int* res_list(char* base, int n) { return (int*)(res_wgs(base, n) + kResMost); }
+
+// Groups of workgroups for problems of widths w (tiles) and lengths t (expected
+// times): widest first, each problem goes to the narrowest group that still
+// has the time before `deadline`, or opens a group of its own width.  False if
+// that takes more than `most` workgroups.
+struct ResGroup {
+    int width = 0;
+    double load = 0.0;
+    std::vector<int> problems;
+};
+bool res_pack(const std::vector<int>& order, const std::vector<int>& w, const std::vector<double>& t,
+              double deadline, int most, std::vector<ResGroup>* out) {
+    out->clear();
+    int used = 0;
+    for (int p : order) {
+        ResGroup* best = nullptr;
+        for (ResGroup& g : *out)
+            if (g.width >= w[p] && g.load + t[p] <= deadline && (!best || g.width < best->width))
+                best = &g;
+        if (!best) {
+            if (t[p] > deadline || used + w[p] > most) return false;
+            used += w[p];
+            out->push_back(ResGroup{});
+            best = &out->back();
+            best->width = w[p];
+        }
+        best->load += t[p];
+        best->problems.push_back(p);
+    }
+    return true;
+}
+
+// Chooses the tile shape and the groups of the resident solve of the assembled
+// step and uploads them; res_shape = -1 where some problem has more tiles than
+// the chip has compute units in every shape.  An iteration takes about 2.7, 3.2
+// and 4.4 us with 62 x 8, 62 x 16 and 62 x 32 anchors a workgroup, plus 2 ns
+// for each workgroup that takes part (measured on single problems), and CG
+// iterations grow with the grid's side: large tiles leave more problems side by
+// side, small ones shorten the longest.
+int plan_resident(vfs_batch* b) {
+    b->res_shape = -1;
+    if (b->res_off) return VFS_OK;
+    const int most = res_most();
+    const double cost[kBResShapes] = {2.7, 3.2, 4.4};
+    std::vector<ResGroup> best, trial;
+    double best_time = 0.0;
+    for (int q = 0; q < kBResShapes; ++q) {
+        std::vector<int> order, w(b->n);
+        std::vector<double> t(b->n);
+        double area = 0.0, longest = 0.0, sum = 0.0;
+        bool fits = true;
+        for (int p = 0; p < b->n; ++p) {
+            const vfs_ctx* c = b->ctx[p];
+            w[p] = c->res_part ? c->res_count[q] : most + 1;
+            if (w[p] > most) fits = false;
+            if (w[p] <= 0) continue;   // nothing to solve
+            t[p] = std::max(c->g.nx, c->g.ny) * (cost[q] + 0.002 * w[p]);
+            area += t[p] * w[p];
+            longest = std::max(longest, t[p]);
+            sum += t[p];
+            order.push_back(p);
+        }
+        if (!fits) continue;
+        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return w[x] > w[y]; });
+        double lo = std::max(longest, area / most), hi = std::max(sum, lo);
+        if (!res_pack(order, w, t, hi, most, &trial)) continue;
+        std::vector<ResGroup> found = trial;
+        for (int it = 0; it < 12; ++it) {
+            const double mid = 0.5 * (lo + hi);
+            if (res_pack(order, w, t, mid, most, &trial)) {
+                found = trial;
+                hi = mid;
+            } else {
+                lo = mid;
+            }
+        }
+        if (b->res_shape < 0 || hi < best_time) {
+            best = found;
+            best_time = hi;
+            b->res_shape = q;
+        }
+    }
+    if (b->res_shape < 0) return VFS_OK;
+    const int n = b->n, q = b->res_shape;
+    if (!b->d_res) {
+        BCHK(hipMalloc((void**)&b->d_res, res_bytes(n)));
+        BCHK(hipHostMalloc((void**)&b->h_res, res_bytes(n), hipHostMallocDefault));
+        BCHK(hipMalloc((void**)&b->d_beats, sizeof(unsigned) * kResMost));
+    }
+    BResProb* rp = (BResProb*)b->h_res;
+    BResWg* wg = res_wgs(b->h_res, n);
+    int* list = res_list(b->h_res, n);
+    for (int p = 0; p < n; ++p) {
+        vfs_ctx* c = b->ctx[p];
+        if (c->res_stamp > 0x7fffffffu) {   // far from wrapping within a solve
+            BCHK(hipMemsetAsync(c->res_part, 0, 2 * kResMost * 16 * sizeof(*c->res_part), b->stream));
+            BCHK(hipMemsetAsync(c->res_msg, 0, c->res_msg_words * sizeof(*c->res_msg), b->stream));
+            c->res_stamp = 0;
+        }
+        int ntx = 0, nty = 0;
+        if (c->res_part) res2d_lattice(c->g, ntx, nty);
+        rp[p] = BResProb{c->res_lists + q * kResMost,
+                         ntx,
+                         c->res_count[q],
+                         c->res_part,
+                         c->res_msg,
+                         res2d_words(c->g, q) / 4,
+                         c->res_stamp,
+                         (c->g.nx + 64) / 64,
+                         c->res_count64,
+                         c->res_list64,
+                         c->res_part64};
+    }
+    for (int i = 0; i < kResMost; ++i) wg[i] = BResWg{0, 0, 0, 0};
+    int at = 0, lat = 0, gi = 0;
+    for (const ResGroup& g : best) {
+        for (int i = 0; i < g.width; ++i)
+            wg[at + i] = BResWg{at, lat, (int)g.problems.size(), gi};
+        for (int p : g.problems) list[lat++] = p;
+        at += g.width;
+        ++gi;
+    }
+    b->res_groups = gi;
+    BCHK(hipMemcpyAsync(b->d_res, b->h_res, res_bytes(n), hipMemcpyHostToDevice, b->stream));
+    return VFS_OK;
+}
+
+// the whole solve: x64 = 0, r64 = b, |b|, then every problem's FP32 CG, FP64
+// residual and refinement, resident or in the persistent kernel
 void enqueue_solve(vfs_batch* b, hipStream_t s) {
+    if (b->res_shape >= 0) {
+        const BatchArgs A = args(b, 0);
+        launch_batch_resident_start(A, b->d_beats, s);
+        launch_batch_resident(b->res_shape, A, (const BResProb*)b->d_res, res_wgs(b->d_res, b->n),
+                              res_list(b->d_res, b->n), b->d_beats, res_most(), s);
+        return;
+    }
     const BatchArgs A0 = args(b, 1);
     launch_batch_zero(A0, s);
     launch_batch_resid(b->variant, A0, b->grid, s);
@@ -250,7 +399,16 @@ void enqueue_solve(vfs_batch* b, hipStream_t s) {
 }
 
 int ensure_graph(vfs_batch* b) {
-    if (b->graph_ok) return VFS_OK;
+    if (b->graph_ok && b->graph_shape == b->res_shape) return VFS_OK;
+    if (b->gexec) {
+        (void)hipGraphExecDestroy(b->gexec);
+        b->gexec = nullptr;
+    }
+    if (b->graph) {
+        (void)hipGraphDestroy(b->graph);
+        b->graph = nullptr;
+    }
+    b->graph_ok = false;
     BCHK(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
     enqueue_solve(b, b->stream);
     hipGraph_t g = nullptr;
@@ -258,6 +416,7 @@ int ensure_graph(vfs_batch* b) {
     b->graph = g;
     BCHK(hipGraphInstantiate(&b->gexec, g, nullptr, nullptr, 0));
     b->graph_ok = true;
+    b->graph_shape = b->res_shape;
     return VFS_OK;
 }
 
@@ -266,12 +425,15 @@ int read_state(vfs_batch* b) {
                         b->stream));
     BCHK(hipMemcpyAsync(b->h_ctl, b->d_ctl, sizeof(BatchCtl), hipMemcpyDeviceToHost, b->stream));
     BCHK(hipStreamSynchronize(b->stream));
-    if (b->h_ctl->abort) return bfail(b, VFS_EHIP, "batched grid barrier timed out (aborted)");
+    if (b->h_ctl->abort && b->res_shape < 0)
+        return bfail(b, VFS_EHIP, "batched grid barrier timed out (aborted)");
     return VFS_OK;
 }
 
 // solve phase of a step on assembled problems (one graph launch); returns status
 int solve_all(vfs_batch* b, bool use_graph) {
+    std::unique_lock<std::mutex> one(res_mutex(), std::defer_lock);
+    if (b->res_shape >= 0) one.lock();
     if (use_graph) {
         int rc = ensure_graph(b);
         if (rc) return rc;
@@ -282,6 +444,16 @@ int solve_all(vfs_batch* b, bool use_graph) {
     BCHK(hipGetLastError());
     int rc = read_state(b);
     if (rc) return rc;
+    if (b->res_shape >= 0) {
+        if (b->h_ctl->abort) {   // again, by the persistent kernel
+            b->res_off = true;
+            b->res_shape = -1;
+            one.unlock();
+            return solve_all(b, use_graph);
+        }
+        for (int p = 0; p < b->n; ++p)
+            if (b->h_state[p].stamp) b->ctx[p]->res_stamp = b->h_state[p].stamp + 4u;
+    }
     int status = VFS_OK;
     for (int p = 0; p < b->n; ++p)
         if (b->h_state[p].rel > b->tol) status = VFS_ENOTCONV;
@@ -316,11 +488,13 @@ int vfs_batch_destroy(vfs_batch* b) {
     if (b->graph) (void)hipGraphDestroy(b->graph);
     for (auto* c : b->ctx) vfs_destroy(c);
     void* bufs[] = {b->d_prob,      b->d_state,   b->d_ctl,   b->d_item_prob, b->d_item_tile,
-                    b->d_full_prob, b->d_flags,   b->d_nlive, b->d_part};
+                    b->d_full_prob, b->d_flags,   b->d_nlive, b->d_part,      b->d_res,
+                    b->d_beats};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
     if (b->h_flags) (void)hipHostFree(b->h_flags);
     if (b->h_state) (void)hipHostFree(b->h_state);
+    if (b->h_res) (void)hipHostFree(b->h_res);
     if (b->h_ctl) (void)hipHostFree(b->h_ctl);
     for (auto& e : b->ev)
         if (e) (void)hipEventDestroy(e);
@@ -457,6 +631,7 @@ int vfs_batch_step(vfs_batch* b, double dt) {
         if (rc) return bfail(b, rc, "problem " + std::to_string(p) + ": " + vfs_last_error(b->ctx[p]));
     }
     int rc = compact_items(b);
+    if (!rc) rc = plan_resident(b);
     if (rc) return rc;
     BCHK(hipEventRecord(b->ev[1], s));
     const int status = solve_all(b, true);
@@ -474,7 +649,7 @@ int vfs_batch_step(vfs_batch* b, double dt) {
     S.n_problems = b->n;
     S.variant = b->variant;
     S.blocks_per_cu = b->bpc_used;
-    S.grid = b->grid;
+    S.grid = b->res_shape >= 0 ? res_most() : b->grid;
     S.graph_used = b->graph_ok ? 1 : 0;
     S.status = status;
     S.t_assemble_ms = ev_ms(b->ev[0], b->ev[1]);
@@ -569,6 +744,7 @@ int vfs_batch_time_variant(vfs_batch* b, int variant, int blocks_per_cu, int ite
     const int v0 = b->variant, c0 = b->blocks_per_cu;
     int rc = vfs_batch_set_tiles(b, variant, blocks_per_cu);
     if (rc) return rc;
+    b->res_shape = -1;   // the probe times the persistent kernel
     const int mip = b->max_iter_pass, mp = b->max_passes;
     b->max_iter_pass = iterations;
     b->max_passes = 1;

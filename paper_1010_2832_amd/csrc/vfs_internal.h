@@ -19,6 +19,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <mutex>
 #include <string>
 
 #include "../../include/vfstokes.h"
@@ -280,6 +281,9 @@ struct vfs_ctx {
     int* res_flags = nullptr;
     int* res_lists = nullptr;
     int res_count[vfs::kResShapes] = {};
+    int* res_list64 = nullptr;       // 64 x 8 tiles, their partial sums
+    double* res_part64 = nullptr;
+    int res_count64 = 0;
     unsigned res_stamp = 0;
     bool res_off = false;
     // 3D: work tiles of the fused iteration holding an active tile, and one
@@ -315,6 +319,11 @@ struct vfs_ctx {
 };
 
 namespace vfs {
+
+// resident solves (vfs_api.hip): the workgroups one may have on this device,
+// and the lock held while one runs
+int res_most();
+std::mutex& res_mutex();
 
 // error message of a call without a context (read by vfs_last_error(NULL))
 int fail_global(int code, const std::string& msg);
@@ -463,11 +472,13 @@ void launch_fused2d(const Geo& g, bool init, const FusedVecs& v, const T* dinv, 
                     const T* c, const T* K, const int* tiles, int count, const RedArgs& ra,
                     hipStream_t s);
 // resident 2D CG (k_resident2d.hip): a whole solve in one launch.  Tile shape
-// q < kResShapes has 62 x 8 2^q anchors (FP64: q <= 2); lists holds one list
-// of `cap` tiles per shape
+// q < kResShapes has 62 x 8 2^q anchors (FP64: q <= 2)
 void res2d_lattice(const Geo& g, int& ntx, int& nty);
 long long res2d_words(const Geo& g, int shape);
-void launch_res2d_lists(const Geo& g, const double* a, int* flags, int* lists, int cap, int* counts,
+// tiles of 64 x 8 anchors; lists and counts (one more than shapes) of the tiles
+// holding an active sample
+int res2d_tiles64(const Geo& g);
+void launch_res2d_lists(const Geo& g, const double* a, int* flags, int* lists, int* list64, int* counts,
                         hipStream_t s);
 template <typename T>
 void launch_resident2d(const Geo& g, int shape, const int* tiles, int count, const T* r, T* x,

@@ -90,14 +90,21 @@ __device__ __forceinline__ void ll_first_wait(int workgroups) {
 }
 
 // Patience of one wait: true when it has to end (abort flag up, or the
-// deadline, which raises it).
+// deadline, which raises it).  A workgroup may wait for others that are still
+// busy with an earlier solve: while `beat` moves, the clock starts again.
 struct LLPatience {
     long long t0 = 0;
     int spin = 0;
-    __device__ __forceinline__ bool over(int* abort_flag) {
+    unsigned last = 0;
+    __device__ __forceinline__ bool over(int* abort_flag, const unsigned* beat) {
         if ((++spin & 63) != 0) return false;
         if (__hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return true;
         const long long t = wall_clock64();
+        if (beat) {
+            const unsigned b = __hip_atomic_load(beat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (b != last) t0 = 0;
+            last = b;
+        }
         if (t0 == 0) {
             t0 = t;
             return false;

@@ -63,3 +63,27 @@ def test_resident2d_repeats_and_cap():
     x1 = ctx.vfs_solve(b)
     assert ctx.vfs_get_stats()["iterations"] == its
     assert np.array_equal(x0, x1)
+
+
+def test_resident_batch_keeps_the_iterates_of_the_persistent_kernel():
+    """A batch that fits on the chip is solved resident; with one problem too
+    large for it (more tiles than compute units) the persistent kernel runs.
+    Both take the same steps for the problems they share: equal iteration
+    counts, equal solutions."""
+    from paper_1010_2832_amd import vfstokes as V
+    sizes = [24, 61, 62, 63, 130, 257, 33]
+    probs = [cases.drop2d(n, 300 + q) for q, n in enumerate(sizes)]
+    big = cases.drop2d(1700, 5)
+    out = []
+    for extra in ([], [big]):
+        b = V.batch_from_cases(probs + extra, tol=1e-9)
+        b.vfs_batch_step(probs[0]["dt"])
+        out.append([(b.vfs_batch_get_problem(i)["iterations"], b.vfs_batch_get_solution(i))
+                    for i in range(len(sizes))])
+        b.close()
+    for n, (i0, x0), (i1, x1) in zip(sizes, *out):
+        print(f"n={n}: {i0} and {i1} iterations", flush=True)
+        assert i0 == i1
+        # the sums differ in order only; their rounding to FP32 may flip once in
+        # millions of iterations, so equality is asked for, not a tolerance
+        assert np.array_equal(x0, x1)
