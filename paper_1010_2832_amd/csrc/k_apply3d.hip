@@ -1408,12 +1408,16 @@ int fused3d_grid(int count) {
     return std::max(1, std::min(std::min(count, kMaxTileBlocks), c));
 }
 
+bool fused3d_pair(const Tiles& ft) { return ft.split >= VFS_FUSED3_PAIR_SPLIT; }
+
+bool fused3d_folds(const Geo& g) { return fused_fold(g.nx); }
+
 void launch_fused3d(const Geo& g, const Tiles& ft, bool init, const FusedVecs& v,
                     const float* ead, const float* a, const float* c, const float* K,
                     const RowBits* rows, unsigned* wq, const RedArgs& ra, hipStream_t s) {
     if (ft.count <= 0) return;
     const dim3 gs(fused3d_grid(ft.items()));
-    if (ft.split >= VFS_FUSED3_PAIR_SPLIT) {
+    if (fused3d_pair(ft)) {
         if (init)
             hipLaunchKernelGGL((k_fused3d<float, true, 2>), gs, dim3(2 * FNA), 0, s, g, ft, v,
                                ead, a, c, K, rows, wq, ra);

@@ -219,12 +219,25 @@ int res2d_shape(const vfs_ctx* ctx, int word) {
     return -1;
 }
 
+// Brick shape of the resident 3D solve, or -1 (FP64 has the first alone).
+int res3d_shape(const vfs_ctx* ctx, int word) {
+    if (!ctx->res_part || ctx->res_off) return -1;
+    const int most = res_most();
+    for (int q = 0; q < (word == 4 ? kRes3dShapes : 1); ++q)
+        if (ctx->res_count[q] > 0 && ctx->res_count[q] <= most) return q;
+    return -1;
+}
+
+int res_shape(const vfs_ctx* ctx, int word) {
+    return ctx->g.dim == 2 ? res2d_shape(ctx, word) : res3d_shape(ctx, word);
+}
+
 // A whole Jacobi-PCG run on the residual in v.r, added to v.x, in one resident
 // kernel.  VFS_OK with *gave_up set when its workgroups could not all run (the
 // context then keeps to the launched iteration; v.r is untouched, v.x void).
 template <typename T>
-int run_resident2d(vfs_ctx* ctx, int shape, Vecs<T>& v, bool set_bb, int max_iter, Scalars* out,
-                   bool* gave_up) {
+int run_resident(vfs_ctx* ctx, int shape, Vecs<T>& v, bool set_bb, int max_iter, Scalars* out,
+                 bool* gave_up) {
     hipStream_t s = ctx->stream;
     if (ctx->res_stamp > 0xfffffff0u - (unsigned)max_iter - 8u) {   // stamps would wrap
         HIPCHK(hipMemsetAsync(ctx->res_part, 0, 2 * kResMost * 16 * sizeof(*ctx->res_part), s));
@@ -233,9 +246,20 @@ int run_resident2d(vfs_ctx* ctx, int shape, Vecs<T>& v, bool set_bb, int max_ite
     }
     std::lock_guard<std::mutex> one(res_mutex());
     if (ctx->prof) HIPCHK(hipEventRecord(ctx->pev[0], s));
-    launch_resident2d<T>(ctx->g, shape, ctx->res_lists + shape * kResMost, ctx->res_count[shape], v.r,
-                         v.x, v.dinv, v.a, v.c, v.K, ctx->res_part, ctx->res_msg, ctx->res_stamp,
-                         set_bb, ctx->sc, s);
+    const int* list = ctx->res_lists + shape * kResMost;
+    if (ctx->g.dim == 2) {
+        launch_resident2d<T>(ctx->g, shape, list, ctx->res_count[shape], v.r, v.x, v.dinv, v.a, v.c, v.K,
+                             ctx->res_part, ctx->res_msg, ctx->res_stamp, set_bb, ctx->sc, s);
+    } else {
+        const T* e;
+        if constexpr (sizeof(T) == 4)
+            e = ctx->ead32;
+        else
+            e = v.dinv;
+        launch_resident3d<T>(ctx->g, shape, list, ctx->res_rank[shape], ctx->res_count[shape], v.r, v.x, e,
+                             v.a, v.c, v.K, ctx->res_part, ctx->res_msg, ctx->res_stamp, set_bb,
+                             fused3d_pair(ctx->ftiles), fused3d_folds(ctx->g), ctx->sc, s);
+    }
     if (ctx->prof) HIPCHK(hipEventRecord(ctx->pev[1], s));
     HIPCHK(hipGetLastError());
     int rc = read_scalars(ctx, 0, out);
@@ -433,13 +457,13 @@ int solve_fp64(vfs_ctx* ctx, const double* b, double* x) {
     const Parts P = parts(ctx);
     Vecs<double> v{x, ctx->r, ctx->p0, ctx->p1, ctx->q, nullptr, ctx->a, ctx->c, ctx->K,
                    ctx->dinv};
-    const int shape = g.dim == 2 ? res2d_shape(ctx, 8) : -1;
+    const int shape = res_shape(ctx, 8);
     if (shape < 0)
         if (int rc0 = zero_dirs(ctx, false)) return rc0;
     auto run = [&](bool set_bb, int most, Scalars* out, bool* gave_up) {
         *gave_up = false;
         return shape < 0 ? run_chunks<double>(ctx, v, set_bb, out)
-                         : run_resident2d<double>(ctx, shape, v, set_bb, most, out, gave_up);
+                         : run_resident<double>(ctx, shape, v, set_bb, most, out, gave_up);
     };
     launch_cg_init<double>(g, b, x, ctx->r, ctx->dinv, nullptr, ctx->tol, ctx->max_iter, ctx->sc,
                            P.B, ctx->stream);
@@ -542,18 +566,18 @@ int solve_mixed(vfs_ctx* ctx, const double* b, double* x) {
         bool gave_up = false;
         if (learned) {
             rc = run_chunks_fcg(ctx, v, true, &s);
-        } else if (g.dim == 2) {
-            const int shape = res2d_shape(ctx, 4);
+        } else {
+            const int shape = res_shape(ctx, 4);
             if (shape >= 0)
-                rc = run_resident2d<float>(ctx, shape, v, true, ctx->max_iter - total, &s, &gave_up);
+                rc = run_resident<float>(ctx, shape, v, true, ctx->max_iter - total, &s, &gave_up);
             if (!rc && gave_up) {   // again by launches, from the same residual
                 launch_cg_init<float>(g, ctx->r32, ctx->x32, ctx->r32, ctx->dinv32, nullptr, tol_in,
                                       ctx->max_iter - total, ctx->sc, P.B, ctx->stream);
                 HIPCHK(hipGetLastError());
             }
-            if (!rc && (shape < 0 || gave_up)) rc = run_chunks_fused(ctx, true, &s);
-        } else
-            rc = run_chunks_fused3d(ctx, true, &s);
+            if (!rc && (shape < 0 || gave_up))
+                rc = g.dim == 2 ? run_chunks_fused(ctx, true, &s) : run_chunks_fused3d(ctx, true, &s);
+        }
         if (rc) return rc;
         total += s.iter;
         fallbacks += s.fallbacks;
@@ -616,10 +640,10 @@ int solve_schwarz(vfs_ctx* ctx, const double* b, double* x) {
                     return fail(ctx, VFS_ENOMEM, "hipMalloc failed (row list)");
             }
             launch_row_list(g, ctx->rowbits, ctx->rowlist, ctx->rowlist_cnt, s);
-            HIPCHK(hipMemcpyAsync(ctx->tile_count_host + 2, ctx->rowlist_cnt + row_list_chunks(g),
+            HIPCHK(hipMemcpyAsync(ctx->tile_count_host + 7, ctx->rowlist_cnt + row_list_chunks(g),
                                   sizeof(int), hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
-            ctx->rowlist_n = ctx->tile_count_host[2];
+            ctx->rowlist_n = ctx->tile_count_host[7];
         }
         rl = RowList{ctx->rowlist, ctx->rowlist_n};
     }
@@ -773,10 +797,16 @@ int assemble_internal(vfs_ctx* ctx, double dt) {
         launch_fused_tiles(g, ctx->tile_flags, ctx->ftile_flags, ctx->ftile_list,
                            ctx->tile_count + 1, s);
         launch_row_bits(g, ctx->a, ctx->rowbits, s);
+        if (ctx->res_part)
+            for (int q = 0; q < kRes3dShapes; ++q)
+                launch_res3d_lists(g, q, ctx->a, ctx->tile_flags, ctx->res_flags,
+                                   ctx->res_lists + q * kResMost, ctx->res_rank[q],
+                                   ctx->tile_count + 2 + q, s);
         ctx->rowlist_n = -1;   // the row list follows the new row bits
-        HIPCHK(hipMemcpyAsync(ctx->tile_count_host, ctx->tile_count, 2 * sizeof(int),
+        HIPCHK(hipMemcpyAsync(ctx->tile_count_host, ctx->tile_count, (2 + kRes3dShapes) * sizeof(int),
                               hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
+        for (int q = 0; q < kRes3dShapes; ++q) ctx->res_count[q] = ctx->tile_count_host[2 + q];
         ctx->tiles.list = ctx->tile_list;
         ctx->tiles.count = ctx->tile_count_host[0];
         ctx->ftiles.list = ctx->ftile_list;
@@ -1033,6 +1063,27 @@ int vfs_create(vfs_ctx** out, int dim, int nx, int ny, int nz, double h, const d
         ALLOC(ctx->ftile_flags, nf);
         ALLOC(ctx->ftile_list, nf);
         ALLOC(ctx->rowbits, row_bytes(g));
+        // the resident solve holds at most 256 bricks; on grids up to about 130^3
+        // that can be a thin or small body of liquid, or half of a 60^3 box
+        if (NP <= 3000000) {
+            long long nb[kRes3dShapes], most = 0, all = 0;
+            for (int q = 0; q < kRes3dShapes; ++q) {
+                int x, y, z;
+                res3d_lattice(g, q, x, y, z);
+                nb[q] = (long long)x * y * z;
+                most = std::max(most, nb[q]);
+                all += nb[q];
+            }
+            const long long part = 2 * kResMost * 16, lists = kRes3dShapes * kResMost;
+            ctx->res_msg_words = res3d_words();
+            // one allocation: words, messages, then lists, ranks and flags
+            ALLOC(ctx->res_part, part + ctx->res_msg_words + (lists + all + most + 1) / 2);
+            ctx->res_msg = ctx->res_part + part;
+            ctx->res_lists = (int*)(ctx->res_msg + ctx->res_msg_words);
+            ctx->res_rank[0] = ctx->res_lists + lists;
+            for (int q = 1; q < kRes3dShapes; ++q) ctx->res_rank[q] = ctx->res_rank[q - 1] + nb[q - 1];
+            ctx->res_flags = ctx->res_rank[kRes3dShapes - 1] + nb[kRes3dShapes - 1];
+        }
     } else {
         ALLOC(ctx->tile_flags, nt2);
         ALLOC(ctx->tile_list, nt2);

@@ -87,3 +87,44 @@ def test_resident_batch_keeps_the_iterates_of_the_persistent_kernel():
         # the sums differ in order only; their rounding to FP32 may flip once in
         # millions of iterations, so equality is asked for, not a tolerance
         assert np.array_equal(x0, x1)
+
+
+# one brick is 8 x 8 x 8 anchors (cells + 1), 16 x 8 x 8 in FP32 when those are
+# more than the compute units: one brick, a full one, one anchor more, several,
+# the folded column of the launched iteration (64), the wide bricks (48 cells a
+# side) and more bricks than fit
+@pytest.mark.parametrize("n", [(6, 5, 6), (7, 7, 7), (8, 8, 8), (15, 16, 17), (64, 9, 12), (9, 40, 11)])
+@pytest.mark.parametrize("precision,tol,bar", [(0, 1e-11, 1e-6), (1, 1e-9, 1e-4)])
+def test_resident3d_brick_edges(n, precision, tol, bar):
+    case = cases.crop(cases.pool3d(max(n), 7), (0, 0, 0), n)
+    print(f"resident 3D {n} precision {precision}", flush=True)
+    asm, x, u = oracle(case)
+    ctx = gpu_run(case, precision=precision, tol=tol)
+    assert ctx.vfs_get_stats()["rel_residual"] <= tol
+    assert velocity_rel_linf(asm, flat_faces(asm.grid, ctx.vfs_get_velocity()), u) <= bar
+
+
+@pytest.mark.parametrize("n,precision", [((30, 33, 31), 0), ((48, 48, 48), 0), ((48, 48, 48), 1),
+                                         ((65, 47, 63), 1), ((96, 80, 72), 0), ((96, 80, 72), 1)])
+def test_resident3d_shapes(n, precision):
+    tol = 1e-8
+    print(f"resident 3D pool {n} precision {precision}", flush=True)
+    case = cases.crop(cases.pool3d(max(n), 7), (0, 0, 0), n)
+    ctx = gpu_run(case, precision=precision, tol=tol)
+    assert _residual(ctx) <= 1.01 * tol
+
+
+def test_resident3d_repeats_and_cap():
+    case = cases.crop(cases.pool3d(40, 7), (0, 0, 0), (40, 33, 37))
+    ctx = gpu_run(case, tol=1e-10, step=False)
+    b = ctx.vfs_get_rhs()
+    x0 = ctx.vfs_solve(b)
+    its = ctx.vfs_get_stats()["iterations"]
+    ctx.vfs_set_solver(1, 0, 1e-10, 37, 1e-3)
+    ctx.vfs_solve(b, allow_unconverged=True)
+    st = ctx.vfs_get_stats()
+    assert st["iterations"] == 37 and st["status"] == -4
+    ctx.vfs_set_solver(1, 0, 1e-10, 200000, 1e-3)
+    x1 = ctx.vfs_solve(b)
+    assert ctx.vfs_get_stats()["iterations"] == its
+    assert np.array_equal(x0, x1)
