@@ -279,13 +279,12 @@ int vfs_get_sizes(const vfs_ctx* ctx, int64_t* n_samples, int64_t* n_faces);
  *   phi_liquid: DEVICE memory, (nx+1) x (ny+1) [x (nz+1)] FP64, x-fastest.
  *   out:        DEVICE memory, the set's native shape (see the conventions).
  * Work is queued on hip_stream (NULL = the null stream) and the call returns
- * without synchronising; NaN/Inf in phi_liquid are not checked.  The work
- * space is one fixed 96 MiB device array per GPU, held until the process
- * ends: it takes (16 (nx ny [nz]) + 2 nsets NP) doubles, NP the padded grid
- * size of the conventions above, which admits square 2D grids up to 882^2
- * and cubic 3D grids up to 69^3; larger grids return VFS_EINVAL.  Every call on a
- * GPU shares that GPU's array, so calls that overlap in time on one GPU
- * (different streams or threads) race and must be serialised by the caller.
+ * without synchronising; NaN/Inf in phi_liquid are not checked.  One kernel
+ * reads the level set and writes out, with no work space: calls on one GPU may
+ * overlap (different streams or threads).  Grids whose fractions and weights,
+ * (16 (nx ny [nz]) + 2 nsets NP) doubles in 3D and (8 nx ny + 2 nsets NP) in 2D,
+ * NP the padded grid size of the conventions above, are over 96 MiB return
+ * VFS_EINVAL: square 2D grids up to 882^2 and cubic 3D grids up to 69^3 pass.
  * Errors: VFS_EINVAL (sizes, set, w_min, NULL pointers), VFS_EHIP; the
  * message is vfs_last_error(NULL). */
 int vfs_liquid_weights_noalloc(int dim, int nx, int ny, int nz, double w_min,

@@ -21,29 +21,39 @@
 namespace vfs {
 namespace {
 
+// Puts the negative values first, each kind in its order, and counts them:
+// exchanges of neighbours, so that the values stay in registers.
+template <int N>
+__device__ __forceinline__ int negatives_first(double (&w)[N]) {
+    int k = 0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) k += w[q] < 0.0 ? 1 : 0;
+#pragma unroll
+    for (int r = N - 1; r > 0; --r)
+#pragma unroll
+        for (int q = 0; q < r; ++q) {
+            const double u = w[q], v = w[q + 1];
+            const bool swap = !(u < 0.0) && v < 0.0;
+            w[q] = swap ? v : u;
+            w[q + 1] = swap ? u : v;
+        }
+    return k;
+}
+
 // Fraction of a triangle with phi < 0 for vertex values v0, v1, v2.
 // Negative values are taken first in vertex order, then the others.
 __device__ __forceinline__ double tri_frac(double v0, double v1, double v2) {
-    double V[3] = {v0, v1, v2};
-    double w[3];
-    int m = 0;
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-        if (V[q] < 0.0) w[m++] = V[q];
-    const int k = m;
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-        if (!(V[q] < 0.0)) w[m++] = V[q];
+    double w[3] = {v0, v1, v2};
+    const int k = negatives_first(w);
+    const double a = w[0], b = w[1], c = w[2];
     double f;
     if (k == 0) {
         f = 0.0;
     } else if (k == 3) {
         f = 1.0;
     } else if (k == 1) {
-        const double a = w[0], b = w[1], c = w[2];
         f = (a * a) / ((a - b) * (a - c));
     } else {
-        const double a = w[0], b = w[1], c = w[2];
         f = 1.0 - (c * c) / ((c - a) * (c - b));
     }
     return fmin(fmax(f, 0.0), 1.0);
@@ -51,104 +61,332 @@ __device__ __forceinline__ double tri_frac(double v0, double v1, double v2) {
 
 // Fraction of a tetrahedron with phi < 0.
 __device__ __forceinline__ double tet_frac(double v0, double v1, double v2, double v3) {
-    double V[4] = {v0, v1, v2, v3};
-    double w[4];
-    int m = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        if (V[q] < 0.0) w[m++] = V[q];
-    const int k = m;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        if (!(V[q] < 0.0)) w[m++] = V[q];
+    double w[4] = {v0, v1, v2, v3};
+    const int k = negatives_first(w);
     const double a = w[0], b = w[1], c = w[2], d = w[3];
-    double f;
-    if (k == 0) {
-        f = 0.0;
-    } else if (k == 4) {
-        f = 1.0;
-    } else if (k == 1) {
-        f = ((a * a) * a) / (((a - b) * (a - c)) * (a - d));
+    double num, den;
+    if (k == 0) return 0.0;
+    if (k == 4) return 1.0;
+    // one division for the three cases
+    if (k == 1) {
+        num = (a * a) * a;
+        den = ((a - b) * (a - c)) * (a - d);
     } else if (k == 2) {
-        const double num = ((a * a) * (b * b) - ((a * b) * (a + b)) * (c + d)) +
-                           (c * d) * (((a * a) + (a * b)) + (b * b));
-        const double den = ((a - c) * (a - d)) * ((b - c) * (b - d));
-        f = num / den;
+        num = ((a * a) * (b * b) - ((a * b) * (a + b)) * (c + d)) +
+              (c * d) * (((a * a) + (a * b)) + (b * b));
+        den = ((a - c) * (a - d)) * ((b - c) * (b - d));
     } else {
-        f = 1.0 - ((d * d) * d) / (((d - a) * (d - b)) * (d - c));
+        num = (d * d) * d;
+        den = ((d - a) * (d - b)) * (d - c);
     }
+    const double q = num / den, f = k == 3 ? 1.0 - q : q;
     return fmin(fmax(f, 0.0), 1.0);
 }
 
-// h/2-lattice value at (A,B) from compact nodal values (x-fastest, NX1 per row).
-__device__ __forceinline__ double half2(const double* __restrict__ phi, int NX1, int A, int B) {
-    const int i = A >> 1, j = B >> 1;
-    const bool ox = A & 1, oy = B & 1;
-    const double* r0 = phi + (long long)j * NX1;
-    const double x0 = ox ? (r0[i] + r0[i + 1]) * 0.5 : r0[i];
-    if (!oy) return x0;
-    const double* r1 = r0 + NX1;
-    const double x1 = ox ? (r1[i] + r1[i + 1]) * 0.5 : r1[i];
-    return (x0 + x1) * 0.5;
+// Value along an axis of the h/2 lattice inside a cell: its near node (0), the
+// midpoint (1) or its far node (2).
+__device__ __forceinline__ double half(double p, double q, int at) {
+    return at == 0 ? p : (at == 1 ? (p + q) * 0.5 : q);
 }
 
-__device__ __forceinline__ double half3(const double* __restrict__ phi, int NX1, int NY1, int A,
-                                        int B, int C) {
-    const int k = C >> 1;
-    const long long plane = (long long)NX1 * NY1;
-    const double z0 = half2(phi + k * plane, NX1, A, B);
-    if (!(C & 1)) return z0;
-    const double z1 = half2(phi + (k + 1) * plane, NX1, A, B);
-    return (z0 + z1) * 0.5;
+// Liquid fraction of sub-cell (ox, oy) of a cell with nodal values p[y][x].
+// The value's sign is that of the nodes where these agree (a mean keeps it), and
+// a sub-cell of one sign is 0 or 1 without a look at its triangles.
+__device__ __forceinline__ double sub_frac(const double (&p)[2][2], int ox, int oy) {
+    double c[2][2];
+#pragma unroll
+    for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
+        for (int dx = 0; dx < 2; ++dx)
+            c[dy][dx] = half(half(p[0][0], p[0][1], ox + dx), half(p[1][0], p[1][1], ox + dx), oy + dy);
+    const double t1 = tri_frac(c[0][0], c[0][1], c[1][1]);
+    const double t2 = tri_frac(c[0][0], c[1][0], c[1][1]);
+    return (t1 + t2) * 0.5;
 }
 
-__global__ void k_subcell2d(int nx, int ny, const double* __restrict__ phi,
-                            double* __restrict__ th, int complement) {
-    const long long n = 4LL * nx * ny;
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    const int A = (int)(t % (2 * nx));
-    const int B = (int)(t / (2 * nx));
-    const int NX1 = nx + 1;
-    const double c00 = half2(phi, NX1, A, B);
-    const double c10 = half2(phi, NX1, A + 1, B);
-    const double c01 = half2(phi, NX1, A, B + 1);
-    const double c11 = half2(phi, NX1, A + 1, B + 1);
-    const double t1 = tri_frac(c00, c10, c11);
-    const double t2 = tri_frac(c00, c01, c11);
-    const double f = (t1 + t2) * 0.5;
-    th[t] = complement ? 1.0 - f : f;
-}
-
-__global__ void k_subcell3d(int nx, int ny, int nz, const double* __restrict__ phi,
-                            double* __restrict__ th, int complement) {
-    const long long sx = 2LL * nx, sy = 2LL * ny;
-    const long long n = sx * sy * 2LL * nz;
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    const int A = (int)(t % sx);
-    const int B = (int)((t / sx) % sy);
-    const int C = (int)(t / (sx * sy));
-    const int NX1 = nx + 1, NY1 = ny + 1;
-    double cv[2][2][2];
+// The same in 3D, p[z][y][x].
+__device__ __forceinline__ double sub_frac(const double (&p)[2][2][2], int ox, int oy, int oz) {
+    double c[2][2][2];   // [x][y][z]
 #pragma unroll
     for (int dz = 0; dz < 2; ++dz)
 #pragma unroll
         for (int dy = 0; dy < 2; ++dy)
 #pragma unroll
-            for (int dx = 0; dx < 2; ++dx)
-                cv[dx][dy][dz] = half3(phi, NX1, NY1, A + dx, B + dy, C + dz);
-    const double c000 = cv[0][0][0], c111 = cv[1][1][1];
+            for (int dx = 0; dx < 2; ++dx) {
+                double z[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    z[k] = half(half(p[k][0][0], p[k][0][1], ox + dx), half(p[k][1][0], p[k][1][1], ox + dx),
+                                oy + dy);
+                c[dx][dy][dz] = half(z[0], z[1], oz + dz);
+            }
     // permutations xyz, xzy, yxz, yzx, zxy, zyx: v1 = +e_p0, v2 = v1 + e_p1
     double acc;
-    acc = tet_frac(c000, cv[1][0][0], cv[1][1][0], c111);          // xyz
-    acc = acc + tet_frac(c000, cv[1][0][0], cv[1][0][1], c111);    // xzy
-    acc = acc + tet_frac(c000, cv[0][1][0], cv[1][1][0], c111);    // yxz
-    acc = acc + tet_frac(c000, cv[0][1][0], cv[0][1][1], c111);    // yzx
-    acc = acc + tet_frac(c000, cv[0][0][1], cv[1][0][1], c111);    // zxy
-    acc = acc + tet_frac(c000, cv[0][0][1], cv[0][1][1], c111);    // zyx
-    const double f = acc / 6.0;
-    th[t] = complement ? 1.0 - f : f;
+    acc = tet_frac(c[0][0][0], c[1][0][0], c[1][1][0], c[1][1][1]);          // xyz
+    acc = acc + tet_frac(c[0][0][0], c[1][0][0], c[1][0][1], c[1][1][1]);    // xzy
+    acc = acc + tet_frac(c[0][0][0], c[0][1][0], c[1][1][0], c[1][1][1]);    // yxz
+    acc = acc + tet_frac(c[0][0][0], c[0][1][0], c[0][1][1], c[1][1][1]);    // yzx
+    acc = acc + tet_frac(c[0][0][0], c[0][0][1], c[1][0][1], c[1][1][1]);    // zxy
+    acc = acc + tet_frac(c[0][0][0], c[0][0][1], c[0][1][1], c[1][1][1]);    // zyx
+    return acc / 6.0;
+}
+
+// Nodal values of cell (i, j[, k]), and how many are negative.
+__device__ __forceinline__ int cell_nodes(const double* __restrict__ phi, int NX1, int i, int j,
+                                          double (&p)[2][2]) {
+    const double* q = phi + (long long)j * NX1 + i;
+    int neg = 0;
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            p[y][x] = q[y * NX1 + x];
+            neg += p[y][x] < 0.0 ? 1 : 0;
+        }
+    return neg;
+}
+
+__device__ __forceinline__ int cell_nodes(const double* __restrict__ phi, int NX1, int NY1, int i, int j,
+                                          int k, double (&p)[2][2][2]) {
+    const long long plane = (long long)NX1 * NY1;
+    const double* q = phi + k * plane + (long long)j * NX1 + i;
+    int neg = 0;
+#pragma unroll
+    for (int z = 0; z < 2; ++z)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                p[z][y][x] = q[z * plane + y * NX1 + x];
+                neg += p[z][y][x] < 0.0 ? 1 : 0;
+            }
+    return neg;
+}
+
+__device__ __forceinline__ int clamp_cell(int A, int S) { return A < 0 ? 0 : (A >= S ? S - 1 : A); }
+
+__device__ __forceinline__ double snap(double w, double w_min) { return w < w_min ? 0.0 : w; }
+
+// Weights of all sample sets of a tile of anchors, both materials, in one pass.
+// Writing the sub-cell fractions to memory and averaging them in a second kernel
+// took 8.9 ms at 256^3 (a pool with a solid), this one takes 0.91, and the 2.1 GB
+// it cannot do without about 0.45: every sub-cell ran its six tetrahedra, and
+// 4.3 GB of fractions were written and read again.
+// Here a tile's sub-cells live in LDS.  Anchor i averages sub-cells 2i - 1 to
+// 2i + 1 of each axis, so TX anchors need 2 TX + 1 of them.  Cells whose nodes
+// have one sign are filled in; the sub-cells of the others, few and unevenly
+// spread, are listed and shared out over the whole workgroup.  x positions are
+// split by parity, so that lanes read neighbouring words.
+template <int DIM>
+struct FTile {
+    static constexpr int TX = 32, TY = DIM == 2 ? 8 : 4, TZ = DIM == 2 ? 1 : 4, NT = 256;
+    static constexpr int CX = TX + 1, CY = TY + 1, CZ = DIM == 2 ? 1 : TZ + 1;   // cells
+    static constexpr int SX = 2 * TX + 2, SY = 2 * TY + 1, SZ = DIM == 2 ? 1 : 2 * TZ + 1;
+    static constexpr int cells = CX * CY * CZ, subs = 1 << DIM;
+    static constexpr int per = TX * TY * TZ / NT;   // anchors per thread
+};
+
+template <int DIM>
+struct FLds {
+    double th[FTile<DIM>::SZ][FTile<DIM>::SY][FTile<DIM>::SX];
+    short mixed[FTile<DIM>::cells];
+    int n;
+};
+
+// Sub-cell fractions of the tile at (i0, j0, k0) into LDS.  Returns 0 or 1 when
+// every sub-cell of the tile has that value (LDS is then not written), else -1.
+template <int DIM>
+__device__ __forceinline__ int tile_fractions(const Geo& g, int i0, int j0, int k0,
+                                              const double* __restrict__ phi, bool complement,
+                                              FLds<DIM>& sh) {
+    using F = FTile<DIM>;
+    const int tid = threadIdx.x, NX1 = g.nx + 1, NY1 = g.ny + 1;
+    if (tid == 0) sh.n = 0;
+    __syncthreads();
+    constexpr int rounds = (F::cells + F::NT - 1) / F::NT;
+    int kind[rounds];   // 1: fraction 0, 2: fraction 1, 4: both signs, 0: outside
+    int any = 0;
+    double p3[2][2][2], p2[2][2];
+    auto cell = [&](int e, int& i, int& j, int& k) {
+        i = i0 - 1 + e % F::CX;
+        j = j0 - 1 + (e / F::CX) % F::CY;
+        k = DIM == 2 ? 0 : k0 - 1 + e / (F::CX * F::CY);
+        return i >= 0 && i < g.nx && j >= 0 && j < g.ny && (DIM == 2 || (k >= 0 && k < g.nz));
+    };
+#pragma unroll
+    for (int r = 0; r < rounds; ++r) {
+        const int e = tid + F::NT * r;
+        int i, j, k;
+        kind[r] = 0;
+        if (e < F::cells && cell(e, i, j, k)) {
+            const int neg = DIM == 2 ? cell_nodes(phi, NX1, i, j, p2) : cell_nodes(phi, NX1, NY1, i, j, k, p3);
+            kind[r] = neg == 0 ? (complement ? 2 : 1) : (neg == F::subs ? (complement ? 1 : 2) : 4);
+            if (kind[r] == 4) sh.mixed[atomicAdd(&sh.n, 1)] = (short)e;
+        }
+        any |= kind[r];
+    }
+    any = (__syncthreads_or(any & 1) ? 1 : 0) | (__syncthreads_or(any & 2) ? 2 : 0) |
+          (sh.n ? 4 : 0);
+    if (any == 1 || any == 2) return any - 1;
+    auto at = [&](int e, int q) -> double* {
+        // sub-cell q of cell e; the tile starts at the upper half of its first cell
+        const int a = 2 * (e % F::CX) - 1 + (q & 1), b = 2 * ((e / F::CX) % F::CY) - 1 + ((q >> 1) & 1),
+                  c = DIM == 2 ? 0 : 2 * (e / (F::CX * F::CY)) - 1 + (q >> 2);
+        if (a < 0 || b < 0 || c < 0) return nullptr;
+        return &sh.th[c][b][(a & 1) * (F::SX / 2) + (a >> 1)];
+    };
+#pragma unroll
+    for (int r = 0; r < rounds; ++r)
+        if (kind[r] == 1 || kind[r] == 2) {
+            const double v = kind[r] == 2 ? 1.0 : 0.0;
+#pragma unroll
+            for (int q = 0; q < F::subs; ++q)
+                if (double* d = at(tid + F::NT * r, q)) *d = v;
+        }
+    const int items = sh.n * F::subs;
+    for (int t = tid; t < items; t += F::NT) {
+        const int e = sh.mixed[t / F::subs], q = t % F::subs;
+        double* d = at(e, q);
+        if (!d) continue;
+        int i, j, k;
+        cell(e, i, j, k);
+        double f;
+        if constexpr (DIM == 2) {
+            cell_nodes(phi, NX1, i, j, p2);
+            f = sub_frac(p2, q & 1, q >> 1);
+        } else {
+            cell_nodes(phi, NX1, NY1, i, j, k, p3);
+            f = sub_frac(p3, q & 1, (q >> 1) & 1, q >> 2);
+        }
+        *d = complement ? 1.0 - f : f;
+    }
+    __syncthreads();
+    return -1;
+}
+
+// The sub-cells 2i - 1 to 2i + 1 of each axis around an anchor.  Box rule: liquid
+// mirrors (clamps) into the box, fluid is 0 outside.
+template <int DIM>
+__device__ __forceinline__ void sub_cells(const Geo& g, const FLds<DIM>& sh, int uniform, bool liquid, int i0,
+                                          int j0, int k0, int i, int j, int k,
+                                          double (&t)[DIM == 2 ? 1 : 3][3][3]) {
+    constexpr int NZ = DIM == 2 ? 1 : 3;
+    int x[3], y[3], z[3];
+    bool ox[3], oy[3], oz[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int A = 2 * i - 1 + q, B = 2 * j - 1 + q, C = 2 * k - 1 + q;
+        const int a = clamp_cell(A, 2 * g.nx) - (2 * i0 - 1);
+        x[q] = (a & 1) * (FTile<DIM>::SX / 2) + (a >> 1);
+        y[q] = clamp_cell(B, 2 * g.ny) - (2 * j0 - 1);
+        z[q] = DIM == 2 ? 0 : clamp_cell(C, 2 * g.nz) - (2 * k0 - 1);
+        ox[q] = !liquid && (A < 0 || A >= 2 * g.nx);
+        oy[q] = !liquid && (B < 0 || B >= 2 * g.ny);
+        oz[q] = DIM == 3 && !liquid && (C < 0 || C >= 2 * g.nz);
+    }
+#pragma unroll
+    for (int c = 0; c < NZ; ++c)
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                t[c][b][a] = uniform >= 0 ? (double)uniform : sh.th[z[c]][y[b]][x[a]];
+                if (ox[a] || oy[b] || oz[c]) t[c][b][a] = 0.0;
+            }
+}
+
+// Mean over the control volume of a sample of stagger (sx, sy, sz).
+__device__ __forceinline__ double cv_mean(const double (&t)[1][3][3], int sx, int sy, int) {
+    return ((t[0][sy][sx] + t[0][sy][sx + 1]) + (t[0][sy + 1][sx] + t[0][sy + 1][sx + 1])) * 0.25;
+}
+__device__ __forceinline__ double cv_mean(const double (&t)[3][3][3], int sx, int sy, int sz) {
+    double z[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        z[q] = (t[sz + q][sy][sx] + t[sz + q][sy][sx + 1]) + (t[sz + q][sy + 1][sx] + t[sz + q][sy + 1][sx + 1]);
+    return (z[0] + z[1]) * 0.125;
+}
+
+// staggers of the sample sets:
+// 2D 0 cell (1,1), 1 u (0,1), 2 v (1,0), 3 node (0,0)
+// 3D 0 cell (1,1,1), 1 u (0,1,1), 2 v (1,0,1), 3 w (1,1,0),
+//    4 z-edge (0,0,1), 5 y-edge (0,1,0), 6 x-edge (1,0,0)
+template <int DIM>
+__device__ __forceinline__ void stagger_of(int s, int& sx, int& sy, int& sz) {
+    constexpr int x[7] = {1, 0, 1, 1, 0, 0, 1}, y[7] = {1, 1, 0, 1, 0, 1, 0}, z[7] = {1, 1, 1, 0, 1, 0, 0};
+    sx = DIM == 2 ? (s == 0 || s == 2) : x[s];
+    sy = DIM == 2 ? s < 2 : y[s];
+    sz = DIM == 2 ? 1 : z[s];
+}
+
+template <int DIM>
+__global__ __launch_bounds__(256) void k_weights(Geo g, const double* __restrict__ phi_l,
+                                                 const double* __restrict__ phi_s, double w_min,
+                                                 double* __restrict__ WL, double* __restrict__ WF) {
+    using F = FTile<DIM>;
+    __shared__ FLds<DIM> sh;
+    const int i0 = blockIdx.x * F::TX, j0 = blockIdx.y * F::TY, k0 = blockIdx.z * F::TZ;
+    for (int m = 0; m < 2; ++m) {
+        const bool liquid = m == 0;
+        const double* phi = liquid ? phi_l : phi_s;
+        double* __restrict__ W = liquid ? WL : WF;
+        const int uniform = phi ? tile_fractions<DIM>(g, i0, j0, k0, phi, !liquid, sh) : 1;
+#pragma unroll 1
+        for (int n = 0; n < F::per; ++n) {
+            const int t = threadIdx.x + F::NT * n;
+            const int i = i0 + t % F::TX, j = j0 + (t / F::TX) % F::TY, k = k0 + t / (F::TX * F::TY);
+            if (i > g.nx || j > g.ny || (DIM == 3 && k > g.nz)) continue;
+            const long long o = DIM == 2 ? g.idx(i, j) : g.idx(i, j, k);
+            double th[DIM == 2 ? 1 : 3][3][3];
+            sub_cells<DIM>(g, sh, uniform, liquid, i0, j0, k0, i, j, k, th);
+#pragma unroll
+            for (int s = 0; s < (DIM == 2 ? 4 : 7); ++s) {
+                int sx, sy, sz;
+                stagger_of<DIM>(s, sx, sy, sz);
+                const bool valid = (i < g.nx + (sx ? 0 : 1)) && (j < g.ny + (sy ? 0 : 1)) &&
+                                   (DIM == 2 || k < g.nz + (sz ? 0 : 1));
+                if (!valid) continue;
+                double w = snap(cv_mean(th, sx, sy, sz), w_min);
+                if (!liquid && ((s == 1 && (i == 0 || i == g.nx)) || (s == 2 && (j == 0 || j == g.ny)) ||
+                                (DIM == 3 && s == 3 && (k == 0 || k == g.nz))))
+                    w = 0.0;
+                W[s * g.NP + o] = w;
+            }
+        }
+        __syncthreads();   // the next material reuses the LDS
+    }
+}
+
+// Liquid weights of one sample set, to the caller's compact array.  The control
+// volumes of one set share no sub-cell: a lane computes one, and the 2^d lanes of
+// a sample add theirs in pairs along x, y and z.  3.4 us at 64^2, where the
+// launches of filling, sub-cell, weight and unpack kernels took 18.
+template <int DIM>
+__global__ __launch_bounds__(256) void k_weights_set(Geo g, int n0, int n1, int n2, int sx, int sy, int sz,
+                                                     const double* __restrict__ phi, double w_min,
+                                                     double* __restrict__ out) {
+    constexpr int subs = 1 << DIM;
+    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x, e = t / subs;
+    const int q = (int)(t % subs);
+    if (e >= (long long)n0 * n1 * n2) return;   // whole groups of lanes
+    const int i = (int)(e % n0), j = (int)((e / n0) % n1), k = (int)(e / ((long long)n0 * n1));
+    const int A = clamp_cell(2 * i + (sx ? 0 : -1) + (q & 1), 2 * g.nx),
+              B = clamp_cell(2 * j + (sy ? 0 : -1) + ((q >> 1) & 1), 2 * g.ny);
+    double f;
+    if constexpr (DIM == 2) {
+        double p[2][2];
+        const int neg = cell_nodes(phi, g.nx + 1, A >> 1, B >> 1, p);
+        f = neg == 0 ? 0.0 : (neg == 4 ? 1.0 : sub_frac(p, A & 1, B & 1));
+    } else {
+        const int C = clamp_cell(2 * k + (sz ? 0 : -1) + (q >> 2), 2 * g.nz);
+        double p[2][2][2];
+        const int neg = cell_nodes(phi, g.nx + 1, g.ny + 1, A >> 1, B >> 1, C >> 1, p);
+        f = neg == 0 ? 0.0 : (neg == 8 ? 1.0 : sub_frac(p, A & 1, B & 1, C & 1));
+    }
+    f = f + __shfl_xor(f, 1);
+    f = f + __shfl_xor(f, 2);
+    if constexpr (DIM == 3) f = f + __shfl_xor(f, 4);
+    if (q == 0) out[e] = snap(f * (DIM == 2 ? 0.25 : 0.125), w_min);
 }
 
 __global__ void k_fill(double* __restrict__ d, long long n, double v) {
@@ -156,128 +394,7 @@ __global__ void k_fill(double* __restrict__ d, long long n, double v) {
     if (t < n) d[t] = v;
 }
 
-// Sub-cell value with the box rule: liquid mirrors (clamps) into the box,
-// fluid is 0 outside.
-__device__ __forceinline__ double sub2(const double* th, int SX, int SY, int A, int B,
-                                       bool liquid) {
-    if (A < 0 || A >= SX || B < 0 || B >= SY) {
-        if (!liquid) return 0.0;
-        A = A < 0 ? 0 : (A >= SX ? SX - 1 : A);
-        B = B < 0 ? 0 : (B >= SY ? SY - 1 : B);
-    }
-    return th[(long long)B * SX + A];
-}
-
-__device__ __forceinline__ double sub3(const double* th, int SX, int SY, int SZ, int A, int B,
-                                       int C, bool liquid) {
-    if (A < 0 || A >= SX || B < 0 || B >= SY || C < 0 || C >= SZ) {
-        if (!liquid) return 0.0;
-        A = A < 0 ? 0 : (A >= SX ? SX - 1 : A);
-        B = B < 0 ? 0 : (B >= SY ? SY - 1 : B);
-        C = C < 0 ? 0 : (C >= SZ ? SZ - 1 : C);
-    }
-    return th[((long long)C * SY + B) * SX + A];
-}
-
-__device__ __forceinline__ double cvmean2(const double* th, int SX, int SY, int i, int j, int sx,
-                                          int sy, bool liquid) {
-    const int A = 2 * i + (sx ? 0 : -1);
-    const int B = 2 * j + (sy ? 0 : -1);
-    const double t00 = sub2(th, SX, SY, A, B, liquid);
-    const double t10 = sub2(th, SX, SY, A + 1, B, liquid);
-    const double t01 = sub2(th, SX, SY, A, B + 1, liquid);
-    const double t11 = sub2(th, SX, SY, A + 1, B + 1, liquid);
-    return ((t00 + t10) + (t01 + t11)) * 0.25;
-}
-
-__device__ __forceinline__ double cvmean3(const double* th, int SX, int SY, int SZ, int i, int j,
-                                          int k, int sx, int sy, int sz, bool liquid) {
-    const int A = 2 * i + (sx ? 0 : -1);
-    const int B = 2 * j + (sy ? 0 : -1);
-    const int C = 2 * k + (sz ? 0 : -1);
-    const double t000 = sub3(th, SX, SY, SZ, A, B, C, liquid);
-    const double t100 = sub3(th, SX, SY, SZ, A + 1, B, C, liquid);
-    const double t010 = sub3(th, SX, SY, SZ, A, B + 1, C, liquid);
-    const double t110 = sub3(th, SX, SY, SZ, A + 1, B + 1, C, liquid);
-    const double t001 = sub3(th, SX, SY, SZ, A, B, C + 1, liquid);
-    const double t101 = sub3(th, SX, SY, SZ, A + 1, B, C + 1, liquid);
-    const double t011 = sub3(th, SX, SY, SZ, A, B + 1, C + 1, liquid);
-    const double t111 = sub3(th, SX, SY, SZ, A + 1, B + 1, C + 1, liquid);
-    return (((t000 + t100) + (t010 + t110)) + ((t001 + t101) + (t011 + t111))) * 0.125;
-}
-
-__device__ __forceinline__ double snap(double w, double w_min) { return w < w_min ? 0.0 : w; }
-
-// 2D sets: 0 cell (1,1), 1 u (0,1), 2 v (1,0), 3 node (0,0)
-__global__ void k_weights2d(Geo g, const double* __restrict__ thL,
-                            const double* __restrict__ thF, double w_min,
-                            double* __restrict__ WL, double* __restrict__ WF) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int j = blockIdx.y * blockDim.y + threadIdx.y;
-    if (i > g.nx || j > g.ny) return;
-    const int SX = 2 * g.nx, SY = 2 * g.ny;
-    const long long o = g.idx(i, j);
-    const int sxs[4] = {1, 0, 1, 0};
-    const int sys[4] = {1, 1, 0, 0};
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const int sx = sxs[s], sy = sys[s];
-        const bool valid = (i < g.nx + (sx ? 0 : 1)) && (j < g.ny + (sy ? 0 : 1));
-        if (!valid) continue;
-        double wl = snap(cvmean2(thL, SX, SY, i, j, sx, sy, true), w_min);
-        double wf = snap(cvmean2(thF, SX, SY, i, j, sx, sy, false), w_min);
-        if (s == 1 && (i == 0 || i == g.nx)) wf = 0.0;
-        if (s == 2 && (j == 0 || j == g.ny)) wf = 0.0;
-        WL[s * g.NP + o] = wl;
-        WF[s * g.NP + o] = wf;
-    }
-}
-
-// 3D sets: 0 cell (1,1,1), 1 u (0,1,1), 2 v (1,0,1), 3 w (1,1,0),
-//          4 z-edge (0,0,1), 5 y-edge (0,1,0), 6 x-edge (1,0,0)
-__global__ void k_weights3d(Geo g, const double* __restrict__ thL,
-                            const double* __restrict__ thF, double w_min,
-                            double* __restrict__ WL, double* __restrict__ WF) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int j = blockIdx.y * blockDim.y + threadIdx.y;
-    const int k = blockIdx.z * blockDim.z + threadIdx.z;
-    if (i > g.nx || j > g.ny || k > g.nz) return;
-    const int SX = 2 * g.nx, SY = 2 * g.ny, SZ = 2 * g.nz;
-    const long long o = g.idx(i, j, k);
-    const int sxs[7] = {1, 0, 1, 1, 0, 0, 1};
-    const int sys[7] = {1, 1, 0, 1, 0, 1, 0};
-    const int szs[7] = {1, 1, 1, 0, 1, 0, 0};
-#pragma unroll
-    for (int s = 0; s < 7; ++s) {
-        const int sx = sxs[s], sy = sys[s], sz = szs[s];
-        const bool valid = (i < g.nx + (sx ? 0 : 1)) && (j < g.ny + (sy ? 0 : 1)) &&
-                           (k < g.nz + (sz ? 0 : 1));
-        if (!valid) continue;
-        double wl = snap(cvmean3(thL, SX, SY, SZ, i, j, k, sx, sy, sz, true), w_min);
-        double wf = snap(cvmean3(thF, SX, SY, SZ, i, j, k, sx, sy, sz, false), w_min);
-        if (s == 1 && (i == 0 || i == g.nx)) wf = 0.0;
-        if (s == 2 && (j == 0 || j == g.ny)) wf = 0.0;
-        if (s == 3 && (k == 0 || k == g.nz)) wf = 0.0;
-        WL[s * g.NP + o] = wl;
-        WF[s * g.NP + o] = wf;
-    }
-}
-
 }  // namespace
-
-void launch_subcell_fractions(const Geo& g, const double* phi, double* theta, bool complement,
-                              hipStream_t s) {
-    const int bs = 256;
-    if (g.dim == 2) {
-        const long long n = 4LL * g.nx * g.ny;
-        hipLaunchKernelGGL(k_subcell2d, dim3((unsigned)((n + bs - 1) / bs)), dim3(bs), 0, s, g.nx,
-                           g.ny, phi, theta, complement ? 1 : 0);
-    } else {
-        const long long n = 8LL * g.nx * g.ny * g.nz;
-        hipLaunchKernelGGL(k_subcell3d, dim3((unsigned)((n + bs - 1) / bs)), dim3(bs), 0, s, g.nx,
-                           g.ny, g.nz, phi, theta, complement ? 1 : 0);
-    }
-}
 
 void launch_fill(double* dst, long long n, double v, hipStream_t s) {
     const int bs = 256;
@@ -285,17 +402,35 @@ void launch_fill(double* dst, long long n, double v, hipStream_t s) {
     hipLaunchKernelGGL(k_fill, dim3((unsigned)((n + bs - 1) / bs)), dim3(bs), 0, s, dst, n, v);
 }
 
-void launch_weights(const Geo& g, const double* thL, const double* thF, double w_min, double* WL,
+template <int DIM>
+static void launch_weights_dim(const Geo& g, const double* phi_l, const double* phi_s, double w_min,
+                               double* WL, double* WF, hipStream_t s) {
+    using F = FTile<DIM>;
+    const dim3 gs(g.nx / F::TX + 1, g.ny / F::TY + 1, DIM == 2 ? 1 : g.nz / F::TZ + 1);
+    hipLaunchKernelGGL(k_weights<DIM>, gs, dim3(F::NT), 0, s, g, phi_l, phi_s, w_min, WL, WF);
+}
+
+void launch_weights(const Geo& g, const double* phi_l, const double* phi_s, double w_min, double* WL,
                     double* WF, hipStream_t s) {
-    if (g.dim == 2) {
-        dim3 bs(64, 4);
-        dim3 gs((g.nx + 1 + 63) / 64, (g.ny + 1 + 3) / 4);
-        hipLaunchKernelGGL(k_weights2d, gs, bs, 0, s, g, thL, thF, w_min, WL, WF);
-    } else {
-        dim3 bs(64, 2, 2);
-        dim3 gs((g.nx + 1 + 63) / 64, (g.ny + 1 + 1) / 2, (g.nz + 1 + 1) / 2);
-        hipLaunchKernelGGL(k_weights3d, gs, bs, 0, s, g, thL, thF, w_min, WL, WF);
-    }
+    if (g.dim == 2)
+        launch_weights_dim<2>(g, phi_l, phi_s, w_min, WL, WF, s);
+    else
+        launch_weights_dim<3>(g, phi_l, phi_s, w_min, WL, WF, s);
+}
+
+void launch_weights_set(const Geo& g, int set, const double* phi_l, double w_min, double* out,
+                        hipStream_t s) {
+    int shp[3];
+    set_shape(g, set, shp);
+    const long long n = (long long)shp[0] * shp[1] * (g.dim == 3 ? shp[2] : 1);
+    const int sx = shp[0] == g.nx, sy = shp[1] == g.ny, sz = g.dim == 3 ? shp[2] == g.nz : 1;
+    const unsigned nb = (unsigned)((n * (1 << g.dim) + 255) / 256);
+    if (g.dim == 2)
+        hipLaunchKernelGGL(k_weights_set<2>, dim3(nb), dim3(256), 0, s, g, shp[0], shp[1], 1, sx, sy, sz,
+                           phi_l, w_min, out);
+    else
+        hipLaunchKernelGGL(k_weights_set<3>, dim3(nb), dim3(256), 0, s, g, shp[0], shp[1], shp[2], sx, sy,
+                           sz, phi_l, w_min, out);
 }
 
 }  // namespace vfs

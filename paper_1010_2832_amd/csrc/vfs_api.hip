@@ -79,9 +79,7 @@ int dalloc(vfs_ctx* ctx, T** p, long long n) {
 long long node_count(const Geo& g) {
     return (long long)(g.nx + 1) * (g.ny + 1) * (g.dim == 3 ? g.nz + 1 : 1);
 }
-long long sub_count(const Geo& g) {
-    return (long long)(2 * g.nx) * (2 * g.ny) * (g.dim == 3 ? 2 * g.nz : 1);
-}
+
 long long set_count(const Geo& g, int set) {
     int shp[3];
     set_shape(g, set, shp);
@@ -744,12 +742,7 @@ int assemble_internal(vfs_ctx* ctx, double dt) {
     if (!ctx->have_phi || !ctx->have_rho || !ctx->have_mu || !ctx->have_u)
         return fail(ctx, VFS_ESTATE, "level sets, density, viscosity and velocity must be set");
     hipStream_t s = ctx->stream;
-    launch_subcell_fractions(g, ctx->phi_l, ctx->thL, false, s);
-    if (ctx->has_solid)
-        launch_subcell_fractions(g, ctx->phi_s, ctx->thF, true, s);
-    else
-        launch_fill(ctx->thF, sub_count(g), 1.0, s);
-    launch_weights(g, ctx->thL, ctx->thF, ctx->w_min, ctx->WL, ctx->WF, s);
+    launch_weights(g, ctx->phi_l, ctx->has_solid ? ctx->phi_s : nullptr, ctx->w_min, ctx->WL, ctx->WF, s);
     HIPCHK(hipMemsetAsync(&ctx->sc->n_active, 0, sizeof(long long), s));
     if (g.dim == 2) {
         launch_face_coef2d(g, dt, ctx->gravity, ctx->WL, ctx->WF, ctx->rho, ctx->u, ctx->ustar,
@@ -949,7 +942,7 @@ const char* vfs_last_error(const vfs_ctx* ctx) {
 int vfs_destroy(vfs_ctx* ctx) {
     if (!ctx) return VFS_OK;
     void* bufs[] = {ctx->phi_l, ctx->phi_s, ctx->rho,  ctx->mu,     ctx->u,      ctx->ubc,
-                    ctx->thL,   ctx->thF,   ctx->WL,   ctx->WF,     ctx->fflag,  ctx->ustar,
+                    ctx->WL,   ctx->WF,     ctx->fflag,  ctx->ustar,
                     ctx->rhof,  ctx->K,     ctx->a,    ctx->c,      ctx->dinv,   ctx->b,
                     ctx->K32,   ctx->a32,   ctx->c32,  ctx->dinv32, ctx->x,      ctx->r,
                     ctx->p0,    ctx->p1,    ctx->q,    ctx->z,      ctx->x32,    ctx->r32,
@@ -1007,8 +1000,6 @@ int vfs_create(vfs_ctx** out, int dim, int nx, int ny, int nz, double h, const d
     ALLOC(ctx->mu, NP);
     ALLOC(ctx->u, nf * NP);
     ALLOC(ctx->ubc, nf * NP);
-    ALLOC(ctx->thL, sub_count(g));
-    ALLOC(ctx->thF, sub_count(g));
     ALLOC(ctx->WL, nsets * NP);
     ALLOC(ctx->WF, nsets * NP);
     ALLOC(ctx->fflag, nf * NP);

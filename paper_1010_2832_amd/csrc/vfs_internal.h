@@ -219,8 +219,6 @@ struct vfs_ctx {
     bool have_x = false;         // ctx->x holds a solution of the last step
 
     // assembly (device)
-    double* thL = nullptr;       // compact sub-cell liquid fractions (2n)^d
-    double* thF = nullptr;       // compact sub-cell fluid fractions
     double* WL = nullptr;        // padded, nsets slices
     double* WF = nullptr;        // padded, nsets slices (faces: after invalidation)
     uint8_t* fflag = nullptr;    // padded faces, dim slices: bit0 K>0, bit1 bad, bit2 invalid
@@ -332,11 +330,14 @@ int fail_global(int code, const std::string& msg);
 
 // ---- launchers (defined in the .hip files) ----
 // fractions / weights (k_fractions.hip)
-void launch_subcell_fractions(const Geo& g, const double* phi, double* theta, bool complement,
-                              hipStream_t s);
 void launch_fill(double* dst, long long n, double v, hipStream_t s);
-void launch_weights(const Geo& g, const double* thL, const double* thF, double w_min,
+// liquid and fluid weights of every set from the nodal level sets (phi_s NULL:
+// no solid)
+void launch_weights(const Geo& g, const double* phi_l, const double* phi_s, double w_min,
                     double* WL, double* WF, hipStream_t s);
+// liquid weights of one set (numbered as stored) to a compact array
+void launch_weights_set(const Geo& g, int set, const double* phi_l, double w_min, double* out,
+                        hipStream_t s);
 // 2D assembly (k_assemble2d.hip)
 void launch_face_coef2d(const Geo& g, double dt, const double* g3, const double* WL, double* WF,
                         const double* rho, const double* u, double* ustar, double* rhof,
