@@ -127,3 +127,26 @@ def test_warm_start_across_steps():
     assert res[False][1] == [1.0] * steps
     for got, want in zip(res[True][1], want_start):
         assert abs(got - want) <= 1e-4 * want, (got, want)
+
+
+# grids of one cell (no second sample along an axis), thin ones, and the edges of
+# the 64 x 4 and 64 x 2 x 2 blocks
+@pytest.mark.parametrize("n", [(1, 1), (1, 6), (63, 4), (64, 5), (1, 1, 1), (5, 1, 3), (63, 2, 3), (64, 3, 2)])
+def test_one_advection_at_small_extents(n):
+    from paper_1010_2832_amd import vfstokes as V
+    rng = np.random.default_rng(5)
+    d, h, dt = len(n), 1.0 / max(n), 0.3 / max(n)
+    grid = Grid(n, h)
+    phi = rng.standard_normal([q + 1 for q in n])
+    u = [rng.standard_normal([n[b] + (1 if b == a else 0) for b in range(d)]) for a in range(d)]
+    ctx = V.Context(d, n, h)
+    ctx.vfs_set_level_sets(phi)
+    ctx.vfs_set_density(np.ones(n))
+    ctx.vfs_set_viscosity(np.ones(n))
+    ctx.vfs_set_velocity(u)
+    ctx.vfs_advect(dt)
+    du = np.abs(flat_faces(grid, ctx.vfs_get_velocity()) - flat_faces(grid, advect.advect_velocity(grid, u, dt))).max()
+    dp = np.abs(ctx.vfs_get_level_set() - advect.advect_level_set(grid, phi, u, dt)).max()
+    _banner(f"{n}: velocity {du:.2e}, level set {dp:.2e}")
+    # values of size 1, weights off by the rounding of positions up to 64
+    assert du <= 1e-12 and dp <= 1e-12
