@@ -2,6 +2,8 @@
 // padded device grid, input validation and precision conversion.
 #include "vfs_internal.h"
 
+#include <algorithm>
+
 namespace vfs {
 namespace {
 
@@ -27,6 +29,47 @@ __global__ void k_unpack(Geo g, int n0, int n1, int n2, const double* __restrict
     const int k = (int)(t / ((long long)n0 * n1));
     const long long o = g.dim == 2 ? g.idx(i, j) : g.idx(i, j, k);
     dst[t] = src[o];
+}
+
+// The caller's device arrays and the padded slices they belong to, straight from
+// one to the other: blockIdx.y is the array.  A copy to a staging array, a check,
+// a flag read back and a pack for each of the six slices, then as many unpacks
+// and copies, took 320 of the 484 us of one operator application at
+// 128 x 96 x 113 (8.5 million values each way); now about 70 of 229.
+// MODE: 1 check the values, 2 write them, 4 only if no array so far (this one
+// excepted while it is being checked) had a bad one.  FLAT: dst is compact too.
+template <int MODE, bool FLAT>
+__global__ __launch_bounds__(256) void k_take(Geo g, SliceMap m, int positive, int* __restrict__ bad,
+                                              int* __restrict__ bad_host) {
+    const int s = blockIdx.y + m.first;
+    if ((MODE & 4) && (*bad & (((MODE & 1) ? 1 : 2) << s) - 1)) return;
+    const int n0 = m.n[blockIdx.y][0], n1 = m.n[blockIdx.y][1];
+    const long long n = (long long)n0 * n1 * m.n[blockIdx.y][2];
+    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n) return;
+    const double x = m.user[blockIdx.y][t];
+    if ((MODE & 1) && (!isfinite(x) || (positive && !(x > 0.0)))) {
+        atomicOr(bad, 1 << s);
+        __hip_atomic_store(bad_host + s, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    if (MODE & 2) {
+        long long o = t;
+        if (!FLAT) {
+            const int i = (int)(t % n0), j = (int)((t / n0) % n1), k = (int)(t / ((long long)n0 * n1));
+            o = g.dim == 2 ? g.idx(i, j) : g.idx(i, j, k);
+        }
+        m.pad[blockIdx.y][o] = x;
+    }
+}
+
+// the way back
+__global__ __launch_bounds__(256) void k_give(Geo g, SliceMap m) {
+    const int n0 = m.n[blockIdx.y][0], n1 = m.n[blockIdx.y][1];
+    const long long n = (long long)n0 * n1 * m.n[blockIdx.y][2];
+    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n) return;
+    const int i = (int)(t % n0), j = (int)((t / n0) % n1), k = (int)(t / ((long long)n0 * n1));
+    m.user[blockIdx.y][t] = m.pad[blockIdx.y][g.dim == 2 ? g.idx(i, j) : g.idx(i, j, k)];
 }
 
 __global__ void k_unpack_active(Geo g, int n0, int n1, int n2, const double* __restrict__ a,
@@ -104,6 +147,36 @@ void launch_unpack(const Geo& g, const int shp[3], const double* src, double* ds
     if (n <= 0) return;
     hipLaunchKernelGGL(k_unpack, dim3(nblk(n, 256)), dim3(256), 0, s, g, shp[0], shp[1], shp[2],
                        src, dst);
+}
+
+static dim3 slice_grid(const SliceMap& m) {
+    long long most = 0;
+    for (int s = 0; s < m.count; ++s)
+        most = std::max(most, (long long)m.n[s][0] * m.n[s][1] * m.n[s][2]);
+    return dim3(nblk(most, 256), m.count);
+}
+
+void launch_take(const Geo& g, const SliceMap& m, TakeMode mode, int positive, int* bad, int* bad_host,
+                 hipStream_t s) {
+    const dim3 gs = slice_grid(m), bs(256);
+    switch (mode) {
+        case TakeMode::check:
+            hipLaunchKernelGGL((k_take<1, false>), gs, bs, 0, s, g, m, positive, bad, bad_host);
+            break;
+        case TakeMode::check_write:
+            hipLaunchKernelGGL((k_take<3, false>), gs, bs, 0, s, g, m, positive, bad, bad_host);
+            break;
+        case TakeMode::write_if_good:
+            hipLaunchKernelGGL((k_take<6, false>), gs, bs, 0, s, g, m, positive, bad, bad_host);
+            break;
+        case TakeMode::flat_check_write:
+            hipLaunchKernelGGL((k_take<7, true>), gs, bs, 0, s, g, m, positive, bad, bad_host);
+            break;
+    }
+}
+
+void launch_give(const Geo& g, const SliceMap& m, hipStream_t s) {
+    hipLaunchKernelGGL(k_give, slice_grid(m), dim3(256), 0, s, g, m);
 }
 
 void launch_unpack_active(const Geo& g, const int shp[3], const double* a, uint8_t* dst,

@@ -86,6 +86,10 @@ long long set_count(const Geo& g, int set) {
     return (long long)shp[0] * shp[1] * shp[2];
 }
 
+std::string bad_value(const char* what, int positive) {
+    return std::string(what) + (positive ? ": non-finite or non-positive value" : ": non-finite value");
+}
+
 // stream-ordered check of a staged array: returns true if all values valid
 int check_stage(vfs_ctx* ctx, const double* v, long long n, int positive, const char* what) {
     HIPCHK(hipMemsetAsync(ctx->flag, 0, sizeof(int), ctx->stream));
@@ -93,39 +97,113 @@ int check_stage(vfs_ctx* ctx, const double* v, long long n, int positive, const 
     HIPCHK(hipMemcpyAsync(ctx->flag_host, ctx->flag, sizeof(int), hipMemcpyDeviceToHost,
                           ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
-    if (*ctx->flag_host)
-        return fail(ctx, VFS_EINVAL,
-                    std::string(what) + (positive ? ": non-finite or non-positive value"
-                                                  : ": non-finite value"));
+    const int bad = *ctx->flag_host;
+    *ctx->flag_host = 0;
+    if (bad) {
+        HIPCHK(hipMemsetAsync(ctx->flag, 0, sizeof(int), ctx->stream));
+        return fail(ctx, VFS_EINVAL, bad_value(what, positive));
+    }
     return VFS_OK;
 }
 
-// user (host or device) compact array of a weight set -> padded device slice
-int put_set(vfs_ctx* ctx, int set, const double* user, double* dst, int positive,
-            const char* what) {
-    int shp[3];
-    set_shape(ctx->g, set, shp);
-    const long long n = (long long)shp[0] * shp[1] * shp[2];
-    HIPCHK(hipMemcpyAsync(ctx->stage, user, (size_t)n * sizeof(double), hipMemcpyDefault,
-                          ctx->stream));
-    int rc = check_stage(ctx, ctx->stage, n, positive, what);
-    if (rc) return rc;
-    launch_pack(ctx->g, shp, ctx->stage, dst, ctx->stream);
-    HIPCHK(hipGetLastError());
-    return VFS_OK;
+// Whether kernels may use the caller's memory as it is: device memory of the
+// current GPU, aligned to its elements.  Other memory goes through the staging
+// array.
+bool direct(const double* user) {
+    if (!user || (uintptr_t)user % sizeof(double)) return false;
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, user) != hipSuccess) {
+        (void)hipGetLastError();   // host memory that HIP does not know
+        return false;
+    }
+    int dev = -1;
+    return hipGetDevice(&dev) == hipSuccess && at.type == hipMemoryTypeDevice && at.device == dev;
 }
 
-// padded device slice of a weight set -> user (host or device) compact array
-int get_set(vfs_ctx* ctx, int set, const double* src, double* user) {
-    int shp[3];
-    set_shape(ctx->g, set, shp);
-    const long long n = (long long)shp[0] * shp[1] * shp[2];
-    launch_unpack(ctx->g, shp, src, ctx->stage, ctx->stream);
+bool direct(const double* const* user, int count) {
+    for (int q = 0; q < count; ++q)
+        if (!direct(user[q])) return false;
+    return true;
+}
+
+void map_slice(SliceMap& m, const Geo& g, int set, const double* user, const double* pad) {
+    const int q = m.count++;
+    m.user[q] = const_cast<double*>(user);
+    m.pad[q] = const_cast<double*>(pad);
+    set_shape(g, set, m.n[q]);
+}
+
+// Waits for the takes since the flags were last read (0 from then on, on the
+// device as on the host).  Returns the number of the first bad array, or -1.
+int taken(vfs_ctx* ctx, int* first_bad) {
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(user, ctx->stage, (size_t)n * sizeof(double), hipMemcpyDefault,
-                          ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
+    *first_bad = -1;
+    for (int q = 5; q >= 0; --q) {
+        if (ctx->flag_host[q]) *first_bad = q;
+        ctx->flag_host[q] = 0;
+    }
+    if (*first_bad >= 0) HIPCHK(hipMemsetAsync(ctx->flag, 0, sizeof(int), ctx->stream));
     return VFS_OK;
+}
+
+// user (host or device) compact arrays of weight sets -> padded device slices.
+// An array with a bad value changes neither its slice nor a later one.
+int put_sets(vfs_ctx* ctx, int count, const int* sets, const double* const* users, double* const* dsts,
+             int positive, const char* what) {
+    if (direct(users, count)) {
+        SliceMap m{};
+        for (int q = 0; q < count; ++q) map_slice(m, ctx->g, sets[q], users[q], dsts[q]);
+        launch_take(ctx->g, m, TakeMode::check, positive, ctx->flag, ctx->flag_host, ctx->stream);
+        launch_take(ctx->g, m, TakeMode::write_if_good, positive, ctx->flag, ctx->flag_host, ctx->stream);
+        int bad;
+        int rc = taken(ctx, &bad);
+        if (!rc && bad >= 0) rc = fail(ctx, VFS_EINVAL, bad_value(what, positive));
+        return rc;
+    }
+    for (int q = 0; q < count; ++q) {
+        int shp[3];
+        set_shape(ctx->g, sets[q], shp);
+        const long long n = (long long)shp[0] * shp[1] * shp[2];
+        HIPCHK(hipMemcpyAsync(ctx->stage, users[q], (size_t)n * sizeof(double), hipMemcpyDefault,
+                              ctx->stream));
+        int rc = check_stage(ctx, ctx->stage, n, positive, what);
+        if (rc) return rc;
+        launch_pack(ctx->g, shp, ctx->stage, dsts[q], ctx->stream);
+        HIPCHK(hipGetLastError());
+    }
+    return VFS_OK;
+}
+
+int put_set(vfs_ctx* ctx, int set, const double* user, double* dst, int positive, const char* what) {
+    return put_sets(ctx, 1, &set, &user, &dst, positive, what);
+}
+
+// padded device slices -> user (host or device) compact arrays
+int get_sets(vfs_ctx* ctx, int count, const int* sets, const double* const* srcs, double* const* users) {
+    if (direct(users, count)) {
+        SliceMap m{};
+        for (int q = 0; q < count; ++q) map_slice(m, ctx->g, sets[q], users[q], srcs[q]);
+        launch_give(ctx->g, m, ctx->stream);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipStreamSynchronize(ctx->stream));
+        return VFS_OK;
+    }
+    for (int q = 0; q < count; ++q) {
+        int shp[3];
+        set_shape(ctx->g, sets[q], shp);
+        const long long n = (long long)shp[0] * shp[1] * shp[2];
+        launch_unpack(ctx->g, shp, srcs[q], ctx->stage, ctx->stream);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipMemcpyAsync(users[q], ctx->stage, (size_t)n * sizeof(double), hipMemcpyDefault,
+                              ctx->stream));
+        HIPCHK(hipStreamSynchronize(ctx->stream));
+    }
+    return VFS_OK;
+}
+
+int get_set(vfs_ctx* ctx, int set, const double* src, double* user) {
+    return get_sets(ctx, 1, &set, &src, &user);
 }
 
 int face_set(int a) { return 1 + a; }
@@ -839,35 +917,50 @@ int recover_internal(vfs_ctx* ctx) {
     return VFS_OK;
 }
 
+// user sample-order vector -> padded work vector (its old values are lost)
 int pack_samples(vfs_ctx* ctx, const double* user, double* dst) {
     const Geo& g = ctx->g;
+    const double* users[6];
+    int sets[6];
     long long off = 0;
     for (int s = 0; s < g.nsamp(); ++s) {
-        const int set = sample_set(g.dim, s);
-        int shp[3];
-        set_shape(g, set, shp);
-        const long long n = (long long)shp[0] * shp[1] * shp[2];
-        HIPCHK(hipMemcpyAsync(ctx->stage, user + off, (size_t)n * sizeof(double),
-                              hipMemcpyDefault, ctx->stream));
-        int rc = check_stage(ctx, ctx->stage, n, 0, "vector");
-        if (rc) return rc;
-        launch_pack(g, shp, ctx->stage, dst + s * g.NP, ctx->stream);
-        off += n;
+        sets[s] = sample_set(g.dim, s);
+        users[s] = user + off;
+        off += set_count(g, sets[s]);
     }
-    HIPCHK(hipGetLastError());
+    if (direct(user)) {
+        SliceMap m{};
+        for (int s = 0; s < g.nsamp(); ++s) map_slice(m, g, sets[s], users[s], dst + s * g.NP);
+        launch_take(g, m, TakeMode::check_write, 0, ctx->flag, ctx->flag_host, ctx->stream);
+        int bad;
+        int rc = taken(ctx, &bad);
+        if (!rc && bad >= 0) {   // work vectors stay finite
+            HIPCHK(hipMemsetAsync(dst, 0, (size_t)g.nsamp() * g.NP * sizeof(double), ctx->stream));
+            rc = fail(ctx, VFS_EINVAL, bad_value("vector", 0));
+        }
+        return rc;
+    }
+    for (int s = 0; s < g.nsamp(); ++s) {
+        double* to = dst + s * g.NP;
+        int rc = put_sets(ctx, 1, sets + s, users + s, &to, 0, "vector");
+        if (rc) return rc;
+    }
     return VFS_OK;
 }
 
 int unpack_samples(vfs_ctx* ctx, const double* src, double* user) {
     const Geo& g = ctx->g;
+    const double* srcs[6];
+    double* users[6];
+    int sets[6];
     long long off = 0;
     for (int s = 0; s < g.nsamp(); ++s) {
-        const int set = sample_set(g.dim, s);
-        int rc = get_set(ctx, set, src + s * g.NP, user + off);
-        if (rc) return rc;
-        off += set_count(g, set);
+        sets[s] = sample_set(g.dim, s);
+        srcs[s] = src + s * g.NP;
+        users[s] = user + off;
+        off += set_count(g, sets[s]);
     }
-    return VFS_OK;
+    return get_sets(ctx, g.nsamp(), sets, srcs, users);
 }
 
 }  // namespace
@@ -1100,13 +1193,14 @@ int vfs_create(vfs_ctx** out, int dim, int nx, int ny, int nz, double h, const d
 #undef ALLOC
     if (hipHostMalloc((void**)&ctx->sc_host, 4 * sizeof(Scalars), hipHostMallocDefault) !=
             hipSuccess ||
-        hipHostMalloc((void**)&ctx->flag_host, 4 * sizeof(int), hipHostMallocDefault) !=
+        hipHostMalloc((void**)&ctx->flag_host, 8 * sizeof(int), hipHostMallocDefault) !=
             hipSuccess ||
         hipHostMalloc((void**)&ctx->tile_count_host, 8 * sizeof(int), hipHostMallocDefault) !=
             hipSuccess) {
         vfs_destroy(ctx);
         return fail(nullptr, VFS_ENOMEM, "hipHostMalloc failed");
     }
+    std::fill(ctx->flag_host, ctx->flag_host + 8, 0);
     for (auto& e : ctx->ev) {
         if (hipEventCreate(&e) != hipSuccess) {
             vfs_destroy(ctx);
@@ -1136,6 +1230,26 @@ int vfs_set_level_sets(vfs_ctx* ctx, const double* phi_liquid, const double* phi
     if (!ctx) return VFS_EINVAL;
     if (!phi_liquid) return fail(ctx, VFS_EINVAL, "phi_liquid is NULL");
     const long long n = node_count(ctx->g);
+    if (direct(phi_liquid) && (!phi_solid || direct(phi_solid))) {
+        // a bad liquid level set keeps the solid one from being taken
+        const double* from[2] = {phi_liquid, phi_solid};
+        double* to[2] = {ctx->phi_l, ctx->phi_s};
+        for (int q = 0; q < (phi_solid ? 2 : 1); ++q) {
+            SliceMap m{1, q, {const_cast<double*>(from[q])}, {to[q]}, {}};
+            m.n[0][0] = ctx->g.nx + 1;
+            m.n[0][1] = ctx->g.ny + 1;
+            m.n[0][2] = ctx->g.dim == 3 ? ctx->g.nz + 1 : 1;
+            launch_take(ctx->g, m, TakeMode::flat_check_write, 0, ctx->flag, ctx->flag_host, ctx->stream);
+        }
+        int bad;
+        int rc = taken(ctx, &bad);
+        if (!rc && bad >= 0) rc = fail(ctx, VFS_EINVAL, bad_value(bad ? "phi_solid" : "phi_liquid", 0));
+        if (rc) return rc;
+        ctx->has_solid = phi_solid != nullptr;
+        ctx->have_phi = true;
+        ctx->assembled = false;
+        return VFS_OK;
+    }
     HIPCHK(hipMemcpyAsync(ctx->phi_l, phi_liquid, (size_t)n * sizeof(double), hipMemcpyDefault,
                           ctx->stream));
     int rc = check_stage(ctx, ctx->phi_l, n, 0, "phi_liquid");
@@ -1175,11 +1289,15 @@ int vfs_set_viscosity(vfs_ctx* ctx, const double* mu) {
 int vfs_set_velocity(vfs_ctx* ctx, const double* u, const double* v, const double* w) {
     if (!ctx) return VFS_EINVAL;
     const double* comp[3] = {u, v, w};
-    for (int a = 0; a < ctx->g.dim; ++a) {
-        if (!comp[a]) return fail(ctx, VFS_EINVAL, "velocity component is NULL");
-        int rc = put_set(ctx, face_set(a), comp[a], ctx->u + a * ctx->g.NP, 0, "velocity");
-        if (rc) return rc;
+    double* dst[3];
+    int sets[3], given = 0;
+    for (; given < ctx->g.dim && comp[given]; ++given) {
+        dst[given] = ctx->u + given * ctx->g.NP;
+        sets[given] = face_set(given);
     }
+    int rc = given ? put_sets(ctx, given, sets, comp, dst, 0, "velocity") : VFS_OK;
+    if (rc) return rc;
+    if (given < ctx->g.dim) return fail(ctx, VFS_EINVAL, "velocity component is NULL");
     ctx->have_u = true;
     ctx->u_from_step = false;
     ctx->assembled = false;
@@ -1343,14 +1461,13 @@ int vfs_step(vfs_ctx* ctx, double dt) {
     ctx->u_from_step = true;
     ctx->have_x = true;
     HIPCHK(hipEventRecord(ctx->ev[3], s));
-    HIPCHK(hipEventSynchronize(ctx->ev[3]));
+    Scalars sc{};
+    rc = read_scalars(ctx, 0, &sc);   // waits for the step
+    if (rc) return rc;
     ctx->stats.t_assemble_ms = elapsed(ctx->ev[0], ctx->ev[1]);
     ctx->stats.t_solve_ms = elapsed(ctx->ev[1], ctx->ev[2]);
     ctx->stats.t_recover_ms = elapsed(ctx->ev[2], ctx->ev[3]);
     ctx->stats.t_step_ms = elapsed(ctx->ev[0], ctx->ev[3]);
-    Scalars sc{};
-    rc = read_scalars(ctx, 0, &sc);
-    if (rc) return rc;
     ctx->stats.n_active = sc.n_active;
     return status;
 }
@@ -1388,12 +1505,16 @@ int vfs_solve(vfs_ctx* ctx, const double* b, double* x) {
 int vfs_get_velocity(vfs_ctx* ctx, double* u, double* v, double* w) {
     if (!ctx) return VFS_EINVAL;
     double* comp[3] = {u, v, w};
+    double* users[3];
+    const double* srcs[3];
+    int sets[3], count = 0;
     for (int a = 0; a < ctx->g.dim; ++a) {
         if (!comp[a]) continue;
-        int rc = get_set(ctx, face_set(a), ctx->u + a * ctx->g.NP, comp[a]);
-        if (rc) return rc;
+        users[count] = comp[a];
+        srcs[count] = ctx->u + a * ctx->g.NP;
+        sets[count++] = face_set(a);
     }
-    return VFS_OK;
+    return count ? get_sets(ctx, count, sets, srcs, users) : VFS_OK;
 }
 
 int vfs_get_pressure(vfs_ctx* ctx, double* p) {

@@ -417,6 +417,19 @@ void launch_pcg_check(const double* part, int nb, Scalars* S, hipStream_t st);
 // packing and checks (k_util.hip)
 void launch_pack(const Geo& g, const int shp[3], const double* src, double* dst, hipStream_t s);
 void launch_unpack(const Geo& g, const int shp[3], const double* src, double* dst, hipStream_t s);
+// up to six compact arrays of the caller's and their padded slices
+struct SliceMap {
+    int count, first;   // arrays; number of the first one's bad flag
+    double* user[6];
+    double* pad[6];
+    int n[6][3];
+};
+enum class TakeMode { check, check_write, write_if_good, flat_check_write };
+// checks the caller's arrays and copies them to the slices; a bad value of array
+// s sets bit s of *bad and bad_host[s] (pinned memory)
+void launch_take(const Geo& g, const SliceMap& m, TakeMode mode, int positive, int* bad, int* bad_host,
+                 hipStream_t s);
+void launch_give(const Geo& g, const SliceMap& m, hipStream_t s);
 void launch_unpack_active(const Geo& g, const int shp[3], const double* a, uint8_t* dst,
                           hipStream_t s);
 void launch_check(const double* v, long long n, int positive, int* flag, hipStream_t s);
