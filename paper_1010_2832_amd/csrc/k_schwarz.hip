@@ -13,16 +13,25 @@
 // relaxed at once.  z = sum over subdomains I of W_I G_I W_I r, W_I =
 // diag(m^-1/2), m the number of extended bricks holding the sample's anchor
 // (a symmetric partition of unity on the overlap): with OV = 0 the bricks are
-// disjoint (m = 1, block symmetric Gauss-Seidel); with OV > 0 the launches
-// take the bricks in 2^d colour classes whose extended bricks do not overlap,
-// so each class adds its corrections without write conflicts.
+// disjoint (m = 1, block symmetric Gauss-Seidel); with OV > 0 the corrections
+// are added in the order of 2^d colour classes of bricks, whose extended bricks
+// do not overlap (where the buffer below cannot be had, by a launch of each
+// class, which adds without write conflicts).
 //
 // One workgroup per brick, one thread per anchor of the extended brick: the
 // thread keeps r, a = W_L active, c = W_F W_L / mu (stresses), D^-1 and the
 // local iterate x of its anchor's samples in registers, and the workgroup
 // keeps the face coefficients K (one anchor beyond the extended brick) and the
-// face values g in LDS.  (A_loc x)_s is evaluated matrix-free from the same
-// stencils as the apply kernels:
+// face values g in LDS.  Overlapping bricks leave their corrections in a buffer
+// and a second kernel adds them up: one launch of all bricks, whose neighbours
+// find their inputs in the L2, where eight launches of a class each fetched 170
+// MB.  One application at 96 x 112 x 80 (1.9 million active samples) took 424 us
+// and now 196: 142 of the bricks (217 MB fetched, and 24 colours, each a round
+// trip through LDS and a barrier) and 54 of the sums (230 MB).  A thread for two
+// anchors, one of each parity, so that no lane idles in a colour, took 224: it
+// has half the waves to hide both behind.
+// (A_loc x)_s is evaluated matrix-free from the same stencils as the apply
+// kernels:
 //   (A x)_s = a_s sum_f sigma_fs K_f g_f + c_s x_s [+ (1/2) min(c_xx, c_yy) x
 //   of the other diagonal stress in 3D],  g_f = sum_t sigma_ft a_t x_t,
 // with x = 0 outside the subdomain.
@@ -86,11 +95,20 @@ struct SgsArgs {
     double* z;
     int nb[3];        // bricks per axis
     int cls[3];       // brick class of this launch (parity per axis), -1: every brick
+    double* out;      // overlapping bricks: the corrections, brick by brick, or null
+    int* has;         // with out: the brick has active samples
     int accumulate;   // z += correction (overlapping bricks) or z = correction
     const int* done;  // skip when set (a converged solve)
     const RowBits* rows;   // 3D row bits (active sample slices per row half) or null
     int rntx;              // x tiles of the row bits
 };
+
+constexpr int kXcds = 8, kBrickRows = 4;
+
+// m^-1/2 of 1, 2, 4 or 8 bricks
+__device__ __forceinline__ double root_weight(int m) {
+    return m == 1 ? 1.0 : (m == 2 ? 1.0 / sqrt(2.0) : (m == 4 ? 0.5 : 1.0 / sqrt(8.0)));
+}
 
 // threads of a brick workgroup: one per anchor of the extended brick
 template <int DIM, int B, int OV>
@@ -117,7 +135,18 @@ __global__ __launch_bounds__((BrickShape<DIM, B, OV>::T)) void k_sgs_bricks(Geo 
 
     // brick of this workgroup
     int bi[3] = {0, 0, 0};
-    {
+    long long brick = blockIdx.x;
+    if (OV > 0 && s.out) {
+        // every XCD takes rows of bricks along x, kBrickRows neighbours at a time:
+        // bricks of a row share cache lines
+        const int xcd = blockIdx.x % kXcds, t = blockIdx.x / kXcds;
+        const int row = (t / (kBrickRows * s.nb[0]) * kXcds + xcd) * kBrickRows + t / s.nb[0] % kBrickRows;
+        bi[0] = t % s.nb[0];
+        bi[1] = row % s.nb[1];
+        bi[2] = row / s.nb[1];
+        if (row >= s.nb[1] * s.nb[2]) return;
+        brick = (long long)row * s.nb[0] + bi[0];
+    } else {
         long long w = blockIdx.x;
         for (int a = 0; a < DIM; ++a) {
             const int cnt = s.cls[a] < 0 ? s.nb[a] : (s.nb[a] - s.cls[a] + 1) / 2;
@@ -143,7 +172,7 @@ __global__ __launch_bounds__((BrickShape<DIM, B, OV>::T)) void k_sgs_bricks(Geo 
             const int J = id[a] / B, t = id[a] % B;
             m *= 1 + ((t == 0 && J >= 1) ? 1 : 0) + ((t == B - 1 && J + 1 < s.nb[a]) ? 1 : 0);
         }
-        return 1.0 / sqrt((double)m);
+        return root_weight(m);
     };
 
     // this thread's anchor (anchors outside 0..n are absent)
@@ -167,7 +196,10 @@ __global__ __launch_bounds__((BrickShape<DIM, B, OV>::T)) void k_sgs_bricks(Geo 
                     any |= s.rows[t + (long long)s.rntx * (rj + (long long)(nmax[1] + 1) * rk)];
             }
         }
-        if (!__syncthreads_or(any)) {
+        any = __syncthreads_or(any);
+        if (OV > 0 && s.out && l == 0) s.has[brick] = any;
+        if (!any) {
+            if (OV > 0 && s.out) return;
             if (in && !s.accumulate)
                 for (int q = 0; q < S::NS; ++q) s.z[q * NP + o] = 0.0;
             return;
@@ -213,13 +245,14 @@ __global__ __launch_bounds__((BrickShape<DIM, B, OV>::T)) void k_sgs_bricks(Geo 
             // samples of one colour share no face: their updates of the face
             // values below never meet
             if (mine && par_l == par && av[q] != 0.0) {
-                double y = 0.0;
+                double y = 0.0, gv[S::ST];
 #pragma unroll
                 for (int t = 0; t < S::ST; ++t) {
                     const Term tm = samp_term<DIM>(q, t);
                     if (tm.s == 0) continue;
                     const int fe = fidx(tm);
-                    y += (double)tm.s * sk[tm.q][fe] * sg[tm.q][fe];
+                    gv[t] = sg[tm.q][fe];
+                    y += (double)tm.s * sk[tm.q][fe] * gv[t];
                 }
                 const double aq = av[q];
                 y *= aq;
@@ -234,7 +267,7 @@ __global__ __launch_bounds__((BrickShape<DIM, B, OV>::T)) void k_sgs_bricks(Geo 
                 for (int t = 0; t < S::ST; ++t) {
                     const Term tm = samp_term<DIM>(q, t);
                     if (tm.s == 0) continue;
-                    sg[tm.q][fidx(tm)] += (double)tm.s * aq * dx;
+                    sg[tm.q][fidx(tm)] = gv[t] + (double)tm.s * aq * dx;
                 }
             }
             __syncthreads();
@@ -242,6 +275,13 @@ __global__ __launch_bounds__((BrickShape<DIM, B, OV>::T)) void k_sgs_bricks(Geo 
     }
 
     // write (or add) the correction of the active samples
+    if (OV > 0 && s.out) {
+        if (mine) {
+#pragma unroll
+            for (int q = 0; q < S::NS; ++q) s.out[(brick * S::NS + q) * NE + l] = xv[q];
+        }
+        return;
+    }
     if (in) {
 #pragma unroll
         for (int q = 0; q < S::NS; ++q) {
@@ -252,6 +292,55 @@ __global__ __launch_bounds__((BrickShape<DIM, B, OV>::T)) void k_sgs_bricks(Geo 
             }
         }
     }
+}
+
+// z from the corrections that the overlapping bricks left in s.out: an anchor
+// adds those of the bricks that hold it, weighted, in the order of their classes
+// (parity of the brick's index, x fastest), as one launch per class would.
+template <int DIM, int B>
+__global__ __launch_bounds__(256) void k_sgs_gather(Geo g, SgsArgs s) {
+    using S = Shape<DIM>;
+    using BS = BrickShape<DIM, B, 1>;
+    constexpr int E = BS::E;
+    if (s.done && *s.done) return;
+    const int id[3] = {(int)(blockIdx.x * blockDim.x + threadIdx.x),
+                       (int)(blockIdx.y * blockDim.y + threadIdx.y),
+                       (int)(blockIdx.z * blockDim.z + threadIdx.z)};
+    if (id[0] > g.nx || id[1] > g.ny || (DIM == 3 && id[2] > g.nz)) return;
+    const long long o = DIM == 2 ? g.idx(id[0], id[1]) : g.idx(id[0], id[1], id[2]);
+    int brick[3][2], m = 1;   // per axis and parity: the brick that holds the index, or -1
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        const int J = id[a] / B, t = id[a] % B;
+        const int other = t == 0 ? J - 1 : (t == B - 1 && J + 1 < s.nb[a] ? J + 1 : -1);
+        brick[a][J & 1] = J;
+        brick[a][~J & 1] = other;
+        m *= other >= 0 ? 2 : 1;
+    }
+    const double w = root_weight(m);
+    double z[S::NS] = {};
+    bool act[S::NS];
+#pragma unroll
+    for (int q = 0; q < S::NS; ++q) act[q] = s.a[q * g.NP + o] != 0.0;
+#pragma unroll
+    for (int c = 0; c < 1 << DIM; ++c) {
+        long long bk = 0;
+        int at = 0;
+        bool use = true;
+#pragma unroll
+        for (int a = DIM - 1; a >= 0; --a) {
+            const int J = brick[a][(c >> a) & 1];
+            use = use && J >= 0;
+            bk = bk * s.nb[a] + J;
+            at = at * E + id[a] - J * B + 1;
+        }
+        if (!use || (s.rows && !s.has[bk])) continue;
+#pragma unroll
+        for (int q = 0; q < S::NS; ++q)
+            if (act[q]) z[q] += w * s.out[(bk * S::NS + q) * BS::NE + at];
+    }
+#pragma unroll
+    for (int q = 0; q < S::NS; ++q) s.z[q * g.NP + o] = z[q];
 }
 
 // ---- PCG on the padded FP64 vectors (slot sc of the context's scalars) ----
@@ -474,6 +563,10 @@ void sgs_launch(const Geo& g, const SgsArgs& base, hipStream_t st) {
     const int n[3] = {g.nx, g.ny, g.nz};
     SgsArgs s = base;
     for (int a = 0; a < 3; ++a) s.nb[a] = a < DIM ? (n[a] + 1 + B - 1) / B : 1;
+    auto launch = [&](long long bricks) {
+        hipLaunchKernelGGL((k_sgs_bricks<DIM, B, OV>), dim3((unsigned)bricks),
+                           dim3(BrickShape<DIM, B, OV>::T), 0, st, g, s);
+    };
     if (OV == 0) {
         long long nbk = 1;
         for (int a = 0; a < DIM; ++a) {
@@ -482,10 +575,22 @@ void sgs_launch(const Geo& g, const SgsArgs& base, hipStream_t st) {
         }
         for (int a = DIM; a < 3; ++a) s.cls[a] = -1;
         s.accumulate = 0;
-        hipLaunchKernelGGL((k_sgs_bricks<DIM, B, OV>), dim3((unsigned)nbk),
-                           dim3(BrickShape<DIM, B, OV>::T), 0, st, g, s);
+        launch(nbk);
         return;
     }
+    if (s.out) {   // every brick at once, then the sums
+        s.accumulate = 0;
+        for (int a = 0; a < 3; ++a) s.cls[a] = -1;
+        const int rows = s.nb[1] * s.nb[2], span = kXcds * kBrickRows;
+        hipLaunchKernelGGL((k_sgs_bricks<DIM, B, OV>), dim3((rows + span - 1) / span * span * s.nb[0]),
+                           dim3(BrickShape<DIM, B, OV>::T), 0, st, g, s);
+        const dim3 bs = DIM == 2 ? dim3(64, 4) : dim3(32, 4, 2);
+        hipLaunchKernelGGL((k_sgs_gather<DIM, B>),
+                           dim3(g.nx / bs.x + 1, g.ny / bs.y + 1, DIM == 3 ? g.nz / bs.z + 1 : 1), bs, 0, st,
+                           g, s);
+        return;
+    }
+    launch_fill(s.z, (long long)g.nsamp() * g.NP, 0.0, st);
     s.accumulate = 1;
     for (int cls = 0; cls < (1 << DIM); ++cls) {
         long long nbk = 1;
@@ -498,8 +603,7 @@ void sgs_launch(const Geo& g, const SgsArgs& base, hipStream_t st) {
             }
         }
         if (nbk == 0) continue;
-        hipLaunchKernelGGL((k_sgs_bricks<DIM, B, OV>), dim3((unsigned)nbk),
-                           dim3(BrickShape<DIM, B, OV>::T), 0, st, g, s);
+        launch(nbk);
     }
 }
 
@@ -510,10 +614,20 @@ int schwarz_brick(int dim, int overlap) {
     return dim == 2 ? 16 : 4;
 }
 
+// bricks of a grid, and the values of their corrections, with overlap
+void schwarz_space(const Geo& g, long long* bricks, long long* values) {
+    const int n[3] = {g.nx, g.ny, g.nz}, B = schwarz_brick(g.dim, 1);
+    *bricks = 1;
+    for (int a = 0; a < g.dim; ++a) *bricks *= n[a] / B + 1;
+    *values = *bricks * g.nsamp() * (g.dim == 2 ? BrickShape<2, 16, 1>::NE : BrickShape<3, 4, 1>::NE);
+}
+
 void launch_schwarz(const Geo& g, int overlap, const double* r, const double* a, const double* c,
                     const double* dinv, const double* K, const RowBits* rows, double* z,
-                    const int* done, hipStream_t st) {
+                    const int* done, double* bricks, int* has, hipStream_t st) {
     SgsArgs s{};
+    s.out = overlap > 0 ? bricks : nullptr;
+    s.has = has;
     s.rows = g.dim == 3 ? rows : nullptr;
     s.rntx = (g.nx + kRow3X) / kRow3X;
     s.r = r;
@@ -523,7 +637,6 @@ void launch_schwarz(const Geo& g, int overlap, const double* r, const double* a,
     s.K = K;
     s.z = z;
     s.done = done;
-    if (overlap > 0) launch_fill(z, (long long)g.nsamp() * g.NP, 0.0, st);
     if (g.dim == 2) {
         if (overlap > 0)
             sgs_launch<2, 16, 1>(g, s, st);

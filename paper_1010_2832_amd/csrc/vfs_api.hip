@@ -738,7 +738,7 @@ int solve_schwarz(vfs_ctx* ctx, const double* b, double* x) {
                 const bool timed = ctx->prof && k == 0;
                 if (timed) HIPCHK(hipEventRecord(ctx->pev[3], s));
                 launch_schwarz(g, overlap, r, ctx->a, ctx->c, ctx->dinv, ctx->K, ctx->rowbits, z,
-                               done, s);
+                               done, ctx->bricks, ctx->brick_has, s);
                 if (timed) HIPCHK(hipEventRecord(ctx->pev[0], s));
                 launch_pcg_dot(g, rl, r, z, part, done, s);
                 launch_pcg_rz(part, nb, S, s);
@@ -1040,7 +1040,7 @@ int vfs_destroy(vfs_ctx* ctx) {
                     ctx->K32,   ctx->a32,   ctx->c32,  ctx->dinv32, ctx->x,      ctx->r,
                     ctx->p0,    ctx->p1,    ctx->q,    ctx->z,      ctx->x32,    ctx->r32,
                     ctx->p032,  ctx->p132,  ctx->q32,  ctx->z32,    ctx->partials, ctx->counter,
-                    ctx->sc,    ctx->flag,  ctx->stage, ctx->netvec, ctx->netpart, ctx->netcoef,
+                    ctx->bricks, ctx->sc,    ctx->flag,  ctx->stage, ctx->netvec, ctx->netpart, ctx->netcoef,
                     ctx->f32b,  ctx->fpart, ctx->ybc, ctx->adv_a, ctx->adv_b, ctx->adv_ka,
                     ctx->adv_kb, ctx->phi_tmp, ctx->ead32, ctx->res_part};
     for (void* p : bufs)
@@ -1425,6 +1425,18 @@ int vfs_set_solver(vfs_ctx* ctx, int precond, int precision, double rel_tol, int
     if (!(rel_tol > 0.0) || !(rel_tol < 1.0)) return fail(ctx, VFS_EINVAL, "rel_tol must be in (0,1)");
     if (max_iter < 1) return fail(ctx, VFS_EINVAL, "max_iter must be >= 1");
     if (!(w_min >= 0.0) || !(w_min < 0.5)) return fail(ctx, VFS_EINVAL, "w_min must be in [0,0.5)");
+    if (precond == VFS_PRECOND_SCHWARZ && !ctx->bricks) {
+        // without room for the bricks' corrections they are added class by class
+        long long bricks, values;
+        schwarz_space(ctx->g, &bricks, &values);
+        if (hipMalloc((void**)&ctx->bricks, (size_t)values * sizeof(double) + (size_t)bricks * sizeof(int)) ==
+            hipSuccess) {
+            ctx->brick_has = (int*)(ctx->bricks + values);
+        } else {
+            ctx->bricks = nullptr;
+            (void)hipGetLastError();
+        }
+    }
     ctx->precond = precond;
     ctx->precision = precision;
     ctx->tol = rel_tol;

@@ -259,6 +259,8 @@ struct vfs_ctx {
     vfs::Scalars* sc_host = nullptr; // pinned mirror
     int* flag = nullptr;             // device: input validation flag
     int* flag_host = nullptr;        // pinned
+    double* bricks = nullptr;        // corrections of the overlapping Schwarz bricks
+    int* brick_has = nullptr;
 
     // staging for user copies (device, compact)
     double* stage = nullptr;
@@ -398,9 +400,12 @@ long long row_items(const Geo& g);
 int row_list_chunks(const Geo& g);
 void launch_row_list(const Geo& g, const RowBits* rows, int* list, int* cnt, hipStream_t st);
 int schwarz_brick(int dim, int overlap);
+void schwarz_space(const Geo& g, long long* bricks, long long* values);
+// bricks, has: room for the overlapping bricks' corrections and flags (NULL: one
+// launch per class of bricks)
 void launch_schwarz(const Geo& g, int overlap, const double* r, const double* a, const double* c,
                     const double* dinv, const double* K, const RowBits* rows, double* z,
-                    const int* done, hipStream_t st);
+                    const int* done, double* bricks, int* has, hipStream_t st);
 int pcg_blocks(const Geo& g);
 void launch_pcg_dot(const Geo& g, const RowList& rl, const double* u, const double* v,
                     double* part, const int* done, hipStream_t st);
