@@ -295,16 +295,27 @@ int res2d_shape(const vfs_ctx* ctx, int word) {
     return -1;
 }
 
-// Brick shape of the resident 3D solve, or -1 (FP64 has the first alone).
-int res3d_shape(const vfs_ctx* ctx, int word) {
+// Brick shape of the resident 3D solve, or -1: small bricks, one to a compute
+// unit; more of them, in FP32 twice as large, in FP64 two to a unit.
+int res3d_shape(vfs_ctx* ctx, int word) {
     if (!ctx->res_part || ctx->res_off) return -1;
     const int most = res_most();
-    for (int q = 0; q < (word == 4 ? kRes3dShapes : 1); ++q)
-        if (ctx->res_count[q] > 0 && ctx->res_count[q] <= most) return q;
-    return -1;
+    auto fits = [&](int q, int n) { return ctx->res_count[q] > 0 && ctx->res_count[q] <= n; };
+    if (fits(0, most)) return 0;
+    if (word == 4) return fits(1, most) ? 1 : -1;
+    if (!fits(0, 2 * most) || !res3d_two()) return -1;
+    if (!ctx->res_stream) {   // 54 MB, for the solves that use it
+        const size_t bytes = (size_t)res3d_stream(2 * most) * sizeof(double);
+        if (hipMalloc((void**)&ctx->res_stream, bytes) != hipSuccess) {
+            ctx->res_stream = nullptr;
+            (void)hipGetLastError();
+            return -1;
+        }
+    }
+    return 2;
 }
 
-int res_shape(const vfs_ctx* ctx, int word) {
+int res_shape(vfs_ctx* ctx, int word) {
     return ctx->g.dim == 2 ? res2d_shape(ctx, word) : res3d_shape(ctx, word);
 }
 
@@ -316,25 +327,28 @@ int run_resident(vfs_ctx* ctx, int shape, Vecs<T>& v, bool set_bb, int max_iter,
                  bool* gave_up) {
     hipStream_t s = ctx->stream;
     if (ctx->res_stamp > 0xfffffff0u - (unsigned)max_iter - 8u) {   // stamps would wrap
-        HIPCHK(hipMemsetAsync(ctx->res_part, 0, 2 * kResMost * 16 * sizeof(*ctx->res_part), s));
+        const size_t part = (ctx->g.dim == 2 ? 2 * kResMost : 4 * kRes3dMost) * 16;
+        HIPCHK(hipMemsetAsync(ctx->res_part, 0, part * sizeof(*ctx->res_part), s));
         HIPCHK(hipMemsetAsync(ctx->res_msg, 0, ctx->res_msg_words * sizeof(*ctx->res_msg), s));
         ctx->res_stamp = 0;
     }
     std::lock_guard<std::mutex> one(res_mutex());
     if (ctx->prof) HIPCHK(hipEventRecord(ctx->pev[0], s));
-    const int* list = ctx->res_lists + shape * kResMost;
     if (ctx->g.dim == 2) {
+        const int* list = ctx->res_lists + shape * kResMost;
         launch_resident2d<T>(ctx->g, shape, list, ctx->res_count[shape], v.r, v.x, v.dinv, v.a, v.c, v.K,
                              ctx->res_part, ctx->res_msg, ctx->res_stamp, set_bb, ctx->sc, s);
     } else {
+        const int bricks = shape == 1 ? 1 : 0;
+        const int* list = ctx->res_lists + bricks * kRes3dMost;
         const T* e;
         if constexpr (sizeof(T) == 4)
             e = ctx->ead32;
         else
             e = v.dinv;
-        launch_resident3d<T>(ctx->g, shape, list, ctx->res_rank[shape], ctx->res_count[shape], v.r, v.x, e,
-                             v.a, v.c, v.K, ctx->res_part, ctx->res_msg, ctx->res_stamp, set_bb,
-                             fused3d_pair(ctx->ftiles), fused3d_folds(ctx->g), ctx->sc, s);
+        launch_resident3d<T>(ctx->g, shape, list, ctx->res_rank[bricks], ctx->res_count[bricks], v.r, v.x, e,
+                             v.a, v.c, v.K, ctx->res_stream, ctx->res_part, ctx->res_msg, ctx->res_stamp,
+                             set_bb, fused3d_pair(ctx->ftiles), fused3d_folds(ctx->g), ctx->sc, s);
     }
     if (ctx->prof) HIPCHK(hipEventRecord(ctx->pev[1], s));
     HIPCHK(hipGetLastError());
@@ -871,7 +885,7 @@ int assemble_internal(vfs_ctx* ctx, double dt) {
         if (ctx->res_part)
             for (int q = 0; q < kRes3dShapes; ++q)
                 launch_res3d_lists(g, q, ctx->a, ctx->tile_flags, ctx->res_flags,
-                                   ctx->res_lists + q * kResMost, ctx->res_rank[q],
+                                   ctx->res_lists + q * kRes3dMost, ctx->res_rank[q],
                                    ctx->tile_count + 2 + q, s);
         ctx->rowlist_n = -1;   // the row list follows the new row bits
         HIPCHK(hipMemcpyAsync(ctx->tile_count_host, ctx->tile_count, (2 + kRes3dShapes) * sizeof(int),
@@ -1040,7 +1054,7 @@ int vfs_destroy(vfs_ctx* ctx) {
                     ctx->K32,   ctx->a32,   ctx->c32,  ctx->dinv32, ctx->x,      ctx->r,
                     ctx->p0,    ctx->p1,    ctx->q,    ctx->z,      ctx->x32,    ctx->r32,
                     ctx->p032,  ctx->p132,  ctx->q32,  ctx->z32,    ctx->partials, ctx->counter,
-                    ctx->bricks, ctx->sc,    ctx->flag,  ctx->stage, ctx->netvec, ctx->netpart, ctx->netcoef,
+                    ctx->bricks, ctx->res_stream, ctx->sc,    ctx->flag,  ctx->stage, ctx->netvec, ctx->netpart, ctx->netcoef,
                     ctx->f32b,  ctx->fpart, ctx->ybc, ctx->adv_a, ctx->adv_b, ctx->adv_ka,
                     ctx->adv_kb, ctx->phi_tmp, ctx->ead32, ctx->res_part};
     for (void* p : bufs)
@@ -1147,8 +1161,8 @@ int vfs_create(vfs_ctx** out, int dim, int nx, int ny, int nz, double h, const d
         ALLOC(ctx->ftile_flags, nf);
         ALLOC(ctx->ftile_list, nf);
         ALLOC(ctx->rowbits, row_bytes(g));
-        // the resident solve holds at most 256 bricks; on grids up to about 130^3
-        // that can be a thin or small body of liquid, or half of a 60^3 box
+        // the resident solve holds at most 256 or 512 bricks; on grids up to about
+        // 130^3 that can be a thin or small body of liquid, or half of a 60^3 box
         if (NP <= 3000000) {
             long long nb[kRes3dShapes], most = 0, all = 0;
             for (int q = 0; q < kRes3dShapes; ++q) {
@@ -1158,7 +1172,7 @@ int vfs_create(vfs_ctx** out, int dim, int nx, int ny, int nz, double h, const d
                 most = std::max(most, nb[q]);
                 all += nb[q];
             }
-            const long long part = 2 * kResMost * 16, lists = kRes3dShapes * kResMost;
+            const long long part = 4 * kRes3dMost * 16, lists = kRes3dShapes * kRes3dMost;
             ctx->res_msg_words = res3d_words();
             // one allocation: words, messages, then lists, ranks and flags
             ALLOC(ctx->res_part, part + ctx->res_msg_words + (lists + all + most + 1) / 2);

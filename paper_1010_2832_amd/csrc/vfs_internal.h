@@ -31,7 +31,7 @@ namespace vfs {
 using LLWordBuf = unsigned long long*;
 constexpr int kResShapes = 4;
 constexpr int kResMost = 256;
-constexpr int kRes3dShapes = 2;
+constexpr int kRes3dShapes = 2, kRes3dMost = 512;   // 3D: two workgroups may share a unit
 
 constexpr int kFront = 32;   // elements before the body (128-byte rows, see make_geo)
 // 3D kernels run at most this many workgroups, each looping over tiles, so
@@ -285,6 +285,7 @@ struct vfs_ctx {
     int* res_list64 = nullptr;       // 64 x 8 tiles, their partial sums
     double* res_part64 = nullptr;
     int res_count64 = 0;
+    double* res_stream = nullptr;   // 3D FP64, two bricks to a unit: their fields
     int* res_rank[vfs::kRes3dShapes] = {};   // 3D: workgroup of every brick
     unsigned res_stamp = 0;
     bool res_off = false;
@@ -505,16 +506,18 @@ template <typename T>
 void launch_resident2d(const Geo& g, int shape, const int* tiles, int count, const T* r, T* x,
                        const T* dinv, const T* a, const T* c, const T* K, LLWordBuf part,
                        LLWordBuf msg, unsigned stamp, bool set_bb, Scalars* sc, hipStream_t s);
-// resident 3D CG (k_resident3d.hip) over bricks of 8 x 8 x 8 (shape 0) or, in
-// FP32, 16 x 8 x 8 anchors (shape 1); e = a D^-1 (FP64: D^-1); pair and fold: what the
+// resident 3D CG (k_resident3d.hip) over bricks of 8 x 8 x 8 (shape 0; shape 2, in
+// FP64: two to a compute unit) or, in FP32, 16 x 8 x 8 anchors (shape 1); e = a D^-1 (FP64: D^-1); pair and fold: what the
 // launched iteration would do (its Tiles::split, its folded column)
 void res3d_lattice(const Geo& g, int shape, int& nbx, int& nby, int& nbz);
 long long res3d_words();
+bool res3d_two();                  // shape 2 fits
+long long res3d_stream(int n);     // its buffer, in doubles, for n bricks
 void launch_res3d_lists(const Geo& g, int shape, const double* a, const int* tile_flags, int* flags,
                         int* list, int* rank, int* count, hipStream_t s);
 template <typename T>
 void launch_resident3d(const Geo& g, int shape, const int* list, const int* rank, int count, const T* r,
-                       T* x, const T* e, const T* a, const T* c, const T* K, LLWordBuf part,
+                       T* x, const T* e, const T* a, const T* c, const T* K, double* buf, LLWordBuf part,
                        LLWordBuf msg, unsigned stamp, bool set_bb, bool pair, bool fold, Scalars* sc,
                        hipStream_t s);
 bool fused3d_pair(const Tiles& ft);

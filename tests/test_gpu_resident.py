@@ -92,7 +92,7 @@ def test_resident_batch_keeps_the_iterates_of_the_persistent_kernel():
 # one brick is 8 x 8 x 8 anchors (cells + 1), 16 x 8 x 8 in FP32 when those are
 # more than the compute units: one brick, a full one, one anchor more, several,
 # the folded column of the launched iteration (64), the wide bricks (48 cells a
-# side) and more bricks than fit
+# side), FP64 two to a unit (56 and 60) and more bricks than fit
 @pytest.mark.parametrize("n", [(6, 5, 6), (7, 7, 7), (8, 8, 8), (15, 16, 17), (64, 9, 12), (9, 40, 11)])
 @pytest.mark.parametrize("precision,tol,bar", [(0, 1e-11, 1e-6), (1, 1e-9, 1e-4)])
 def test_resident3d_brick_edges(n, precision, tol, bar):
@@ -105,7 +105,7 @@ def test_resident3d_brick_edges(n, precision, tol, bar):
 
 
 @pytest.mark.parametrize("n,precision", [((30, 33, 31), 0), ((48, 48, 48), 0), ((48, 48, 48), 1),
-                                         ((65, 47, 63), 1), ((96, 80, 72), 0), ((96, 80, 72), 1)])
+                                         ((65, 47, 63), 1), ((56, 56, 56), 0), ((60, 71, 63), 0), ((96, 80, 72), 0), ((96, 80, 72), 1)])
 def test_resident3d_shapes(n, precision):
     tol = 1e-8
     print(f"resident 3D pool {n} precision {precision}", flush=True)
