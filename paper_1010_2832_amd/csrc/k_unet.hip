@@ -82,24 +82,32 @@ __device__ __forceinline__ long long tap_off(const Level& L, int t) {
 // ---------------------------------------------------------------------------
 // convolution (forward and input gradient)
 // ---------------------------------------------------------------------------
-template <int CIN, int COUT>
+// A wave's tile: NV groups of 16 voxels, MT of 16 output channels.  Large where
+// voxels abound (a weight operand feeds NV products); on the coarse levels that
+// leaves most of the chip idle (8^3 voxels, 128 to 64 channels: 2 workgroups, 122
+// us), and a wave takes 16 voxels and 16 channels, a workgroup each (18 us; 64 to
+// 32 channels at 16^3 40 and 14; at 28 x 26 x 24, 68 workgroups, 40 and 35).  The
+// sum over K is the same either way.
+template <int CIN, int COUT, bool SMALL>
 struct ConvShape {
     static constexpr int KP = conv_kp(CIN);
     static constexpr int NKC = KP / 32;
-    static constexpr int MT = COUT / 16;               // output-channel tiles
-    static constexpr int NV = COUT >= 128 ? 2 : 4;      // 16-voxel tiles per wave
-    static constexpr int VPB = 4 * 16 * NV;             // voxels per workgroup
+    static constexpr int MT = SMALL ? 1 : COUT / 16;                // output-channel tiles
+    static constexpr int NV = SMALL ? 1 : (COUT >= 128 ? 2 : 4);     // 16-voxel tiles per wave
+    static constexpr int WAVES = SMALL ? 1 : 4;
+    static constexpr int VPB = WAVES * 16 * NV;                      // voxels per workgroup
 };
 
-template <int CIN, int COUT, int EPI>
-__global__ __launch_bounds__(CT) void k_conv3(ConvArgs A) {
+template <int CIN, int COUT, int EPI, bool SMALL>
+__global__ __launch_bounds__((ConvShape<CIN, COUT, SMALL>::WAVES * 64)) void k_conv3(ConvArgs A) {
     if (A.skip && *A.skip) return;
-    using S = ConvShape<CIN, COUT>;
+    using S = ConvShape<CIN, COUT, SMALL>;
     constexpr int KP = S::KP, NKC = S::NKC, MT = S::MT, NV = S::NV;
+    const int mt0 = blockIdx.y * MT;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const Level L = A.L;
     const long long V = L.voxels();
-    const long long vbase = ((long long)blockIdx.x * 4 + wave) * (16 * NV);
+    const long long vbase = ((long long)blockIdx.x * S::WAVES + wave) * (16 * NV);
     if (vbase >= V) return;   // the wave has no voxel; no workgroup barrier follows
     long long vof[NV];
     bool valid[NV];
@@ -115,8 +123,9 @@ __global__ __launch_bounds__(CT) void k_conv3(ConvArgs A) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[nv][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int kq = lane >> 4;
-    const uint16_t* wrow = A.w + (long long)(lane & 15) * KP + kq * 8;
+    const uint16_t* wrow = A.w + (long long)(mt0 * 16 + (lane & 15)) * KP + kq * 8;
     const bf16x8 zero8 = __builtin_bit_cast(bf16x8, uint4{0u, 0u, 0u, 0u});
+#pragma unroll(SMALL ? (CIN == 128 ? 12 : 6) : 1)
     for (int kc = 0; kc < NKC; ++kc) {
         const int K = kc * 32 + kq * 8;
         const int t = K / CIN, ci = K % CIN;
@@ -143,7 +152,7 @@ __global__ __launch_bounds__(CT) void k_conv3(ConvArgs A) {
         const long long v = vbase + nv * 16 + (lane & 15);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            const int co0 = mt * 16 + kq * 4;
+            const int co0 = (mt0 + mt) * 16 + kq * 4;
             float o[4] = {acc[nv][mt][0], acc[nv][mt][1], acc[nv][mt][2], acc[nv][mt][3]};
             if (EPI == EPI_F32) {
                 if (co0 < 8)
@@ -176,7 +185,7 @@ __global__ __launch_bounds__(CT) void k_conv3(ConvArgs A) {
 // and the 27 taps read their operands from LDS, while the weight operands of
 // a lane stay in registers for the whole launch.
 //
-// Workgroup: a 32 x ZY voxel tile in x,y marching kZZ planes in z.  LDS holds
+// Workgroup: a 32 x ZY voxel tile in x,y marching up to kZZ planes in z.  LDS holds
 // a ring of 4 input planes of 34 x (ZY + 2) voxels, each split into CIN / 8
 // arrays of 8 channels (16 bytes per voxel, so the 16 lanes of one MFMA
 // column group read 256 contiguous bytes).  Step z: issue the global loads of
@@ -187,7 +196,7 @@ __global__ __launch_bounds__(CT) void k_conv3(ConvArgs A) {
 // 2 kc + 1 (tap 27, for kc = 13 and kq >= 2, is the zero padding of K); with
 // 32 they all read tap kc, 8 channels per lane group.
 // ---------------------------------------------------------------------------
-constexpr int kZX = 32, kZZ = 16;   // output tile in x and z (ZY in y)
+constexpr int kZX = 32, kZZ = 16, kZLeast = 2;   // output tile in x, most and fewest planes (ZY in y)
 
 template <int CIN, int ZY>
 struct ZTile {
@@ -200,7 +209,7 @@ struct ZTile {
 };
 
 template <int CIN, int COUT, int ZY, int EPI>
-__global__ __launch_bounds__(CT) void k_conv3_z(ConvArgs A, int ntx, int nty, int ntz) {
+__global__ __launch_bounds__(CT) void k_conv3_z(ConvArgs A, int ntx, int nty, int zc) {
     if (A.skip && *A.skip) return;
     using Z = ZTile<CIN, ZY>;
     static_assert(CIN == 16 || CIN == 32, "input channels");
@@ -219,8 +228,8 @@ __global__ __launch_bounds__(CT) void k_conv3_z(ConvArgs A, int ntx, int nty, in
         tile = x8 * q + min(x8, rem) + (b >> 3);
     }
     const int tx = tile % ntx, ty = (tile / ntx) % nty, tz = tile / (ntx * nty);
-    const int x0 = tx * kZX, y0 = ty * ZY, z0 = tz * kZZ;
-    const int zend = min(z0 + kZZ, L.Z);
+    const int x0 = tx * kZX, y0 = ty * ZY, z0 = tz * zc;
+    const int zend = min(z0 + zc, L.Z);
 
     // weight operands: row co = 16 mt + n, K = 32 kc + 8 kq .. +7
     bf16x8 a[NKC][MT];
@@ -329,31 +338,205 @@ __global__ __launch_bounds__(CT) void k_conv3_z(ConvArgs A, int ntx, int nty, in
 template <int CIN, int COUT, int ZY, int EPI>
 void conv_launch_z(const ConvArgs& a, hipStream_t s) {
     const int ntx = (a.L.X + kZX - 1) / kZX, nty = (a.L.Y + ZY - 1) / ZY;
-    const int ntz = (a.L.Z + kZZ - 1) / kZZ;
+    if (ntx * nty == 0 || a.L.Z == 0) return;
+    // planes a workgroup marches: 16, or fewer, down to 2 (the first reads three),
+    // where that leaves compute units idle: at 32^3, 16 to 32 channels, 8 workgroups
+    // took 48 us and 64 take 12.6; at 64^3, 16 to 16, 64 took 37 and 512 take 19
+    const int want = std::min(a.L.Z, (512 + ntx * nty - 1) / (ntx * nty));
+    const int zc = std::max(std::min(kZZ, (a.L.Z + want - 1) / want), kZLeast);
+    const int ntz = (a.L.Z + zc - 1) / zc;
     const long long nb = (long long)ntx * nty * ntz;
-    if (nb == 0) return;
     hipLaunchKernelGGL((k_conv3_z<CIN, COUT, ZY, EPI>), dim3((unsigned)nb), dim3(CT), 0, s, a, ntx,
-                       nty, ntz);
+                       nty, zc);
 }
+
+constexpr unsigned kConvFew = 256;
 
 template <int CIN, int COUT, int EPI>
 void conv_launch(const ConvArgs& a, hipStream_t s) {
-    using S = ConvShape<CIN, COUT>;
+    using S = ConvShape<CIN, COUT, false>;
     const long long V = a.L.voxels();
     const unsigned nb = (unsigned)((V + S::VPB - 1) / S::VPB);
     if (nb == 0) return;
-    hipLaunchKernelGGL((k_conv3<CIN, COUT, EPI>), dim3(nb), dim3(CT), 0, s, a);
+    if (nb < kConvFew)   // fewer than the compute units
+        hipLaunchKernelGGL((k_conv3<CIN, COUT, EPI, true>), dim3((unsigned)((V + 15) / 16), COUT / 16), dim3(64),
+                           0, s, a);
+    else
+        hipLaunchKernelGGL((k_conv3<CIN, COUT, EPI, false>), dim3(nb), dim3(CT), 0, s, a);
 }
 
 // ---------------------------------------------------------------------------
-// weight gradient: per (voxel chunk, tap) workgroup, the COUT x CIN product
-// of the output gradient and the tap-shifted input over the chunk.  Each
-// wave stages 32 voxels of both operands in LDS per step and reads them
-// transposed as MFMA operands (the reduction runs over voxels); the four
-// waves' sums are added in wave order.
+// weight gradient: the COUT x CIN products of the output gradient and the
+// tap-shifted input, summed over voxels.  The reduction runs over voxels, so both
+// operands are read transposed.
+//
+// Full and half resolution (few channels, many voxels): a workgroup takes all 27
+// taps of a 32 x 4 voxel tile marching in z, so that input and gradient are read
+// once and not once a tap (64^3, 16 to 16 channels: 450 MB from the L2 and 94 us, now
+// 24).  Of two products' worth of channels three workgroups share a tile's taps by
+// their step in z, as 27 more products would not fit (32^3, 16 to 32: 13 us).
+// Planes lie in LDS channel by channel, x running along: a lane's 8 voxels are 16
+// consecutive bytes, those of the taps left and right of it the same shifted by
+// two.  A wave has a row of the tile and 27 products in registers; the four waves'
+// are added in wave order.
 // ---------------------------------------------------------------------------
+constexpr int kWgX = 32, kWgY = 4, kWgPitch = 40;   // tile; row of a channel in LDS
+
+struct WgradTiles {
+    int ntx, nty, ntz, zc;   // tiles, planes of one
+    int chunks() const { return ntx * nty * ntz; }
+};
+
+template <int CIN, int COUT, int ND>
+__global__ __launch_bounds__(CT) void k_wgrad_z(const uint16_t* __restrict__ in,
+                                                const uint16_t* __restrict__ g, Level L,
+                                                float* __restrict__ part, WgradTiles W, const int* skip) {
+    if (skip && *skip) return;
+    constexpr int MT = COUT / 16, NTc = CIN / 16;
+    constexpr int RX = kWgX + 2, RY = kWgY + 2;
+    constexpr int IN = RY * RX * (CIN / 8), OUT = kWgY * kWgX * (COUT / 8);   // 16-byte items of a plane
+    constexpr int LI = (IN + CT - 1) / CT, LO = (OUT + CT - 1) / CT;
+    constexpr int TAPS = 9 * ND;
+    const int dz0 = ND == 3 ? 0 : blockIdx.y;   // first of the workgroup's taps in z
+    struct Planes {
+        uint16_t x[ND == 3 ? 4 : 2][RY][CIN][kWgPitch];
+        uint16_t y[2][kWgY][COUT][kWgPitch];
+    };
+    union Smem {
+        Planes p;
+        float red[TAPS * COUT * CIN];
+    };
+    __shared__ __align__(16) Smem sm;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int kq = lane >> 4, col = lane & 15;
+    const int tx = blockIdx.x % W.ntx, ty = (blockIdx.x / W.ntx) % W.nty, tz = blockIdx.x / (W.ntx * W.nty);
+    const int x0 = tx * kWgX, y0 = ty * kWgY, z0 = tz * W.zc, z1 = min(z0 + W.zc, L.Z);
+
+    // plane zz of the input (with a ring of voxels) and of the gradient; voxels
+    // fastest, so that a wave writes neighbouring places of a channel
+    auto fetch_x = [&](int zz, uint4 (&r)[LI]) {
+#pragma unroll
+        for (int m = 0; m < LI; ++m) {
+            const int e = threadIdx.x + m * CT, u = e % RX, h = e / RX % (CIN / 8), v = e / (RX * (CIN / 8));
+            r[m] = uint4{0u, 0u, 0u, 0u};
+            const int x = x0 - 1 + u, y = y0 - 1 + v;
+            if (e < IN && x <= L.X && y <= L.Y && zz <= L.Z)
+                r[m] = *reinterpret_cast<const uint4*>(in + L.off(x, y, zz) * CIN + h * 8);
+        }
+    };
+    auto fetch_g = [&](int zz, uint4 (&r)[LO]) {
+#pragma unroll
+        for (int m = 0; m < LO; ++m) {
+            const int e = threadIdx.x + m * CT, u = e % kWgX, h = e / kWgX % (COUT / 8),
+                      v = e / (kWgX * (COUT / 8));
+            r[m] = uint4{0u, 0u, 0u, 0u};
+            if (e < OUT && x0 + u < L.X && y0 + v < L.Y && zz < L.Z)
+                r[m] = *reinterpret_cast<const uint4*>(g + L.off(x0 + u, y0 + v, zz) * COUT + h * 8);
+        }
+    };
+    auto spread = [](uint16_t* to, const uint4& r) {   // 8 channels of a voxel
+        const uint32_t w[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+        for (int j = 0; j < 8; ++j) to[j * kWgPitch] = (uint16_t)(w[j >> 1] >> (16 * (j & 1)));
+    };
+    auto commit_x = [&](int zz, const uint4 (&r)[LI]) {
+#pragma unroll
+        for (int m = 0; m < LI; ++m) {
+            const int e = threadIdx.x + m * CT, u = e % RX, h = e / RX % (CIN / 8), v = e / (RX * (CIN / 8));
+            if (e < IN) spread(&sm.p.x[(zz + 4) & (ND == 3 ? 3 : 1)][v][h * 8][u], r[m]);
+        }
+    };
+    auto commit_g = [&](int zz, const uint4 (&r)[LO]) {
+#pragma unroll
+        for (int m = 0; m < LO; ++m) {
+            const int e = threadIdx.x + m * CT, u = e % kWgX, h = e / kWgX % (COUT / 8),
+                      v = e / (kWgX * (COUT / 8));
+            if (e < OUT) spread(&sm.p.y[zz & 1][v][h * 8][u], r[m]);
+        }
+    };
+
+    f32x4 acc[TAPS][MT][NTc];
+#pragma unroll
+    for (int t = 0; t < TAPS; ++t)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NTc; ++nt) acc[t][mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    uint4 px[LI], pg[LO];
+    for (int zz = z0 - 1; zz < z0 - 1 + ND; ++zz) {
+        fetch_x(zz + dz0, px);
+        commit_x(zz + dz0, px);
+    }
+    fetch_g(z0, pg);
+    commit_g(z0, pg);
+    __syncthreads();
+    for (int z = z0; z < z1; ++z) {
+        const bool more = z + 1 < z1;
+        if (more) {
+            fetch_x(z + ND - 1 + dz0, px);
+            fetch_g(z + 1, pg);
+        }
+        bf16x8 av[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+            av[mt] = ld16(&sm.p.y[z & 1][wave][mt * 16 + col][8 * kq]);
+#pragma unroll
+        for (int q = 0; q < 3 * ND; ++q) {
+            const int dz = q / 3, dy = q % 3;
+#pragma unroll
+            for (int nt = 0; nt < NTc; ++nt) {
+                const uint16_t* row = &sm.p.x[(z + dz + dz0 - 1 + 4) & (ND == 3 ? 3 : 1)][wave + dy][nt * 16 + col][8 * kq];
+                const uint4 b = *reinterpret_cast<const uint4*>(row);
+                const uint32_t e = *reinterpret_cast<const uint32_t*>(row + 8);
+                const uint4 s[3] = {b,
+                                    {b.x >> 16 | b.y << 16, b.y >> 16 | b.z << 16, b.z >> 16 | b.w << 16,
+                                     b.w >> 16 | e << 16},
+                                    {b.y, b.z, b.w, e}};
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        acc[3 * q + dx][mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            av[mt], __builtin_bit_cast(bf16x8, s[dx]), acc[3 * q + dx][mt][nt], 0, 0, 0);
+            }
+        }
+        // plane z + 2 replaces plane z - 2, and the gradient's z + 1 its z - 1, which
+        // no wave reads any more
+        if (more) {
+            commit_x(z + ND - 1 + dz0, px);
+            commit_g(z + 1, pg);
+        }
+        __syncthreads();
+    }
+    // D[co = mt*16 + 4 kq + i][ci = nt*16 + col]
+    for (int w = 0; w < 4; ++w) {
+        if (wave == w) {
+#pragma unroll
+            for (int t = 0; t < TAPS; ++t)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int nt = 0; nt < NTc; ++nt)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            float& r = sm.red[(t * COUT + mt * 16 + kq * 4 + i) * CIN + nt * 16 + col];
+                            r = w == 0 ? acc[t][mt][nt][i] : r + acc[t][mt][nt][i];
+                        }
+        }
+        __syncthreads();
+    }
+    float* dst = part + ((long long)blockIdx.x * 27 + 9 * dz0) * COUT * CIN;
+    for (int e = threadIdx.x; e < TAPS * COUT * CIN; e += CT) dst[e] = sm.red[e];
+}
+
+// Coarse levels (many channels, few voxels): a workgroup takes one tap, a chunk of
+// voxels and 32 output channels.  Each wave stages 32 voxels of both operands in
+// LDS per step and reads them transposed; the four waves' sums are added in wave
+// order.  (With all output channels and 2048 voxels a workgroup there were 27 of
+// them at 8^3, 50 us, against 11 and 14 now.)
 constexpr int kWgradStep = 32;
-constexpr int kWgradTarget = 2048;   // voxels per chunk (before rounding)
+constexpr int kWgradTarget = 2048;   // most voxels per chunk (before rounding)
+constexpr int kWgradCo = 32;         // output channels of a workgroup
 
 template <int CIN, int COUT>
 __global__ __launch_bounds__(CT) void k_wgrad(const uint16_t* __restrict__ in,
@@ -361,19 +544,19 @@ __global__ __launch_bounds__(CT) void k_wgrad(const uint16_t* __restrict__ in,
                                               float* __restrict__ part, int chunk_vox,
                                               const int* skip) {
     if (skip && *skip) return;
-    constexpr int MT = COUT / 16, NTc = CIN / 16;
-    constexpr int STAGE = 4 * kWgradStep * (COUT + CIN) * 2;
-    constexpr int RED = COUT * CIN * 4;
+    constexpr int CO = kWgradCo, MT = CO / 16, NTc = CIN / 16;
+    constexpr int STAGE = 4 * kWgradStep * (CO + CIN) * 2;
+    constexpr int RED = CO * CIN * 4;
     constexpr int SMEM = STAGE > RED ? STAGE : RED;
     __shared__ __align__(16) unsigned char smem[SMEM];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int t = blockIdx.y;
+    const int t = blockIdx.y, c0 = blockIdx.z * CO;
     const long long V = L.voxels();
     const long long v0 = (long long)blockIdx.x * chunk_vox;
     const long long v1 = v0 + chunk_vox < V ? v0 + chunk_vox : V;
     const long long to = tap_off(L, t);
-    uint16_t* sG = reinterpret_cast<uint16_t*>(smem) + wave * kWgradStep * (COUT + CIN);
-    uint16_t* sX = sG + kWgradStep * COUT;
+    uint16_t* sG = reinterpret_cast<uint16_t*>(smem) + wave * kWgradStep * (CO + CIN);
+    uint16_t* sX = sG + kWgradStep * CO;
     f32x4 acc[MT][NTc];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
@@ -383,12 +566,12 @@ __global__ __launch_bounds__(CT) void k_wgrad(const uint16_t* __restrict__ in,
     const int kq = lane >> 4, col = lane & 15;
     for (int s0 = 0; s0 < nsteps; s0 += 4) {
         const long long vs = v0 + (long long)(s0 + wave) * kWgradStep;
-        for (int e = lane; e < kWgradStep * (COUT / 8); e += 64) {
-            const int vi = e / (COUT / 8), cb = (e % (COUT / 8)) * 8;
+        for (int e = lane; e < kWgradStep * (CO / 8); e += 64) {
+            const int vi = e / (CO / 8), cb = (e % (CO / 8)) * 8;
             const long long v = vs + vi;
             uint4 val{0u, 0u, 0u, 0u};
-            if (v < v1) val = *reinterpret_cast<const uint4*>(g + voxel_off(L, v) * COUT + cb);
-            *reinterpret_cast<uint4*>(sG + vi * COUT + cb) = val;
+            if (v < v1) val = *reinterpret_cast<const uint4*>(g + voxel_off(L, v) * COUT + c0 + cb);
+            *reinterpret_cast<uint4*>(sG + vi * CO + cb) = val;
         }
         for (int e = lane; e < kWgradStep * (CIN / 8); e += 64) {
             const int vi = e / (CIN / 8), cb = (e % (CIN / 8)) * 8;
@@ -401,7 +584,7 @@ __global__ __launch_bounds__(CT) void k_wgrad(const uint16_t* __restrict__ in,
         bf16x8 av[MT], bv[NTc];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
-            av[mt] = gather8(sG + kq * 8 * COUT + mt * 16 + col, COUT);
+            av[mt] = gather8(sG + kq * 8 * CO + mt * 16 + col, CO);
 #pragma unroll
         for (int nt = 0; nt < NTc; ++nt)
             bv[nt] = gather8(sX + kq * 8 * CIN + nt * 16 + col, CIN);
@@ -429,22 +612,32 @@ __global__ __launch_bounds__(CT) void k_wgrad(const uint16_t* __restrict__ in,
         }
         __syncthreads();
     }
-    float* dst = part + ((long long)blockIdx.x * 27 + t) * COUT * CIN;
-    for (int e = threadIdx.x; e < COUT * CIN; e += CT) dst[e] = red[e];
+    float* dst = part + (((long long)blockIdx.x * 27 + t) * COUT + c0) * CIN;
+    for (int e = threadIdx.x; e < CO * CIN; e += CT) dst[e] = red[e];
 }
 
-__global__ void k_wgrad_reduce(int cin, int cout, int cout_real, const float* __restrict__ part,
-                               int chunks, float* __restrict__ grad, float scale) {
-    const long long n = (long long)cout_real * cin * 27;
-    for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n;
-         e += (long long)gridDim.x * blockDim.x) {
-        const int t = (int)(e % 27);
-        const long long oc = e / 27;
-        const int ci = (int)(oc % cin), co = (int)(oc / cin);
-        float s = 0.f;
-        for (int c = 0; c < chunks; ++c) s += part[(((long long)c * 27 + t) * cout + co) * cin + ci];
-        grad[e] += scale * s;
+// Adds the chunks' products to the gradient: a wave a quarter of the chunks, in
+// order, then the quarters.  Threads follow the products' layout (input channel
+// fastest): following the gradient's, tap fastest, every load was a line of its own
+// and the 128 chunks of a 64^3 layer took 20 us (now 5).
+__global__ __launch_bounds__(CT) void k_wgrad_reduce(int cin, int cout, int cout_real,
+                                                     const float* __restrict__ part, int chunks,
+                                                     float* __restrict__ grad, float scale) {
+    __shared__ float sum[4][64];
+    const int n = cout * cin * 27, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int e = blockIdx.x * 64 + lane, per = (chunks + 3) / 4;
+    float s = 0.f;
+    if (e < n) {
+        const int hi = min(chunks, (wave + 1) * per);
+#pragma unroll 16
+        for (int c = wave * per; c < hi; ++c) s += part[(long long)c * n + e];
     }
+    sum[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0 || e >= n) return;
+    const int ci = e % cin, co = (e / cin) % cout, t = e / (cin * cout);
+    if (co >= cout_real) return;
+    grad[(co * cin + ci) * 27 + t] += scale * ((sum[0][lane] + sum[1][lane]) + (sum[2][lane] + sum[3][lane]));
 }
 
 // ---------------------------------------------------------------------------
@@ -942,44 +1135,72 @@ bool launch_conv3(int cin, int cout, int epi, const ConvArgs& a, hipStream_t s) 
     return false;
 }
 
-int wgrad_chunks(const Level& L) {
-    const long long V = L.voxels();
-    return (int)std::max<long long>(1, std::min<long long>(512, (V + kWgradTarget - 1) / kWgradTarget));
+static bool wgrad_marches(int cin, int cout) { return cin * cout <= 512; }
+
+// workgroups that share a tile's 27 taps, by their step in z
+static int wgrad_split(int cin, int cout) { return cin * cout > 256 ? 3 : 1; }
+
+// a third of a tile's time goes to its first three planes: at most about two tiles
+// a compute unit
+static WgradTiles wgrad_tiles(int cin, int cout, const Level& L) {
+    WgradTiles W{(L.X + kWgX - 1) / kWgX, (L.Y + kWgY - 1) / kWgY, 0, 0};
+    const int split = wgrad_split(cin, cout), least = split == 3 ? 2 : 4;
+    const int n = std::max(1, std::min(512 / std::max(1, W.ntx * W.nty * split), (L.Z + least - 1) / least));
+    W.zc = (L.Z + n - 1) / n;
+    W.ntz = (L.Z + W.zc - 1) / W.zc;
+    return W;
 }
 
 static int wgrad_chunk_vox(const Level& L) {
     const long long V = L.voxels();
-    const int c = wgrad_chunks(L);
-    const long long per = (V + c - 1) / c;
-    const long long q = 4 * kWgradStep;
+    const long long most = std::max<long long>(4 * kWgradStep, std::min<long long>(kWgradTarget, V / 16));
+    const long long c = std::max<long long>(1, std::min<long long>(512, (V + most - 1) / most));
+    const long long per = (V + c - 1) / c, q = 4 * kWgradStep;
     return (int)((per + q - 1) / q * q);
+}
+
+int wgrad_chunks(int cin, int cout, const Level& L) {
+    if (wgrad_marches(cin, cout)) return wgrad_tiles(cin, cout, L).chunks();
+    const int cv = wgrad_chunk_vox(L);
+    return (int)std::max<long long>(1, (L.voxels() + cv - 1) / cv);
 }
 
 bool launch_wgrad(int cin, int cout, const uint16_t* in, const uint16_t* g, const Level& L,
                   float* part, const int* skip, hipStream_t s) {
-    const dim3 grid(wgrad_chunks(L), 27);
-    const int cv = wgrad_chunk_vox(L);
-#define VFS_WG(CI, CO)                                                                       \
-    if (cin == CI && cout == CO) {                                                           \
-        hipLaunchKernelGGL((k_wgrad<CI, CO>), grid, dim3(CT), 0, s, in, g, L, part, cv, skip); \
-        return true;                                                                         \
+    const int chunks = wgrad_chunks(cin, cout, L), cv = wgrad_chunk_vox(L);
+    const WgradTiles W = wgrad_tiles(cin, cout, L);
+#define VFS_WGZ(CI, CO)                                                                       \
+    if (cin == CI && cout == CO) {                                                            \
+        static_assert(CI * CO <= 512, "wgrad_marches");                                       \
+        constexpr int ND = CI * CO > 256 ? 1 : 3;                                             \
+        hipLaunchKernelGGL((k_wgrad_z<CI, CO, ND>), dim3(chunks, 3 / ND), dim3(CT), 0, s, in, g, L, part, W, \
+                           skip);                                                             \
+        return true;                                                                          \
     }
-    VFS_WG(16, 16)
-    VFS_WG(32, 16)
+#define VFS_WG(CI, CO)                                                                        \
+    if (cin == CI && cout == CO) {                                                            \
+        static_assert(CI * CO > 512, "wgrad_marches");                                        \
+        hipLaunchKernelGGL((k_wgrad<CI, CO>), dim3(chunks, 27, CO / kWgradCo), dim3(CT), 0, s, in, g, L, \
+                           part, cv, skip);                                                   \
+        return true;                                                                          \
+    }
+    VFS_WGZ(16, 16)
+    VFS_WGZ(32, 16)
+    VFS_WGZ(16, 32)
     VFS_WG(64, 32)
     VFS_WG(128, 64)
     VFS_WG(64, 128)
     VFS_WG(32, 64)
-    VFS_WG(16, 32)
 #undef VFS_WG
+#undef VFS_WGZ
     return false;
 }
 
 void launch_wgrad_reduce(int cin, int cout, int cout_real, const float* part, int chunks,
                          float* grad, float scale, hipStream_t s) {
-    const long long n = (long long)cout_real * cin * 27;
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(grid_for(n)), dim3(CT), 0, s, cin, cout, cout_real, part,
-                       chunks, grad, scale);
+    const int n = cout * cin * 27;
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3((n + 63) / 64), dim3(CT), 0, s, cin, cout, cout_real, part, chunks,
+                       grad, scale);
 }
 
 static unsigned blocks8(const Level& L, int C) {

@@ -70,7 +70,7 @@ bool launch_conv3(int cin, int cout, int epi, const ConvArgs& a, hipStream_t s);
 // Weight gradient partials: part[chunk][t][cout][cin] = sum over the chunk's
 // voxels of g[v][co] * in[v + off_t][ci]; then reduced in chunk order into
 // grad (canonical [co][ci][t] layout, first cout_real rows) scaled by scale.
-int wgrad_chunks(const Level& L);
+int wgrad_chunks(int cin, int cout, const Level& L);
 bool launch_wgrad(int cin, int cout, const uint16_t* in, const uint16_t* g, const Level& L,
                   float* part, const int* skip, hipStream_t s);
 void launch_wgrad_reduce(int cin, int cout, int cout_real, const float* part, int chunks,

@@ -72,7 +72,7 @@ int wgrad(vfs_unet* u, int layer, const uint16_t* in, const uint16_t* g, float s
     const int co = pad16(N.cout);
     if (!launch_wgrad(N.cin, co, in, g, L, u->wpart, nullptr, s))
         return ufail(u, VFS_EINVAL, "unsupported weight-gradient shape");
-    launch_wgrad_reduce(N.cin, co, N.cout, u->wpart, wgrad_chunks(L), u->g + u->poff[layer], scale,
+    launch_wgrad_reduce(N.cin, co, N.cout, u->wpart, wgrad_chunks(N.cin, co, L), u->g + u->poff[layer], scale,
                         s);
     return VFS_OK;
 }
@@ -184,7 +184,7 @@ int net_ensure(vfs_unet* u, const Level& L0, bool grads) {
                            {&u->gp0, 1, 16}, {&u->gc0, 0, 16}};
         size_t part = 0;
         for (int l = 0; l < kNetLayers; ++l)
-            part = std::max(part, (size_t)wgrad_chunks(u->L[kNet[l].level]) * 27 *
+            part = std::max(part, (size_t)wgrad_chunks(kNet[l].cin, pad16(kNet[l].cout), u->L[kNet[l].level]) * 27 *
                                       pad16(kNet[l].cout) * kNet[l].cin);
         size_t bytes = align256(part * sizeof(float));
         for (const auto& t : b) bytes += tensor_bytes(u->L[t.level], t.ch);
