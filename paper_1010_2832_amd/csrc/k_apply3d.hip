@@ -59,6 +59,9 @@ __device__ __forceinline__ void tile_origin(const Tiles& t, const Geo& g, int u,
     kend = min(k0 + kz, g.nz + 1);
 }
 
+__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 template <typename T, int MODE, bool ZIN>
 struct Loader {
     const Geo& g;
@@ -75,10 +78,26 @@ struct Loader {
     T bet[kFcgMax];
     const T* prev[kFcgMax];
 
+    // what a value is made of, loaded ahead of its use (MODE_FDIR: nothing, its
+    // directions are too many)
+    struct Raw {
+        T z, w, p;
+    };
+    __device__ __forceinline__ Raw fetch(long long os) const {
+        Raw v{T(0), T(0), T(0)};
+        if (MODE == MODE_JDIR || MODE == MODE_DIR) {
+            v.z = ZIN ? zs[os] : dinv[os];
+            if (!ZIN) v.w = r[os];
+            if (MODE == MODE_DIR && !first) v.p = pin[os];
+        } else if (MODE != MODE_FDIR) {
+            v.p = pin[os];
+        }
+        return v;
+    }
     // value of slice s at offset os (direction update in MODE_DIR / MODE_FDIR)
-    __device__ __forceinline__ T value(long long os, bool own) const {
+    __device__ __forceinline__ T value(long long os, bool own, const Raw& v) const {
         if (MODE == MODE_JDIR) {
-            const T z = ZIN ? zs[os] : dinv[os] * r[os];
+            const T z = ZIN ? v.z : v.z * v.w;
             if (own && pout) pout[os] = z;
             return z;
         }
@@ -91,15 +110,21 @@ struct Loader {
             return val;
         }
         if (MODE == MODE_DIR) {
-            const T z = ZIN ? zs[os] : dinv[os] * r[os];
-            const T val = first ? z : z + beta * pin[os];
+            const T z = ZIN ? v.z : v.z * v.w;
+            const T val = first ? z : z + beta * v.p;
             if (own) pout[os] = val;
             return val;
         }
-        return pin[os];
+        return v.p;
     }
 };
 
+// A workgroup marches through the planes of its tile.  The inputs of the next but
+// one plane, and the face and output coefficients of the next, are loaded while a
+// plane is worked on: with each load where its value is used a plane took three
+// trips to memory, 6 us (FP32 direction at 64^3 62 and 78 us, now 32 and 38; FP64
+// application at 128 x 96 x 113, 290 MB, 160 us and now 85).  In FP64 that takes
+// 214 to 248 registers, two workgroups a compute unit instead of three.
 template <typename T, int MODE, bool ZIN>
 __global__ __launch_bounds__(NT) void k_apply3d(Geo g, Tiles tl, const T* __restrict__ r,
                                                 const T* __restrict__ zs,
@@ -146,119 +171,162 @@ __global__ __launch_bounds__(NT) void k_apply3d(Geo g, Tiles tl, const T* __rest
     tile_origin(tl, g, wtile, i0, j0, k0, kend);
     T vcur[6], acur[6], vnext[6], anext[6];
     __syncthreads();   // LDS of the previous tile is no longer read
-    // load weighted plane kk into ring slot kk&1; own anchor values -> vo, ao
-    auto load_plane = [&](int kk, T (&vo)[6], T (&ao)[6]) {
-        const int sl = kk & 1;
-        {   // own interior anchor
-            const int i = i0 + tx, j = j0 + ty;
-            const bool in = i <= g.nx + 1 && j <= g.ny + 1 && kk <= g.nz + 1;
-            const bool own = in && i <= g.nx && j <= g.ny && kk >= k0 && kk < kend;
-            const long long o = in ? g.idx(i, j, kk) : 0;
+    using Raw = typename Loader<T, MODE, ZIN>::Raw;
+    Raw raw[2][6];    // of the own anchor and of the halo place
+    T rawa[2][6];
+    // halo ring: rows lj = 0 and HY-1 (HX each), columns li = 0 and HX-1 (TY each)
+    const bool ring = tid < 2 * HX + 2 * TY;
+    int hli = 0, hlj = 0;
+    if (tid < HX) {
+        hli = tid;
+    } else if (tid < 2 * HX) {
+        hli = tid - HX;
+        hlj = HY - 1;
+    } else {
+        const int e = tid - 2 * HX;
+        hlj = 1 + (e >> 1);
+        hli = (e & 1) ? HX - 1 : 0;
+    }
+    // places of the own anchor (0) and of the halo (1) in plane kk
+    auto place = [&](int which, int kk, long long& o) {
+        const int i = which ? i0 - 1 + hli : i0 + tx, j = which ? j0 - 1 + hlj : j0 + ty;
+        const bool in = (which == 0 || ring) && i <= g.nx + 1 && j <= g.ny + 1 && kk <= g.nz + 1;
+        o = in ? g.idx(i, j, kk) : 0;
+        return in;
+    };
+    auto fetch_plane = [&](int kk) {
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            long long o;
+            const bool in = place(w, kk, o);
 #pragma unroll
             for (int s = 0; s < 6; ++s) {
-                T val = T(0), aw = T(0);
+                raw[w][s] = Raw{T(0), T(0), T(0)};
+                rawa[w][s] = T(0);
                 if (in) {
-                    const long long os = o + s * NP;
-                    val = ld.value(os, own);
-                    aw = a[os];
+                    raw[w][s] = ld.fetch(o + s * NP);
+                    rawa[w][s] = a[o + s * NP];
                 }
-                vo[s] = val;
-                ao[s] = aw;
-                sW[sl][s][ty + 1][tx + 1] = aw * val;
             }
         }
-        // halo ring: rows lj = 0 and HY-1 (HX each), columns li = 0 and HX-1 (TY each)
-        if (tid < 2 * HX + 2 * TY) {
-            int li, lj;
-            if (tid < HX) {
-                li = tid;
-                lj = 0;
-            } else if (tid < 2 * HX) {
-                li = tid - HX;
-                lj = HY - 1;
-            } else {
-                const int e = tid - 2 * HX;
-                lj = 1 + (e >> 1);
-                li = (e & 1) ? HX - 1 : 0;
-            }
-            const int i = i0 - 1 + li, j = j0 - 1 + lj;
-            const bool in = i <= g.nx + 1 && j <= g.ny + 1 && kk <= g.nz + 1;
-            const long long o = in ? g.idx(i, j, kk) : 0;
+    };
+    // weighted plane kk into ring slot kk&1; own anchor values -> vo, ao
+    auto commit_plane = [&](int kk, T (&vo)[6], T (&ao)[6]) {
+        const int sl = kk & 1;
+        long long o;
+        bool in = place(0, kk, o);
+        const bool own = in && i0 + tx <= g.nx && j0 + ty <= g.ny && kk >= k0 && kk < kend;
+#pragma unroll
+        for (int s = 0; s < 6; ++s) {
+            vo[s] = in ? ld.value(o + s * NP, own, raw[0][s]) : T(0);
+            ao[s] = rawa[0][s];
+            sW[sl][s][ty + 1][tx + 1] = ao[s] * vo[s];
+        }
+        in = place(1, kk, o);
+        if (ring) {
 #pragma unroll
             for (int s = 0; s < 6; ++s) {
                 T w = T(0);
-                if (in) {
-                    const long long os = o + s * NP;
-                    w = a[os] * ld.value(os, false);
-                }
-                sW[sl][s][lj][li] = w;
+                if (in) w = rawa[1][s] * ld.value(o + s * NP, false, raw[1][s]);
+                sW[sl][s][hlj][hli] = w;
             }
+        }
+    };
+    // coefficients of the faces (two rounds of them) and outputs of plane kk
+    constexpr int NE = (FX * FY + NT - 1) / NT;
+    T kf[NE][3], cf[5];
+    auto u_face = [&](int li, int lj, int kk) {
+        const int i = i0 + li, j = j0 - 1 + lj;
+        return i <= g.nx && j >= 0 && j < g.ny && kk >= 0 && kk < g.nz;
+    };
+    auto v_face = [&](int li, int lj, int kk) {
+        const int i = i0 - 1 + li, j = j0 + lj;
+        return i >= 0 && i < g.nx && j <= g.ny && kk >= 0 && kk < g.nz;
+    };
+    auto w_face = [&](int li, int lj, int kw) {
+        const int i = i0 - 1 + li, j = j0 - 1 + lj;
+        return i >= 0 && i < g.nx && j >= 0 && j < g.ny && kw >= 0 && kw <= g.nz;
+    };
+    auto fetch_faces = [&](int kk) {
+#pragma unroll
+        for (int n = 0; n < NE; ++n) {
+            const int e = tid + NT * n, li = e % FX, lj = e / FX;
+            const bool on = e < FX * FY;
+            kf[n][0] = on && u_face(li, lj, kk) ? K[g.idx(i0 + li, j0 - 1 + lj, kk)] : T(0);
+            kf[n][1] = on && v_face(li, lj, kk) ? K[NP + g.idx(i0 - 1 + li, j0 + lj, kk)] : T(0);
+            kf[n][2] = on && w_face(li, lj, kk + 1) ? K[2 * NP + g.idx(i0 - 1 + li, j0 - 1 + lj, kk + 1)] : T(0);
+        }
+    };
+    auto fetch_outputs = [&](int kk) {
+        const int i = i0 + tx, j = j0 + ty;
+        if (i <= g.nx && j <= g.ny && kk < kend) {
+            const long long o = g.idx(i, j, kk);
+#pragma unroll
+            for (int s = 0; s < 5; ++s) cf[s] = c[(s + 1) * NP + o];
         }
     };
 
     // faces: g_u(kk), g_v(kk) from planes kk, kk+1; g_w(kk+1) from planes kk, kk+1
-    auto faces = [&](int kk, bool uv, bool w) {
+    auto faces = [&](int kk) {
         const int s0 = kk & 1, s1 = (kk + 1) & 1;
-        for (int e = tid; e < FX * FY; e += NT) {
-            const int li = e % FX, lj = e / FX;
-            if (uv) {
-                {   // u face (i0+li, j0-1+lj, kk): weighted indices li (i-1), li+1 (i), lj+...
-                    const int i = i0 + li, j = j0 - 1 + lj;
-                    T gv = T(0);
-                    if (i <= g.nx && j >= 0 && j < g.ny && kk >= 0 && kk < g.nz) {
-                        const T kf = K[g.idx(i, j, kk)];
-                        // P,X at (i-1): [lj][li], (i): [lj][li+1]; E at j: [lj][li+1], j+1: [lj+1][li+1]
-                        const T d = (sW[s0][0][lj][li + 1] - sW[s0][0][lj][li]) +
-                                    (sW[s0][1][lj][li] - sW[s0][1][lj][li + 1]) +
-                                    (sW[s0][3][lj][li + 1] - sW[s0][3][lj + 1][li + 1]) +
-                                    (sW[s0][4][lj][li + 1] - sW[s1][4][lj][li + 1]);
-                        gv = kf * d;
-                    }
-                    gU[s0][lj][li] = gv;
-                }
-                {   // v face (i0-1+li, j0+lj, kk)
-                    const int i = i0 - 1 + li, j = j0 + lj;
-                    T gv = T(0);
-                    if (i >= 0 && i < g.nx && j <= g.ny && kk >= 0 && kk < g.nz) {
-                        const T kf = K[NP + g.idx(i, j, kk)];
-                        // weighted (i): li, (i+1): li+1; (j): lj+1, (j-1): lj
-                        const T d = (sW[s0][0][lj + 1][li] - sW[s0][0][lj][li]) +
-                                    (sW[s0][2][lj][li] - sW[s0][2][lj + 1][li]) +
-                                    (sW[s0][3][lj + 1][li] - sW[s0][3][lj + 1][li + 1]) +
-                                    (sW[s0][5][lj + 1][li] - sW[s1][5][lj + 1][li]);
-                        gv = kf * d;
-                    }
-                    gV[s0][lj][li] = gv;
-                }
+#pragma unroll
+        for (int n = 0; n < NE; ++n) {
+            const int e = tid + NT * n, li = e % FX, lj = e / FX;
+            if (e >= FX * FY) continue;
+            T gv = T(0);
+            if (u_face(li, lj, kk)) {
+                // u face (i0+li, j0-1+lj, kk): weighted indices li (i-1), li+1 (i);
+                // P,X at (i-1): [lj][li], (i): [lj][li+1]; E at j: [lj][li+1], j+1: [lj+1][li+1]
+                const T d = (sW[s0][0][lj][li + 1] - sW[s0][0][lj][li]) +
+                            (sW[s0][1][lj][li] - sW[s0][1][lj][li + 1]) +
+                            (sW[s0][3][lj][li + 1] - sW[s0][3][lj + 1][li + 1]) +
+                            (sW[s0][4][lj][li + 1] - sW[s1][4][lj][li + 1]);
+                gv = kf[n][0] * d;
             }
-            if (w) {   // w face (i0-1+li, j0-1+lj, kk+1): weighted (i): li, (j): lj
-                const int i = i0 - 1 + li, j = j0 - 1 + lj, kw = kk + 1;
-                T gv = T(0);
-                if (i >= 0 && i < g.nx && j >= 0 && j < g.ny && kw >= 0 && kw <= g.nz) {
-                    const T kf = K[2 * NP + g.idx(i, j, kw)];
-                    const T d = (sW[s1][0][lj][li] - sW[s0][0][lj][li]) +
-                                (sW[s1][1][lj][li] - sW[s0][1][lj][li]) +
-                                (sW[s1][2][lj][li] - sW[s0][2][lj][li]) +
-                                (sW[s1][4][lj][li] - sW[s1][4][lj][li + 1]) +
-                                (sW[s1][5][lj][li] - sW[s1][5][lj + 1][li]);
-                    gv = kf * d;
-                }
-                gW[s1][lj][li] = gv;
+            gU[s0][lj][li] = gv;
+            gv = T(0);
+            if (v_face(li, lj, kk)) {
+                // v face (i0-1+li, j0+lj, kk): weighted (i): li, (i+1): li+1; (j): lj+1, (j-1): lj
+                const T d = (sW[s0][0][lj + 1][li] - sW[s0][0][lj][li]) +
+                            (sW[s0][2][lj][li] - sW[s0][2][lj + 1][li]) +
+                            (sW[s0][3][lj + 1][li] - sW[s0][3][lj + 1][li + 1]) +
+                            (sW[s0][5][lj + 1][li] - sW[s1][5][lj + 1][li]);
+                gv = kf[n][1] * d;
             }
+            gV[s0][lj][li] = gv;
+            gv = T(0);
+            if (w_face(li, lj, kk + 1)) {
+                // w face (i0-1+li, j0-1+lj, kk+1): weighted (i): li, (j): lj
+                const T d = (sW[s1][0][lj][li] - sW[s0][0][lj][li]) +
+                            (sW[s1][1][lj][li] - sW[s0][1][lj][li]) +
+                            (sW[s1][2][lj][li] - sW[s0][2][lj][li]) +
+                            (sW[s1][4][lj][li] - sW[s1][4][lj][li + 1]) +
+                            (sW[s1][5][lj][li] - sW[s1][5][lj + 1][li]);
+                gv = kf[n][2] * d;
+            }
+            gW[s1][lj][li] = gv;
         }
     };
 
     // prologue: planes k0-1 and k0, faces u,v at k0-1 and w at k0
-    load_plane(k0 - 1, vnext, anext);
-    load_plane(k0, vcur, acur);
+    fetch_plane(k0 - 1);
+    fetch_faces(k0 - 1);
+    commit_plane(k0 - 1, vnext, anext);
+    fetch_plane(k0);
+    commit_plane(k0, vcur, acur);
+    fetch_plane(k0 + 1);
     __syncthreads();
-    faces(k0 - 1, true, true);
+    faces(k0 - 1);
+    fetch_faces(k0);
+    fetch_outputs(k0);
     __syncthreads();
 
     for (int k = k0; k < kend; ++k) {
-        load_plane(k + 1, vnext, anext);
+        commit_plane(k + 1, vnext, anext);
+        if (k + 1 < kend) fetch_plane(k + 2);
         __syncthreads();
-        faces(k, true, true);
+        faces(k);
+        if (k + 1 < kend) fetch_faces(k + 1);
         __syncthreads();
         const int i = i0 + tx, j = j0 + ty;
         if (i <= g.nx && j <= g.ny) {
@@ -270,15 +338,17 @@ __global__ __launch_bounds__(NT) void k_apply3d(Geo g, Tiles tl, const T* __rest
             const T gw0 = gW[sk][ty + 1][tx + 1], gw1 = gW[sn][ty + 1][tx + 1];
             const T gwx = gW[sk][ty + 1][tx], gwy = gW[sk][ty][tx + 1];
             const long long o = g.idx(i, j, k);
-            const T c1 = c[NP + o], c2 = c[2 * NP + o];
+            const T c1 = cf[0], c2 = cf[1];
             const T cross = T(0.5) * fmin(c1, c2);
             T y[6];
             y[0] = acur[0] * ((gu0 - gu1) + (gv0 - gv1) + (gw0 - gw1));
-            y[1] = acur[1] * ((gu1 - gu0) + (gw0 - gw1)) + c1 * vcur[1] + cross * vcur[2];
-            y[2] = acur[2] * ((gv1 - gv0) + (gw0 - gw1)) + c2 * vcur[2] + cross * vcur[1];
-            y[3] = acur[3] * ((gu0 - gum) + (gv0 - gvm)) + c[3 * NP + o] * vcur[3];
-            y[4] = acur[4] * ((gu0 - guz) + (gw0 - gwx)) + c[4 * NP + o] * vcur[4];
-            y[5] = acur[5] * ((gv0 - gvz) + (gw0 - gwy)) + c[5 * NP + o] * vcur[5];
+            // one rounding of a S + c v, in a fixed order: solves take the same steps
+            // however the loads are arranged
+            y[1] = fused(cross, vcur[2], fused(acur[1], (gu1 - gu0) + (gw0 - gw1), c1 * vcur[1]));
+            y[2] = fused(cross, vcur[1], fused(acur[2], (gv1 - gv0) + (gw0 - gw1), c2 * vcur[2]));
+            y[3] = fused(acur[3], (gu0 - gum) + (gv0 - gvm), cf[2] * vcur[3]);
+            y[4] = fused(acur[4], (gu0 - guz) + (gw0 - gwx), cf[3] * vcur[4]);
+            y[5] = fused(acur[5], (gv0 - gvz) + (gw0 - gwy), cf[4] * vcur[5]);
             if (MODE == MODE_RESID) {
 #pragma unroll
                 for (int s = 0; s < 6; ++s) {
@@ -295,6 +365,7 @@ __global__ __launch_bounds__(NT) void k_apply3d(Geo g, Tiles tl, const T* __rest
                 }
             }
         }
+        fetch_outputs(k + 1);
 #pragma unroll
         for (int s = 0; s < 6; ++s) {
             vcur[s] = vnext[s];
