@@ -105,9 +105,9 @@ __device__ __forceinline__ long long anchor(const Geo& g, int i, int j, int k) {
     return g.dim == 2 ? g.idx(i, j) : g.idx(i, j, k);
 }
 
-// known flags of the velocity of the last Stokes step (all = 1: every face)
+// known flags of the velocity of the last Stokes step
 __global__ void k_known_faces(Geo g, const uint8_t* __restrict__ fflag,
-                              const double* __restrict__ WF, int all, uint8_t* __restrict__ known) {
+                              const double* __restrict__ WF, uint8_t* __restrict__ known) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y * blockDim.y + threadIdx.y;
     const int k = blockIdx.z * blockDim.z + threadIdx.z;
@@ -117,7 +117,7 @@ __global__ void k_known_faces(Geo g, const uint8_t* __restrict__ fflag,
         const long long q = (long long)a * g.NP + o;
         uint8_t kn = 0;
         if (face_valid(g, a, i, j, k))
-            kn = (all || (fflag[q] & FK) || WF[(long long)(1 + a) * g.NP + o] == 0.0) ? 1 : 0;
+            kn = ((fflag[q] & FK) || WF[(long long)(1 + a) * g.NP + o] == 0.0) ? 1 : 0;
         known[q] = kn;
     }
 }
@@ -224,10 +224,10 @@ dim3 block_of(const Geo& g) { return g.dim == 2 ? dim3(64, 4, 1) : dim3(64, 2, 2
 
 }  // namespace
 
-void launch_known_faces(const Geo& g, const uint8_t* fflag, const double* WF, bool all,
-                        uint8_t* known, hipStream_t s) {
+void launch_known_faces(const Geo& g, const uint8_t* fflag, const double* WF, uint8_t* known,
+                        hipStream_t s) {
     const dim3 bs = block_of(g);
-    hipLaunchKernelGGL(k_known_faces, grid_of(g, bs, 1), bs, 0, s, g, fflag, WF, all ? 1 : 0, known);
+    hipLaunchKernelGGL(k_known_faces, grid_of(g, bs, 1), bs, 0, s, g, fflag, WF, known);
 }
 
 void launch_extend(const Geo& g, const double* vin, const uint8_t* kin, double* vout,

@@ -58,7 +58,8 @@ __global__ __launch_bounds__(256) void k_take(Geo g, SliceMap m, int positive, i
             const int i = (int)(t % n0), j = (int)((t / n0) % n1), k = (int)(t / ((long long)n0 * n1));
             o = g.dim == 2 ? g.idx(i, j) : g.idx(i, j, k);
         }
-        m.pad[blockIdx.y][o] = x;
+        const bool off = !FLAT && m.mask && m.mask[(m.pad[blockIdx.y] - m.pad[0]) + o] == 0.0;
+        m.pad[blockIdx.y][o] = off ? 0.0 : x;
     }
 }
 

@@ -931,8 +931,10 @@ int recover_internal(vfs_ctx* ctx) {
     return VFS_OK;
 }
 
-// user sample-order vector -> padded work vector (its old values are lost)
-int pack_samples(vfs_ctx* ctx, const double* user, double* dst) {
+// user sample-order vector -> padded work vector (its old values are lost);
+// active: only the active samples, 0 elsewhere (by way of another work vector
+// where the caller's memory is not used as it is)
+int pack_samples(vfs_ctx* ctx, const double* user, double* dst, double* active = nullptr) {
     const Geo& g = ctx->g;
     const double* users[6];
     int sets[6];
@@ -945,6 +947,7 @@ int pack_samples(vfs_ctx* ctx, const double* user, double* dst) {
     if (direct(user)) {
         SliceMap m{};
         for (int s = 0; s < g.nsamp(); ++s) map_slice(m, g, sets[s], users[s], dst + s * g.NP);
+        m.mask = active ? ctx->a : nullptr;
         launch_take(g, m, TakeMode::check_write, 0, ctx->flag, ctx->flag_host, ctx->stream);
         int bad;
         int rc = taken(ctx, &bad);
@@ -955,9 +958,13 @@ int pack_samples(vfs_ctx* ctx, const double* user, double* dst) {
         return rc;
     }
     for (int s = 0; s < g.nsamp(); ++s) {
-        double* to = dst + s * g.NP;
+        double* to = (active ? active : dst) + s * g.NP;
         int rc = put_sets(ctx, 1, sets + s, users + s, &to, 0, "vector");
         if (rc) return rc;
+    }
+    if (active) {
+        launch_mask(dst, active, ctx->a, (long long)g.nsamp() * g.NP, ctx->stream);
+        HIPCHK(hipGetLastError());
     }
     return VFS_OK;
 }
@@ -986,8 +993,8 @@ namespace vfs {
 
 int ctx_assemble(vfs_ctx* ctx, double dt) { return assemble_internal(ctx, dt); }
 int ctx_recover(vfs_ctx* ctx) { return recover_internal(ctx); }
-int ctx_put_samples(vfs_ctx* ctx, const double* user, double* dst) {
-    return pack_samples(ctx, user, dst);
+int ctx_put_active(vfs_ctx* ctx, const double* user, double* dst, double* work) {
+    return pack_samples(ctx, user, dst, work);
 }
 int ctx_get_samples(vfs_ctx* ctx, const double* src, double* user) {
     return unpack_samples(ctx, src, user);
@@ -1386,12 +1393,18 @@ int vfs_advect(vfs_ctx* ctx, double dt) {
     // faces the last Stokes step defined; every face when the velocity came
     // from the caller (or from a previous advection)
     const bool all = !(ctx->u_from_step && ctx->assembled);
-    launch_known_faces(g, ctx->fflag, ctx->WF, all, ctx->adv_kb, s);
-    launch_extend(g, ctx->u, ctx->adv_kb, ctx->adv_a, ctx->adv_ka, s);
-    launch_extend(g, ctx->adv_a, ctx->adv_ka, ctx->adv_b, ctx->adv_kb, s);
-    launch_extend(g, ctx->adv_b, ctx->adv_kb, ctx->adv_a, ctx->adv_ka, s);
-    launch_advect_u(g, dt, ctx->adv_a, ctx->u, s);
-    launch_advect_phi(g, dt, ctx->adv_a, ctx->phi_l, ctx->phi_tmp, s);
+    if (all) {   // nothing to extend: from u to the other array
+        launch_advect_u(g, dt, ctx->u, ctx->adv_a, s);
+        launch_advect_phi(g, dt, ctx->u, ctx->phi_l, ctx->phi_tmp, s);
+        std::swap(ctx->u, ctx->adv_a);
+    } else {
+        launch_known_faces(g, ctx->fflag, ctx->WF, ctx->adv_kb, s);
+        launch_extend(g, ctx->u, ctx->adv_kb, ctx->adv_a, ctx->adv_ka, s);
+        launch_extend(g, ctx->adv_a, ctx->adv_ka, ctx->adv_b, ctx->adv_kb, s);
+        launch_extend(g, ctx->adv_b, ctx->adv_kb, ctx->adv_a, ctx->adv_ka, s);
+        launch_advect_u(g, dt, ctx->adv_a, ctx->u, s);
+        launch_advect_phi(g, dt, ctx->adv_a, ctx->phi_l, ctx->phi_tmp, s);
+    }
     HIPCHK(hipGetLastError());
     std::swap(ctx->phi_l, ctx->phi_tmp);
     ctx->u_from_step = false;

@@ -378,8 +378,8 @@ void launch_traction_pair3d(const Geo& g, const double* y, const double* a, cons
                             double* b, hipStream_t s);
 
 // fractional step (k_advect.hip)
-void launch_known_faces(const Geo& g, const uint8_t* fflag, const double* WF, bool all,
-                        uint8_t* known, hipStream_t s);
+void launch_known_faces(const Geo& g, const uint8_t* fflag, const double* WF, uint8_t* known,
+                        hipStream_t s);
 void launch_extend(const Geo& g, const double* vin, const uint8_t* kin, double* vout,
                    uint8_t* kout, hipStream_t s);
 void launch_advect_u(const Geo& g, double dt, const double* uext, double* uout, hipStream_t s);
@@ -429,6 +429,7 @@ struct SliceMap {
     double* user[6];
     double* pad[6];
     int n[6][3];
+    const double* mask;   // write 0 where this, laid out as pad[0], is 0 (or NULL)
 };
 enum class TakeMode { check, check_write, write_if_good, flat_check_write };
 // checks the caller's arrays and copies them to the slices; a bad value of array

@@ -11,7 +11,7 @@
 
 namespace vfs {
 // sample-order user vectors <-> padded device vectors (vfs_api.hip)
-int ctx_put_samples(vfs_ctx* ctx, const double* user, double* dst);
+int ctx_put_active(vfs_ctx* ctx, const double* user, double* dst, double* work);
 int ctx_get_samples(vfs_ctx* ctx, const double* src, double* user);
 int ctx_fail(vfs_ctx* ctx, int code, const std::string& msg);
 }  // namespace vfs
@@ -531,10 +531,8 @@ int vfs_unet_train_step(vfs_unet* u, vfs_ctx* ctx, const double* r, const double
     if ((rc = ctx_f32(ctx))) return rc;
     if ((rc = net_prepare_ctx(u, ctx))) return rc;
     if ((rc = net_ensure(u, u->L[0], true))) return rc;
-    if ((rc = ctx_put_samples(ctx, r, ctx->z))) return ufail(u, rc, vfs_last_error(ctx));
-    launch_mask(ctx->r, ctx->z, ctx->a, n, s);
-    if ((rc = ctx_put_samples(ctx, e, ctx->q))) return ufail(u, rc, vfs_last_error(ctx));
-    launch_mask(ctx->z, ctx->q, ctx->a, n, s);
+    if ((rc = ctx_put_active(ctx, r, ctx->r, ctx->z))) return ufail(u, rc, vfs_last_error(ctx));
+    if ((rc = ctx_put_active(ctx, e, ctx->z, ctx->q))) return ufail(u, rc, vfs_last_error(ctx));
     launch_to_f32(ctx->r, ctx->r32, n, s);
     float* D = ctx->netvec;
     float* QD = D + n;
@@ -610,10 +608,8 @@ int vfs_precond_apply(vfs_ctx* ctx, const double* r, double* z) {
     if (ctx->precond == VFS_PRECOND_IC || ctx->precond == VFS_PRECOND_SCHWARZ) {
         if (!ctx->assembled) return ctx_fail(ctx, VFS_ESTATE, "call vfs_assemble first");
         const Geo& g = ctx->g;
-        const long long n = (long long)g.nsamp() * g.NP;
-        int rc = ctx_put_samples(ctx, r, ctx->q);
+        int rc = ctx_put_active(ctx, r, ctx->r, ctx->q);
         if (rc) return rc;
-        launch_mask(ctx->r, ctx->q, ctx->a, n, ctx->stream);
         launch_schwarz(g, ctx->precond == VFS_PRECOND_SCHWARZ ? 1 : 0, ctx->r, ctx->a, ctx->c,
                        ctx->dinv, ctx->K, ctx->rowbits, ctx->z, nullptr, ctx->bricks, ctx->brick_has,
                        ctx->stream);
@@ -629,8 +625,7 @@ int vfs_precond_apply(vfs_ctx* ctx, const double* r, double* z) {
     const long long n = (long long)g.nsamp() * g.NP;
     if ((rc = ctx_f32(ctx))) return rc;
     if ((rc = net_prepare_ctx(u, ctx))) return ctx_fail(ctx, rc, u->err);
-    if ((rc = ctx_put_samples(ctx, r, ctx->z))) return rc;
-    launch_mask(ctx->r, ctx->z, ctx->a, n, s);
+    if ((rc = ctx_put_active(ctx, r, ctx->r, ctx->z))) return rc;
     launch_to_f32(ctx->r, ctx->r32, n, s);
     launch_net_rdr(g, ctx->r32, ctx->dinv32, u->dpart, s);
     FcgHist none{};
