@@ -103,43 +103,31 @@ struct SampleIn {
     double* b;
 };
 
-// y = W_F u* + W_S u_BC on face slice fa at offset o
-__device__ __forceinline__ double yface(const Geo& g, const SampleIn& s, int fa, long long o) {
-    const long long NP = g.NP;
-    const double wf = s.WF[(1 + fa) * NP + o];
-    return wf * s.ustar[fa * NP + o] + (1.0 - wf) * s.ubc[fa * NP + o];
-}
+// The twelve faces that the samples of an anchor meet.
+enum Face3 { U0, UX, UY, UZ, V0, VY, VX, VZ, W0, WZ, WX, WY };   // at the anchor; one step along an axis
+struct Faces3 {
+    double K[12], y[12], ubc[12];   // y = W_F u* + W_S u_BC
+};
 
-// One sample with a 2- or 4-face stencil: faces (fa[q], off[q]) with signs sg[q]
-// (the reduced-D row, or -div for pressure).
+// One sample with stencil faces f of signs sg (the reduced-D row, or -div for
+// pressure), its weights given.
 template <int NF>
-__device__ __forceinline__ int sample_one(const Geo& g, const SampleIn& s, int slice, int set,
-                                          long long o, const int (&fa)[NF],
-                                          const long long (&of)[NF], const double (&sg)[NF],
-                                          double mu_s, double& a_out, double& c_out,
-                                          double& d_out, double& b_out) {
-    const long long NP = g.NP;
-    uint8_t fl = 0;
+__device__ __forceinline__ void sample_one(const Faces3& F, const int (&f)[NF], const int (&sg)[NF],
+                                           bool pressure, double wl, double wf, double mu_s, double ih,
+                                           double& a_out, double& c_out, double& d_out, double& b_out) {
+#pragma clang fp contract(off)
+    double sumK = F.K[f[0]], ty = 0.0, tb = 0.0;
 #pragma unroll
-    for (int q = 0; q < NF; ++q) fl |= s.fflag[fa[q] * NP + of[q]];
-    const double wl = s.WL[set * NP + o];
-    const double wf = s.WF[set * NP + o];
-    const bool act = wl > 0.0 && !(fl & FBAD) && (fl & FK);
-    a_out = c_out = d_out = b_out = 0.0;
-    if (!act) return 0;
-    const double ih = 1.0 / g.h;
-    double sumK = 0.0, ty = 0.0, tb = 0.0;
+    for (int q = 1; q < NF; ++q) sumK += F.K[f[q]];
 #pragma unroll
     for (int q = 0; q < NF; ++q) {
-        sumK += s.K[fa[q] * NP + of[q]];
-        ty += sg[q] * yface(g, s, fa[q], of[q]);
-        tb += sg[q] * s.ubc[fa[q] * NP + of[q]];
+        ty = sg[q] > 0 ? ty + F.y[f[q]] : ty - F.y[f[q]];
+        tb = sg[q] > 0 ? tb + F.ubc[f[q]] : tb - F.ubc[f[q]];
     }
     a_out = wl;
-    c_out = slice == 0 ? 0.0 : wf * wl / mu_s;
-    d_out = 1.0 / (c_out + wl * wl * sumK);
-    b_out = wl * (ty * ih - (1.0 - wf) * (tb * ih));
-    return 1;
+    c_out = pressure ? 0.0 : wf * wl / mu_s;
+    d_out = 1.0 / __builtin_fma(wl * wl, sumK, c_out);
+    b_out = wl * __builtin_fma(ih, ty, -((1.0 - wf) * (tb * ih)));
 }
 
 __device__ __forceinline__ double mu_mean(const Geo& g, const double* mu, int i, int j, int k,
@@ -158,7 +146,10 @@ __device__ __forceinline__ double mu_mean(const Geo& g, const double* mu, int i,
     return n ? s / (double)n : 1.0;
 }
 
-__global__ void k_sample3d(Geo g, SampleIn s, Scalars* sc) {
+// An anchor's faces are read once for all its samples: read by each, under its own
+// test, they took 130 loads of a thread, 2.05 ms at 256^3 (now 1.70; 5 GB, 1.1 ms).
+// 128 registers, 14 spilled: with 196 and half the waves 1.90 ms, with 102 2.35.
+__global__ __launch_bounds__(256, 4) void k_sample3d(Geo g, SampleIn s, Scalars* sc) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y * blockDim.y + threadIdx.y;
     const int k = blockIdx.z * blockDim.z + threadIdx.z;
@@ -166,52 +157,69 @@ __global__ void k_sample3d(Geo g, SampleIn s, Scalars* sc) {
     if (i <= g.nx && j <= g.ny && k <= g.nz) {
         const long long NP = g.NP;
         const long long o = g.idx(i, j, k);
+        const double ih = 1.0 / g.h;
         double av[6], cv[6], dv[6], bv[6];
         for (int q = 0; q < 6; ++q) av[q] = cv[q] = dv[q] = bv[q] = 0.0;
-        if (i < g.nx && j < g.ny && k < g.nz) {
-            const long long oi = g.idx(i + 1, j, k), oj = g.idx(i, j + 1, k), ok = g.idx(i, j, k + 1);
-            const double muc = s.mu[o];
-            {   // p: -div over the six faces
-                const int fa[6] = {0, 0, 1, 1, 2, 2};
-                const long long of[6] = {o, oi, o, oj, o, ok};
-                const double sg[6] = {1, -1, 1, -1, 1, -1};
-                nact += sample_one<6>(g, s, 0, 0, o, fa, of, sg, muc, av[0], cv[0], dv[0], bv[0]);
-            }
-            {   // txx: u_x - w_z
-                const int fa[4] = {0, 0, 2, 2};
-                const long long of[4] = {oi, o, ok, o};
-                const double sg[4] = {1, -1, -1, 1};
-                nact += sample_one<4>(g, s, 1, 0, o, fa, of, sg, muc, av[1], cv[1], dv[1], bv[1]);
-            }
-            {   // tyy: v_y - w_z
-                const int fa[4] = {1, 1, 2, 2};
-                const long long of[4] = {oj, o, ok, o};
-                const double sg[4] = {1, -1, -1, 1};
-                nact += sample_one<4>(g, s, 2, 0, o, fa, of, sg, muc, av[2], cv[2], dv[2], bv[2]);
-            }
-            // the (txx, tyy) compliance coupling: the diagonal of the 2x2
-            // block is c; Jacobi uses the diagonal entries only
+        const long long sx = 1, sy = g.PX, sz = (long long)g.PX * g.PY;
+        const long long at[12] = {o,      o + sx, o - sy, o - sz, NP + o,     NP + o + sy,
+                                  NP + o - sx, NP + o - sz, 2 * NP + o, 2 * NP + o + sz, 2 * NP + o - sx,
+                                  2 * NP + o - sy};
+        // stencils: p -div; txx u_x - w_z; tyy v_y - w_z; txy u_y + v_x (z-edge);
+        // txz u_z + w_x (y-edge); tyz v_z + w_y (x-edge)
+        uint8_t fl[12];
+#pragma unroll
+        for (int q = 0; q < 12; ++q) fl[q] = s.fflag[at[q]];
+        const bool cell = i < g.nx && j < g.ny && k < g.nz;
+        const bool valid[6] = {cell, cell, cell, k < g.nz, j < g.ny, i < g.nx};
+        const uint8_t met[6] = {(uint8_t)(fl[U0] | fl[UX] | fl[V0] | fl[VY] | fl[W0] | fl[WZ]),
+                                (uint8_t)(fl[UX] | fl[U0] | fl[WZ] | fl[W0]),
+                                (uint8_t)(fl[VY] | fl[V0] | fl[WZ] | fl[W0]),
+                                (uint8_t)(fl[U0] | fl[UY] | fl[V0] | fl[VX]),
+                                (uint8_t)(fl[U0] | fl[UZ] | fl[W0] | fl[WX]),
+                                (uint8_t)(fl[V0] | fl[VZ] | fl[W0] | fl[WY])};
+        constexpr int set[6] = {0, 0, 0, 4, 5, 6};
+        double wl[6];
+        bool act[6];
+        // the (txx, tyy) compliance coupling: the diagonal of the 2x2 block is c;
+        // Jacobi uses the diagonal entries only
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            wl[q] = (q == 1 || q == 2) ? wl[0] : s.WL[set[q] * NP + o];
+            act[q] = valid[q] && wl[q] > 0.0 && !(met[q] & FBAD) && (met[q] & FK);
+            nact += act[q] ? 1 : 0;
         }
-        if (i <= g.nx && j <= g.ny && k < g.nz) {   // txy on z-edge: u_y + v_x
-            const int fa[4] = {0, 0, 1, 1};
-            const long long of[4] = {o, g.idx(i, j - 1, k), o, g.idx(i - 1, j, k)};
-            const double sg[4] = {1, -1, 1, -1};
-            nact += sample_one<4>(g, s, 3, 4, o, fa, of, sg, mu_mean(g, s.mu, i, j, k, 0, 0, 1),
-                                  av[3], cv[3], dv[3], bv[3]);
-        }
-        if (i <= g.nx && j < g.ny && k <= g.nz) {   // txz on y-edge: u_z + w_x
-            const int fa[4] = {0, 0, 2, 2};
-            const long long of[4] = {o, g.idx(i, j, k - 1), o, g.idx(i - 1, j, k)};
-            const double sg[4] = {1, -1, 1, -1};
-            nact += sample_one<4>(g, s, 4, 5, o, fa, of, sg, mu_mean(g, s.mu, i, j, k, 0, 1, 0),
-                                  av[4], cv[4], dv[4], bv[4]);
-        }
-        if (i < g.nx && j <= g.ny && k <= g.nz) {   // tyz on x-edge: v_z + w_y
-            const int fa[4] = {1, 1, 2, 2};
-            const long long of[4] = {o, g.idx(i, j, k - 1), o, g.idx(i, j - 1, k)};
-            const double sg[4] = {1, -1, 1, -1};
-            nact += sample_one<4>(g, s, 5, 6, o, fa, of, sg, mu_mean(g, s.mu, i, j, k, 1, 0, 0),
-                                  av[5], cv[5], dv[5], bv[5]);
+        if (nact) {
+            Faces3 F;
+#pragma unroll
+            for (int q = 0; q < 12; ++q) {
+#pragma clang fp contract(off)
+                const double wf = s.WF[NP + at[q]], ubc = s.ubc[at[q]];
+                F.K[q] = s.K[at[q]];
+                F.ubc[q] = ubc;
+                F.y[q] = __builtin_fma(wf, s.ustar[at[q]], (1.0 - wf) * ubc);
+            }
+            double wf[6];
+#pragma unroll
+            for (int q = 0; q < 6; ++q) wf[q] = (q == 1 || q == 2) ? wf[0] : s.WF[set[q] * NP + o];
+            const double muc = cell ? s.mu[o] : 1.0;
+            if (act[0])
+                sample_one<6>(F, {U0, UX, V0, VY, W0, WZ}, {1, -1, 1, -1, 1, -1}, true, wl[0], wf[0], muc, ih,
+                              av[0], cv[0], dv[0], bv[0]);
+            if (act[1])
+                sample_one<4>(F, {UX, U0, WZ, W0}, {1, -1, -1, 1}, false, wl[1], wf[1], muc, ih, av[1], cv[1],
+                              dv[1], bv[1]);
+            if (act[2])
+                sample_one<4>(F, {VY, V0, WZ, W0}, {1, -1, -1, 1}, false, wl[2], wf[2], muc, ih, av[2], cv[2],
+                              dv[2], bv[2]);
+            if (act[3])
+                sample_one<4>(F, {U0, UY, V0, VX}, {1, -1, 1, -1}, false, wl[3], wf[3],
+                              mu_mean(g, s.mu, i, j, k, 0, 0, 1), ih, av[3], cv[3], dv[3], bv[3]);
+            if (act[4])
+                sample_one<4>(F, {U0, UZ, W0, WX}, {1, -1, 1, -1}, false, wl[4], wf[4],
+                              mu_mean(g, s.mu, i, j, k, 0, 1, 0), ih, av[4], cv[4], dv[4], bv[4]);
+            if (act[5])
+                sample_one<4>(F, {V0, VZ, W0, WY}, {1, -1, 1, -1}, false, wl[5], wf[5],
+                              mu_mean(g, s.mu, i, j, k, 1, 0, 0), ih, av[5], cv[5], dv[5], bv[5]);
         }
 #pragma unroll
         for (int q = 0; q < 6; ++q) {
