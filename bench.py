@@ -278,7 +278,8 @@ BATCH_TOL = 1e-9
 
 
 def batch64_leg(V):
-    """Many uneven 2D solves in one persistent, graph-captured launch: the 64
+    """Many uneven 2D solves in one graph-captured launch, resident on the chip (or
+    persistent, where they do not fit, in the autotuned shape): the 64
     problems of sizes {64, 96, ..., 512}^2, tile shape and workgroups per CU
     picked by the autotuner, mixed precision to BATCH_TOL.  Reports the solve time,
     aggregate DOF*iter/s and per-problem latency percentiles; returns with
@@ -299,7 +300,7 @@ def batch64_leg(V):
     per = [b.vfs_batch_get_problem(i) for i in range(len(probs))]
     out = {"workload": f"{len(probs)} 2D problems shaped as the 32^2 drop case, sizes "
                        f"{{64, 96, ..., 512}}^2 drawn with seed 4 ({min(sizes)}..{max(sizes)}), "
-                       f"mixed Jacobi PCG to {BATCH_TOL:g}, one persistent launch per step",
+                       f"mixed Jacobi PCG to {BATCH_TOL:g}, one resident launch per step",
            "tol": BATCH_TOL,
            "status": st["status"], "n_problems": st["n_problems"],
            "n_active_total": st["n_active_total"], "dof_iters": st["dof_iters"],
@@ -353,9 +354,11 @@ def device_faces(case, dev):
 
 def pool512_leg(V, dev, stream, steps, warmup):
     """The 2D 512^2 configuration: mixed Jacobi PCG to 1e-6, `steps` timed
-    steps, with the live roofline of its dominant kernel (the fused 2D PCG
-    iteration).  Returns with the figures host copies of the velocity,
-    solution and active set for the CPU leg to check."""
+    steps, with the live timing of its dominant kernel (the resident 2D PCG,
+    whose iterations wait for each other's sums and rims, not for memory: the
+    bytes are those an iteration through memory would move).  Returns with the
+    figures host copies of the velocity, solution and active set for the CPU leg
+    to check."""
     import cases
     case = cases.pool512()
     ctx = V.context_from_case(case, precision=V.VFS_MIXED, tol=1e-6)
@@ -373,9 +376,10 @@ def pool512_leg(V, dev, stream, steps, warmup):
            "cg_iterations_per_step": [q["iterations"] for q in per],
            "solve_ms_per_step": [round(q["t_solve_ms"], 3) for q in per],
            "rel_residual_fp64": [q["rel_residual"] for q in per],
-           "roofline": {"bound": "hbm", "kernel": "k_fused2d (one launch per PCG iteration)",
+           "roofline": {"bound": "latency",
+                        "kernel": "k_resident2d (a PCG run in one launch; per iteration)",
                         "achieved": a2, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                        "frac": a2 / HBM_PEAK_GBS, "traffic": measured_traffic_2d(),
+                        "frac": a2 / HBM_PEAK_GBS, "traffic": None,
                         "avg_launch_ms": t2, "launches_timed": int(st["n_apply_timed"]),
                         "algorithmic_bytes_per_launch": b2}}
     got = {"velocity": ctx.vfs_get_velocity(), "solution": ctx.vfs_get_solution(),

@@ -73,13 +73,8 @@ struct Loader {
     const T* a;
     T beta;
     bool first;
-    bool fb;   // MODE_FDIR: use the Jacobi z instead of zs
-    int mk;    // MODE_FDIR: previous directions subtracted
-    T bet[kFcgMax];
-    const T* prev[kFcgMax];
 
-    // what a value is made of, loaded ahead of its use (MODE_FDIR: nothing, its
-    // directions are too many)
+    // what a value is made of, loaded ahead of its use
     struct Raw {
         T z, w, p;
     };
@@ -89,25 +84,17 @@ struct Loader {
             v.z = ZIN ? zs[os] : dinv[os];
             if (!ZIN) v.w = r[os];
             if (MODE == MODE_DIR && !first) v.p = pin[os];
-        } else if (MODE != MODE_FDIR) {
+        } else {
             v.p = pin[os];
         }
         return v;
     }
-    // value of slice s at offset os (direction update in MODE_DIR / MODE_FDIR)
+    // value of slice s at offset os (direction update in MODE_DIR)
     __device__ __forceinline__ T value(long long os, bool own, const Raw& v) const {
         if (MODE == MODE_JDIR) {
             const T z = ZIN ? v.z : v.z * v.w;
             if (own && pout) pout[os] = z;
             return z;
-        }
-        if (MODE == MODE_FDIR) {
-            T val = fb ? dinv[os] * r[os] : zs[os];
-#pragma unroll
-            for (int i = 0; i < kFcgMax; ++i)
-                if (i < mk) val -= bet[i] * prev[i][os];
-            if (own) pout[os] = val;
-            return val;
         }
         if (MODE == MODE_DIR) {
             const T z = ZIN ? v.z : v.z * v.w;
@@ -134,8 +121,7 @@ __global__ __launch_bounds__(NT) void k_apply3d(Geo g, Tiles tl, const T* __rest
                                                 const T* __restrict__ c, const T* __restrict__ K,
                                                 const T* __restrict__ bv, RedArgs ra) {
     T beta = T(0);
-    bool first = true, fb = false;
-    T bet[kFcgMax] = {};
+    bool first = true;
     if (MODE == MODE_DIR) {
         if (ra.sc->done) return;
         double bd;
@@ -144,12 +130,6 @@ __global__ __launch_bounds__(NT) void k_apply3d(Geo g, Tiles tl, const T* __rest
         beta = (T)bd;
     } else if (MODE == MODE_JDIR) {
         if (ra.skip && *ra.skip) return;
-    } else if (MODE == MODE_FDIR) {
-        if (ra.sc->done) return;
-        double bd[kFcgMax];
-        if (!fcg_direction_preamble<NT>(ra, blockIdx.x, bd, fb)) return;
-#pragma unroll
-        for (int i = 0; i < kFcgMax; ++i) bet[i] = (T)bd[i];
     }
     __shared__ T sW[2][6][HY][HX];
     __shared__ T gU[2][FY][FX];
@@ -158,12 +138,7 @@ __global__ __launch_bounds__(NT) void k_apply3d(Geo g, Tiles tl, const T* __rest
     const long long NP = g.NP;
     const int tid = threadIdx.x;
     const int tx = tid & 63, ty = tid >> 6;
-    Loader<T, MODE, ZIN> ld{g, r, zs, dinv, pin, pout, a, beta, first, fb, ra.fh.mk, {}, {}};
-#pragma unroll
-    for (int i = 0; i < kFcgMax; ++i) {
-        ld.bet[i] = bet[i];
-        ld.prev[i] = static_cast<const T*>(ra.fh.P[i]);
-    }
+    Loader<T, MODE, ZIN> ld{g, r, zs, dinv, pin, pout, a, beta, first};
     double acc = 0.0;
   const TileRange tr = tile_range(tl.items());
   for (int wtile = tr.first; wtile < tr.end; wtile += tr.step) {
@@ -360,7 +335,7 @@ __global__ __launch_bounds__(NT) void k_apply3d(Geo g, Tiles tl, const T* __rest
 #pragma unroll
                 for (int s = 0; s < 6; ++s) {
                     q[s * NP + o] = y[s];
-                    if (MODE == MODE_DIR || MODE == MODE_FDIR || MODE == MODE_JDIR)
+                    if (MODE == MODE_DIR || MODE == MODE_JDIR)
                         acc += (double)vcur[s] * (double)y[s];
                 }
             }
@@ -374,6 +349,218 @@ __global__ __launch_bounds__(NT) void k_apply3d(Geo g, Tiles tl, const T* __rest
     }
   }
     if (MODE == MODE_APPLY) return;
+    double vv[1] = {acc};
+    block_partial<1, NT>(vv, ra.part_out, gridDim.x, blockIdx.x);
+}
+
+template <typename T>
+struct FdirLoader {
+    const Geo& g;
+    const T* r;
+    const T* zs;
+    const T* dinv;
+    T* pout;
+    const T* a;
+    bool fb;   // use the Jacobi z instead of zs
+    int mk;    // previous directions subtracted
+    T bet[kFcgMax];
+    const T* prev[kFcgMax];
+
+    // value of slice s at offset os
+    __device__ __forceinline__ T value(long long os, bool own) const {
+        T val = fb ? dinv[os] * r[os] : zs[os];
+#pragma unroll
+        for (int i = 0; i < kFcgMax; ++i)
+            if (i < mk) val -= bet[i] * prev[i][os];
+        if (own) pout[os] = val;
+        return val;
+    }
+};
+
+// The direction of flexible CG and its A p (MODE_FDIR).  A value is made of up to
+// six fields: loading those ahead as k_apply3d does takes two of its five waves, and
+// 256^3 1.43 ms against 1.00 with each load where its value is used.
+template <typename T>
+__global__ __launch_bounds__(NT) void k_fdir3d(Geo g, Tiles tl, const T* __restrict__ r,
+                                               const T* __restrict__ zs,
+                                               const T* __restrict__ dinv,
+                                               T* __restrict__ pout,
+                                               T* __restrict__ q, const T* __restrict__ a,
+                                               const T* __restrict__ c, const T* __restrict__ K,
+                                               RedArgs ra) {
+    bool fb = false;
+    T bet[kFcgMax] = {};
+    if (ra.sc->done) return;
+    double bd[kFcgMax];
+    if (!fcg_direction_preamble<NT>(ra, blockIdx.x, bd, fb)) return;
+#pragma unroll
+    for (int i = 0; i < kFcgMax; ++i) bet[i] = (T)bd[i];
+    __shared__ T sW[2][6][HY][HX];
+    __shared__ T gU[2][FY][FX];
+    __shared__ T gV[2][FY][FX];
+    __shared__ T gW[2][FY][FX];
+    const long long NP = g.NP;
+    const int tid = threadIdx.x;
+    const int tx = tid & 63, ty = tid >> 6;
+    FdirLoader<T> ld{g, r, zs, dinv, pout, a, fb, ra.fh.mk, {}, {}};
+#pragma unroll
+    for (int i = 0; i < kFcgMax; ++i) {
+        ld.bet[i] = bet[i];
+        ld.prev[i] = static_cast<const T*>(ra.fh.P[i]);
+    }
+    double acc = 0.0;
+  const TileRange tr = tile_range(tl.items());
+  for (int wtile = tr.first; wtile < tr.end; wtile += tr.step) {
+    int i0, j0, k0, kend;
+    tile_origin(tl, g, wtile, i0, j0, k0, kend);
+    T vcur[6], acur[6], vnext[6], anext[6];
+    __syncthreads();   // LDS of the previous tile is no longer read
+    // load weighted plane kk into ring slot kk&1; own anchor values -> vo, ao
+    auto load_plane = [&](int kk, T (&vo)[6], T (&ao)[6]) {
+        const int sl = kk & 1;
+        {   // own interior anchor
+            const int i = i0 + tx, j = j0 + ty;
+            const bool in = i <= g.nx + 1 && j <= g.ny + 1 && kk <= g.nz + 1;
+            const bool own = in && i <= g.nx && j <= g.ny && kk >= k0 && kk < kend;
+            const long long o = in ? g.idx(i, j, kk) : 0;
+#pragma unroll
+            for (int s = 0; s < 6; ++s) {
+                T val = T(0), aw = T(0);
+                if (in) {
+                    const long long os = o + s * NP;
+                    val = ld.value(os, own);
+                    aw = a[os];
+                }
+                vo[s] = val;
+                ao[s] = aw;
+                sW[sl][s][ty + 1][tx + 1] = aw * val;
+            }
+        }
+        // halo ring: rows lj = 0 and HY-1 (HX each), columns li = 0 and HX-1 (TY each)
+        if (tid < 2 * HX + 2 * TY) {
+            int li, lj;
+            if (tid < HX) {
+                li = tid;
+                lj = 0;
+            } else if (tid < 2 * HX) {
+                li = tid - HX;
+                lj = HY - 1;
+            } else {
+                const int e = tid - 2 * HX;
+                lj = 1 + (e >> 1);
+                li = (e & 1) ? HX - 1 : 0;
+            }
+            const int i = i0 - 1 + li, j = j0 - 1 + lj;
+            const bool in = i <= g.nx + 1 && j <= g.ny + 1 && kk <= g.nz + 1;
+            const long long o = in ? g.idx(i, j, kk) : 0;
+#pragma unroll
+            for (int s = 0; s < 6; ++s) {
+                T w = T(0);
+                if (in) {
+                    const long long os = o + s * NP;
+                    w = a[os] * ld.value(os, false);
+                }
+                sW[sl][s][lj][li] = w;
+            }
+        }
+    };
+
+    // faces: g_u(kk), g_v(kk) from planes kk, kk+1; g_w(kk+1) from planes kk, kk+1
+    auto faces = [&](int kk, bool uv, bool w) {
+        const int s0 = kk & 1, s1 = (kk + 1) & 1;
+        for (int e = tid; e < FX * FY; e += NT) {
+            const int li = e % FX, lj = e / FX;
+            if (uv) {
+                {   // u face (i0+li, j0-1+lj, kk): weighted indices li (i-1), li+1 (i), lj+...
+                    const int i = i0 + li, j = j0 - 1 + lj;
+                    T gv = T(0);
+                    if (i <= g.nx && j >= 0 && j < g.ny && kk >= 0 && kk < g.nz) {
+                        const T kf = K[g.idx(i, j, kk)];
+                        // P,X at (i-1): [lj][li], (i): [lj][li+1]; E at j: [lj][li+1], j+1: [lj+1][li+1]
+                        const T d = (sW[s0][0][lj][li + 1] - sW[s0][0][lj][li]) +
+                                    (sW[s0][1][lj][li] - sW[s0][1][lj][li + 1]) +
+                                    (sW[s0][3][lj][li + 1] - sW[s0][3][lj + 1][li + 1]) +
+                                    (sW[s0][4][lj][li + 1] - sW[s1][4][lj][li + 1]);
+                        gv = kf * d;
+                    }
+                    gU[s0][lj][li] = gv;
+                }
+                {   // v face (i0-1+li, j0+lj, kk)
+                    const int i = i0 - 1 + li, j = j0 + lj;
+                    T gv = T(0);
+                    if (i >= 0 && i < g.nx && j <= g.ny && kk >= 0 && kk < g.nz) {
+                        const T kf = K[NP + g.idx(i, j, kk)];
+                        // weighted (i): li, (i+1): li+1; (j): lj+1, (j-1): lj
+                        const T d = (sW[s0][0][lj + 1][li] - sW[s0][0][lj][li]) +
+                                    (sW[s0][2][lj][li] - sW[s0][2][lj + 1][li]) +
+                                    (sW[s0][3][lj + 1][li] - sW[s0][3][lj + 1][li + 1]) +
+                                    (sW[s0][5][lj + 1][li] - sW[s1][5][lj + 1][li]);
+                        gv = kf * d;
+                    }
+                    gV[s0][lj][li] = gv;
+                }
+            }
+            if (w) {   // w face (i0-1+li, j0-1+lj, kk+1): weighted (i): li, (j): lj
+                const int i = i0 - 1 + li, j = j0 - 1 + lj, kw = kk + 1;
+                T gv = T(0);
+                if (i >= 0 && i < g.nx && j >= 0 && j < g.ny && kw >= 0 && kw <= g.nz) {
+                    const T kf = K[2 * NP + g.idx(i, j, kw)];
+                    const T d = (sW[s1][0][lj][li] - sW[s0][0][lj][li]) +
+                                (sW[s1][1][lj][li] - sW[s0][1][lj][li]) +
+                                (sW[s1][2][lj][li] - sW[s0][2][lj][li]) +
+                                (sW[s1][4][lj][li] - sW[s1][4][lj][li + 1]) +
+                                (sW[s1][5][lj][li] - sW[s1][5][lj + 1][li]);
+                    gv = kf * d;
+                }
+                gW[s1][lj][li] = gv;
+            }
+        }
+    };
+
+    // prologue: planes k0-1 and k0, faces u,v at k0-1 and w at k0
+    load_plane(k0 - 1, vnext, anext);
+    load_plane(k0, vcur, acur);
+    __syncthreads();
+    faces(k0 - 1, true, true);
+    __syncthreads();
+
+    for (int k = k0; k < kend; ++k) {
+        load_plane(k + 1, vnext, anext);
+        __syncthreads();
+        faces(k, true, true);
+        __syncthreads();
+        const int i = i0 + tx, j = j0 + ty;
+        if (i <= g.nx && j <= g.ny) {
+            const int sk = k & 1, sp = (k - 1) & 1, sn = (k + 1) & 1;
+            const T gu0 = gU[sk][ty + 1][tx], gu1 = gU[sk][ty + 1][tx + 1];
+            const T gum = gU[sk][ty][tx], guz = gU[sp][ty + 1][tx];
+            const T gv0 = gV[sk][ty][tx + 1], gv1 = gV[sk][ty + 1][tx + 1];
+            const T gvm = gV[sk][ty][tx], gvz = gV[sp][ty][tx + 1];
+            const T gw0 = gW[sk][ty + 1][tx + 1], gw1 = gW[sn][ty + 1][tx + 1];
+            const T gwx = gW[sk][ty + 1][tx], gwy = gW[sk][ty][tx + 1];
+            const long long o = g.idx(i, j, k);
+            const T c1 = c[NP + o], c2 = c[2 * NP + o];
+            const T cross = T(0.5) * fmin(c1, c2);
+            T y[6];
+            y[0] = acur[0] * ((gu0 - gu1) + (gv0 - gv1) + (gw0 - gw1));
+            y[1] = acur[1] * ((gu1 - gu0) + (gw0 - gw1)) + c1 * vcur[1] + cross * vcur[2];
+            y[2] = acur[2] * ((gv1 - gv0) + (gw0 - gw1)) + c2 * vcur[2] + cross * vcur[1];
+            y[3] = acur[3] * ((gu0 - gum) + (gv0 - gvm)) + c[3 * NP + o] * vcur[3];
+            y[4] = acur[4] * ((gu0 - guz) + (gw0 - gwx)) + c[4 * NP + o] * vcur[4];
+            y[5] = acur[5] * ((gv0 - gvz) + (gw0 - gwy)) + c[5 * NP + o] * vcur[5];
+#pragma unroll
+            for (int s = 0; s < 6; ++s) {
+                q[s * NP + o] = y[s];
+                acc += (double)vcur[s] * (double)y[s];
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 6; ++s) {
+            vcur[s] = vnext[s];
+            acur[s] = anext[s];
+        }
+    }
+  }
     double vv[1] = {acc};
     block_partial<1, NT>(vv, ra.part_out, gridDim.x, blockIdx.x);
 }
@@ -1393,18 +1580,24 @@ void launch_row_bits(const Geo& g, const double* a, RowBits* rows, hipStream_t s
 // Workgroups of a 3D apply launch: no more than can be resident at once
 // (occupancy x compute units, queried once per device and precision), so no
 // tail wave runs after the first, and at most kMaxTileBlocks.  The pipelined
-// Jacobi direction kernel holds more registers than the generic kernel and
-// gets its own figure (dir3d_grid); a consumer of an apply's partials uses
+// Jacobi direction kernel holds more registers than the generic kernel, and that
+// of flexible CG fewer (with the generic figure, three instead of five to a unit,
+// it took 1.56 ms at 256^3 and not 1.00): they get their own (dir3d_grid,
+// fdir3d_grid); a consumer of an apply's partials uses
 // the figure of the kernel that produced them.
-static int resident_grid(int count, int word, bool pipelined) {
-    static int cache[2][2][16] = {};
+enum class GridOf { apply, dir, fdir };
+static int resident_grid(int count, int word, GridOf of) {
+    static int cache[3][2][16] = {};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    int& c = cache[pipelined ? 1 : 0][word == 8 ? 1 : 0][dev & 15];
+    int& c = cache[(int)of][word == 8 ? 1 : 0][dev & 15];
     if (c == 0) {
         int nb = 0, ncu = 0;
         hipError_t e;
-        if (pipelined)
+        if (of == GridOf::fdir)
+            e = word == 8 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fdir3d<double>, NT, 0)
+                          : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fdir3d<float>, NT, 0);
+        else if (of == GridOf::dir)
             e = word == 8 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_dir3d_pipe<double>, NT, 0)
                           : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_dir3d_pipe<float>, NT, 0);
         else
@@ -1452,9 +1645,11 @@ Tiles update3d_tiles(const Tiles& tl) {
     return tu;
 }
 
-int apply3d_grid(int count, int word) { return resident_grid(count, word, false); }
+int apply3d_grid(int count, int word) { return resident_grid(count, word, GridOf::apply); }
 
-int dir3d_grid(int count, int word) { return resident_grid(count, word, true); }
+int dir3d_grid(int count, int word) { return resident_grid(count, word, GridOf::dir); }
+
+int fdir3d_grid(int count, int word) { return resident_grid(count, word, GridOf::fdir); }
 
 // Workgroups of the fused 3D iteration (FP32): its occupancy x compute units.
 int fused3d_grid(int count) {
@@ -1519,8 +1714,7 @@ void launch_apply3d(const Geo& g, const Tiles& tl, int mode, bool zin, const T* 
             hipLaunchKernelGGL((k_dir3d_pipe<T>), dim3(dir3d_grid(tl.items(), (int)sizeof(T))),
                                dim3(NT), 0, s, g, tl, r, dinv, pin, pout, q, a, c, K, ra);
     } else if (mode == MODE_FDIR) {
-        hipLaunchKernelGGL((k_apply3d<T, MODE_FDIR, false>), gs, dim3(NT), 0, s, g, tl, r, zsrc,
-                           dinv, pin, pout, q, a, c, K, bvec, ra);
+        hipLaunchKernelGGL(k_fdir3d<T>, dim3(fdir3d_grid(tl.items(), (int)sizeof(T))), dim3(NT), 0, s, g, tl, r, zsrc, dinv, pout, q, a, c, K, ra);
     } else if (mode == MODE_JDIR) {
         if (zin)
             hipLaunchKernelGGL((k_apply3d<T, MODE_JDIR, true>), gs, dim3(NT), 0, s, g, tl, r, zsrc,

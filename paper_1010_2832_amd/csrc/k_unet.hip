@@ -86,7 +86,7 @@ __device__ __forceinline__ long long tap_off(const Level& L, int t) {
 // voxels abound (a weight operand feeds NV products); on the coarse levels that
 // leaves most of the chip idle (8^3 voxels, 128 to 64 channels: 2 workgroups, 122
 // us), and a wave takes 16 voxels and 16 channels, a workgroup each (18 us; 64 to
-// 32 channels at 16^3 40 and 14; at 28 x 26 x 24, 68 workgroups, 40 and 35).  The
+// 32 channels at 16^3 40 and 14).  The
 // sum over K is the same either way.
 template <int CIN, int COUT, bool SMALL>
 struct ConvShape {
@@ -350,7 +350,11 @@ void conv_launch_z(const ConvArgs& a, hipStream_t s) {
                        nty, zc);
 }
 
-constexpr unsigned kConvFew = 256;
+// workgroups of large tiles below which small ones are faster: the small tiles' time
+// grows with the voxels (us at 14 x 13 x 12 and at 32^3, 128 to 64 channels, small 39
+// and 176, large 115 and 94; at 28 x 26 x 24, 64 to 32, 35 and 40, 32 to 64, 21 and 37)
+template <int CIN, int COUT>
+constexpr unsigned kConvFew = CIN == 128 ? 48 : (CIN == 32 ? 128 : (COUT == 32 ? 64 : 96));
 
 template <int CIN, int COUT, int EPI>
 void conv_launch(const ConvArgs& a, hipStream_t s) {
@@ -358,7 +362,7 @@ void conv_launch(const ConvArgs& a, hipStream_t s) {
     const long long V = a.L.voxels();
     const unsigned nb = (unsigned)((V + S::VPB - 1) / S::VPB);
     if (nb == 0) return;
-    if (nb < kConvFew)   // fewer than the compute units
+    if (nb < kConvFew<CIN, COUT>)
         hipLaunchKernelGGL((k_conv3<CIN, COUT, EPI, true>), dim3((unsigned)((V + 15) / 16), COUT / 16), dim3(64),
                            0, s, a);
     else

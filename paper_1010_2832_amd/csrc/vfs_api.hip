@@ -459,7 +459,7 @@ int run_chunks_fcg(vfs_ctx* ctx, Vecs<float>& v, bool set_bb, Scalars* out) {
     const Parts P = parts(ctx);
     vfs_unet* u = ctx->net;
     hipStream_t s = ctx->stream;
-    const int nbA = apply_blocks(g, ctx->tiles, 4), nbU = update_blocks(g, ctx->tiles);
+    const int nbA = fdir3d_grid(ctx->tiles.items(), 4), nbU = update_blocks(g, ctx->tiles);
     const int nbV = vec_grid_blocks(g), nbZ = coarse_blocks(g);
     const int* skip = &ctx->sc->done;
     constexpr int R = kFcgMax + 1;

@@ -463,6 +463,7 @@ int apply_blocks(const Geo& g, const Tiles& tl, int word);
 int dir_apply_blocks(const Geo& g, const Tiles& tl, int word);
 int apply3d_grid(int count, int word);
 int dir3d_grid(int count, int word);
+int fdir3d_grid(int count, int word);
 // one launch per Jacobi-PCG iteration in 3D (FP32), k_apply3d.hip
 // over the work tiles of fused_tile_dims (the list launch_fused_tiles builds
 // from the tile flags), skipping the rows of rowbits without an active sample;
