@@ -121,7 +121,10 @@ typedef struct vfs_stats {
        iterations.  The VFS_MIXED Jacobi solve (2D and 3D) runs one fused
        launch per iteration: t_apply_avg_ms is then its average over the
        back-to-back launches of each chunk after the first, t_update_avg_ms
-       is 0 and n_apply_timed counts the timed chunks. */
+       is 0 and n_apply_timed counts the timed chunks.  Where a whole Jacobi
+       CG run is one launch (small active sets, both arithmetics),
+       t_apply_avg_ms is that launch's time over its iterations and
+       n_apply_timed counts the runs. */
     double  t_apply_avg_ms;
     double  t_update_avg_ms;
     int64_t n_apply_timed;

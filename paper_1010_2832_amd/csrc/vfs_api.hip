@@ -1108,6 +1108,17 @@ int vfs_create(vfs_ctx** out, int dim, int nx, int ny, int nz, double h, const d
         vfs_destroy(ctx);                            \
         return fail(nullptr, rc, m);                 \
     }
+// the resident solve's memory; without it the context keeps to launched iterations
+#define RESIDENT(n)                                                   \
+    if ((rc = dalloc(ctx, &ctx->res_part, (n))) == VFS_ENOMEM) {      \
+        (void)hipGetLastError();                                      \
+        ctx->err.clear();                                             \
+        rc = VFS_OK;                                                  \
+    } else if (rc != VFS_OK) {                                        \
+        const std::string m = ctx->err;                               \
+        vfs_destroy(ctx);                                             \
+        return fail(nullptr, rc, m);                                  \
+    }
     ALLOC(ctx->phi_l, node_count(g));
     ALLOC(ctx->phi_s, node_count(g));
     ALLOC(ctx->rho, NP);
@@ -1182,12 +1193,14 @@ int vfs_create(vfs_ctx** out, int dim, int nx, int ny, int nz, double h, const d
             const long long part = 4 * kRes3dMost * 16, lists = kRes3dShapes * kRes3dMost;
             ctx->res_msg_words = res3d_words();
             // one allocation: words, messages, then lists, ranks and flags
-            ALLOC(ctx->res_part, part + ctx->res_msg_words + (lists + all + most + 1) / 2);
-            ctx->res_msg = ctx->res_part + part;
-            ctx->res_lists = (int*)(ctx->res_msg + ctx->res_msg_words);
-            ctx->res_rank[0] = ctx->res_lists + lists;
-            for (int q = 1; q < kRes3dShapes; ++q) ctx->res_rank[q] = ctx->res_rank[q - 1] + nb[q - 1];
-            ctx->res_flags = ctx->res_rank[kRes3dShapes - 1] + nb[kRes3dShapes - 1];
+            RESIDENT(part + ctx->res_msg_words + (lists + all + most + 1) / 2);
+            if (ctx->res_part) {
+                ctx->res_msg = ctx->res_part + part;
+                ctx->res_lists = (int*)(ctx->res_msg + ctx->res_msg_words);
+                ctx->res_rank[0] = ctx->res_lists + lists;
+                for (int q = 1; q < kRes3dShapes; ++q) ctx->res_rank[q] = ctx->res_rank[q - 1] + nb[q - 1];
+                ctx->res_flags = ctx->res_rank[kRes3dShapes - 1] + nb[kRes3dShapes - 1];
+            }
         }
     } else {
         ALLOC(ctx->tile_flags, nt2);
@@ -1203,15 +1216,18 @@ int vfs_create(vfs_ctx** out, int dim, int nx, int ny, int nz, double h, const d
             // one allocation: words, messages, partial sums, then lists and flags
             const long long part = 2 * kResMost * 16, lists = kResShapes * kResMost;
             const long long t64 = res2d_tiles64(g), tl = (long long)ltx * lty;
-            ALLOC(ctx->res_part, part + ctx->res_msg_words + t64 + (lists + t64 + tl + t64 + 1) / 2);
-            ctx->res_msg = ctx->res_part + part;
-            ctx->res_part64 = (double*)(ctx->res_msg + ctx->res_msg_words);
-            ctx->res_lists = (int*)(ctx->res_part64 + t64);
-            ctx->res_list64 = ctx->res_lists + lists;
-            ctx->res_flags = ctx->res_list64 + t64;
+            RESIDENT(part + ctx->res_msg_words + t64 + (lists + t64 + tl + t64 + 1) / 2);
+            if (ctx->res_part) {
+                ctx->res_msg = ctx->res_part + part;
+                ctx->res_part64 = (double*)(ctx->res_msg + ctx->res_msg_words);
+                ctx->res_lists = (int*)(ctx->res_part64 + t64);
+                ctx->res_list64 = ctx->res_lists + lists;
+                ctx->res_flags = ctx->res_list64 + t64;
+            }
         }
     }
 #undef ALLOC
+#undef RESIDENT
     if (hipHostMalloc((void**)&ctx->sc_host, 4 * sizeof(Scalars), hipHostMallocDefault) !=
             hipSuccess ||
         hipHostMalloc((void**)&ctx->flag_host, 8 * sizeof(int), hipHostMallocDefault) !=
