@@ -1043,6 +1043,12 @@ __global__ __launch_bounds__(G * FNA, 2 * G) void k_fused3d(Geo g, Tiles ft, Fus
     for (int wtile = fq.first; wtile < fq.t1;) {
         int xt, j0, k0, kend;
         fused_origin(ft, g, wtile, xt, j0, k0, kend);
+        // a part of a split tile past the last plane: no row bits are read for it,
+        // so nothing may be loaded (whole tiles, the only claimed items, have planes)
+        if (k0 >= kend) {
+            wtile += fq.step;
+            continue;
+        }
         const int i0 = xt * FTX;
         const int io = i0 + tx, jo = j0 + ty;
         const int ih = i0 - 1 + hli, jh = j0 - 1 + hlj;
