@@ -228,6 +228,26 @@ int vfs_set_gravity(vfs_ctx* ctx, const double* g);
 int vfs_set_solver(vfs_ctx* ctx, int precond, int precision, double rel_tol,
                    int max_iter, double w_min);
 
+/* Forms a solve may take (a sum of VFS_FORM_*, default VFS_FORM_RESIDENT).
+ * RESIDENT: a Jacobi CG run whose active set fits on the chip is one launch
+ * whose workgroups wait for each other; without it every iteration is launched
+ * and the memory that such runs need is given back.  Where the workgroups
+ * cannot all run (another process or stream holds compute units for over a
+ * second) the run is given up and done again by launched iterations.  Both
+ * forms meet the tolerance; VFS_MIXED iterates are the same bits, VFS_FP64 ones
+ * agree to rounding.
+ * GIVE_UP and NO_MEMORY are for tests: every resident run is given up, and no
+ * memory is found beyond that of vfs_create (a preconditioner or resident run
+ * that needs some then takes the form that does not). */
+#define VFS_FORM_RESIDENT  1
+#define VFS_FORM_GIVE_UP   2
+#define VFS_FORM_NO_MEMORY 4
+int vfs_set_forms(vfs_ctx* ctx, int forms);
+/* The forms allowed, the form of the last solve (resident: index of the tile or
+ * brick shape its last run took, -1 launched iterations) and the resident runs
+ * given up so far.  NULL for what is not wanted. */
+int vfs_get_forms(vfs_ctx* ctx, int* forms, int* resident, int* give_ups);
+
 /* One full step: u* = u + dt g, fractions, coefficients, null-space
  * elimination, right-hand side, CG solve, velocity recovery.  The new
  * velocity replaces the context's velocity.  Returns VFS_ENOTCONV /
@@ -295,20 +315,22 @@ int vfs_liquid_weights_noalloc(int dim, int nx, int ny, int nz, double w_min,
 
 /* ------------------------------------------------------------------------
  * Batched 2D steps: many independent problems of different sizes.  All
- * their solves run in one persistent launch (FP32 Jacobi PCG with FP64
- * reductions, FP64 residual and iterative refinement per problem, each
- * problem retiring on its own), captured once in a hipGraph and replayed.
- * Every problem is a full step of the method above (same equations, inputs
+ * their solves run in one launch (FP32 Jacobi PCG with FP64 reductions, FP64
+ * residual and iterative refinement per problem, each problem retiring on its
+ * own), captured once in a hipGraph and replayed: resident on the chip where
+ * every problem fits (vfs_batch_set_forms), else a persistent kernel that
+ * walks the tiles of all problems.  Every problem is a full step of the method above (same equations, inputs
  * and outputs as a single context), always in VFS_MIXED arithmetic.
  * ------------------------------------------------------------------------ */
 typedef struct vfs_batch vfs_batch;
 
 typedef struct vfs_batch_stats {
     int32_t n_problems;
-    int32_t variant;          /* tile shape index (vfs_batch_variant_shape) */
+    int32_t variant;          /* tile shape index (vfs_batch_variant_shape) of the
+                                 persistent kernel, also where the step ran resident */
     int32_t blocks_per_cu;    /* persistent workgroups per compute unit (the requested
-                                 number, capped at what can be resident) */
-    int32_t grid;             /* persistent workgroups launched */
+                                 number, capped at what can be resident), likewise */
+    int32_t grid;             /* workgroups launched */
     int32_t graph_used;       /* 1 if the pass ran from a hipGraph */
     int32_t status;           /* VFS_OK or VFS_ENOTCONV */
     int64_t n_active_total;   /* sum of active unknowns */
@@ -319,8 +341,9 @@ typedef struct vfs_batch_stats {
     double  latency_p50_ms, latency_p90_ms, latency_p99_ms, latency_max_ms;
                               /* per-problem solve latency: device wall clock from
                                  the start of the solve to the pass that met tol */
-    int64_t n_items;          /* work items of the last step: the tiles holding an
-                                 active sample (at least one per problem) */
+    int64_t n_items;          /* work items of the last step in the persistent kernel's
+                                 tiles: those holding an active sample (at least one
+                                 per problem) */
     int64_t n_tile_samples;   /* sample positions those items sweep per CG iteration */
 } vfs_batch_stats;
 
@@ -337,8 +360,9 @@ int vfs_batch_set_problem(vfs_batch* b, int i, const double* phi_liquid, const d
                           const double* rho, const double* mu, const double* u, const double* v,
                           const double* ub, const double* vb, const double* g);
 int vfs_batch_set_solver(vfs_batch* b, double rel_tol, int max_iter, double w_min);
-/* Launch configuration: tile shape variant and persistent workgroups per
- * compute unit (clamped to the occupancy limit); chosen by the autotuner. */
+/* Launch configuration of the persistent kernel: tile shape variant and
+ * workgroups per compute unit (clamped to the occupancy limit); chosen by the
+ * autotuner.  A step that runs resident chooses its own tiles. */
 int vfs_batch_num_variants(void);
 int vfs_batch_variant_shape(int variant, int* bx, int* by);
 int vfs_batch_set_tiles(vfs_batch* b, int variant, int blocks_per_cu);
@@ -359,6 +383,10 @@ int vfs_batch_get_solution(vfs_batch* b, int i, double* x);   /* sample order */
 int vfs_batch_get_problem(vfs_batch* b, int i, int* iterations, int* passes,
                           double* rel_residual, double* latency_ms, int64_t* n_active);
 int vfs_batch_get_stats(vfs_batch* b, vfs_batch_stats* out);
+/* As vfs_set_forms and vfs_get_forms, for the batch: without RESIDENT, and
+ * where a resident launch was given up, the persistent kernel solves. */
+int vfs_batch_set_forms(vfs_batch* b, int forms);
+int vfs_batch_get_forms(vfs_batch* b, int* forms, int* resident, int* give_ups);
 
 /* ------------------------------------------------------------------------
  * Learned preconditioner (3D).  Not part of the paper, whose CG uses an

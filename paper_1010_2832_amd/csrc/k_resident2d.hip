@@ -702,7 +702,7 @@ __global__ __launch_bounds__(NT, 1) void k_batch_resident(BatchArgs B, const BRe
     }
 }
 
-__global__ __launch_bounds__(256) void k_batch_resident_start(BatchArgs A, unsigned* beats) {
+__global__ __launch_bounds__(256) void k_batch_resident_start(BatchArgs A, unsigned* beats, int give_up) {
     const int p = blockIdx.y;
     const BProb& P = A.prob[p];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -712,7 +712,7 @@ __global__ __launch_bounds__(256) void k_batch_resident_start(BatchArgs A, unsig
         S.rel = S.rho2 = S.bb64 = 0.0;
         S.iters_total = S.passes = S.needs = 0;
         S.stamp = 0;
-        if (p == 0) A.ctl->abort = 0;
+        if (p == 0) A.ctl->abort = give_up;
     }
     if (p == 0 && blockIdx.x == 0) beats[threadIdx.x] = 0;
     const long long n = 3 * P.g.NP;
@@ -828,8 +828,9 @@ void launch_resident2d(const Geo& g, int shape, const int* tiles, int count, con
     else if constexpr (sizeof(T) == 4) launch_rpt<T, 8>(S, count, s);
 }
 
-void launch_batch_resident_start(const BatchArgs& A, unsigned* beats, hipStream_t s) {
-    hipLaunchKernelGGL(k_batch_resident_start, dim3(64, A.nprob), dim3(256), 0, s, A, beats);
+void launch_batch_resident_start(const BatchArgs& A, unsigned* beats, bool give_up, hipStream_t s) {
+    hipLaunchKernelGGL(k_batch_resident_start, dim3(64, A.nprob), dim3(256), 0, s, A, beats,
+                       give_up ? 1 : 0);
 }
 
 void launch_batch_resident(int shape, const BatchArgs& A, const BResProb* rp, const BResWg* wg,

@@ -305,6 +305,7 @@ int res3d_shape(vfs_ctx* ctx, int word) {
     if (word == 4) return fits(1, most) ? 1 : -1;
     if (!fits(0, 2 * most) || !res3d_two()) return -1;
     if (!ctx->res_stream) {   // 54 MB, for the solves that use it
+        if (ctx->forms & VFS_FORM_NO_MEMORY) return -1;
         const size_t bytes = (size_t)res3d_stream(2 * most) * sizeof(double);
         if (hipMalloc((void**)&ctx->res_stream, bytes) != hipSuccess) {
             ctx->res_stream = nullptr;
@@ -332,6 +333,7 @@ int run_resident(vfs_ctx* ctx, int shape, Vecs<T>& v, bool set_bb, int max_iter,
         HIPCHK(hipMemsetAsync(ctx->res_msg, 0, ctx->res_msg_words * sizeof(*ctx->res_msg), s));
         ctx->res_stamp = 0;
     }
+    if (ctx->forms & VFS_FORM_GIVE_UP) HIPCHK(hipMemsetAsync(&ctx->sc->aborted, 1, sizeof(int), s));
     std::lock_guard<std::mutex> one(res_mutex());
     if (ctx->prof) HIPCHK(hipEventRecord(ctx->pev[0], s));
     if (ctx->g.dim == 2) {
@@ -357,9 +359,12 @@ int run_resident(vfs_ctx* ctx, int shape, Vecs<T>& v, bool set_bb, int max_iter,
     *gave_up = out->aborted != 0 || out->done == 0;
     if (*gave_up) {
         ctx->res_off = true;
+        ctx->res_ran = -1;
+        ++ctx->res_give_ups;
         return VFS_OK;
     }
     ctx->res_stamp += (unsigned)out->iter + 4u;
+    ctx->res_ran = shape;
     if (ctx->prof) {   // average over the iterations of the run
         ctx->prof_apply_ms += elapsed(ctx->pev[0], ctx->pev[1]) / std::max(1, out->iter + 1);
         ++ctx->prof_apply_n;
@@ -812,6 +817,7 @@ int solve_schwarz(vfs_ctx* ctx, const double* b, double* x) {
 }
 
 int solve_internal(vfs_ctx* ctx, const double* b, double* x) {
+    ctx->res_ran = -1;
     if (ctx->g.dim == 3 && ctx->tiles.count == 0) {   // nothing active: x = 0
         HIPCHK(hipMemsetAsync(x, 0, (size_t)ctx->g.nsamp() * ctx->g.NP * sizeof(double),
                               ctx->stream));
@@ -1000,6 +1006,63 @@ int ctx_get_samples(vfs_ctx* ctx, const double* src, double* user) {
     return unpack_samples(ctx, src, user);
 }
 int ctx_fail(vfs_ctx* ctx, int code, const std::string& msg) { return fail(ctx, code, msg); }
+
+// The resident solve's memory, one allocation; without it (res_part null) the
+// context keeps to launched iterations.
+int res_alloc(vfs_ctx* ctx) {
+    const Geo& g = ctx->g;
+    auto alloc = [&](long long words) {
+        const int rc = dalloc(ctx, &ctx->res_part, words);
+        if (rc != VFS_ENOMEM) return rc;
+        (void)hipGetLastError();
+        ctx->err.clear();
+        return (int)VFS_OK;
+    };
+    std::fill(ctx->res_count, ctx->res_count + kResShapes, 0);   // until the next assembly
+    if (g.dim == 3) {
+        // at most 256 or 512 bricks; on grids up to about 130^3 that can be a thin
+        // or small body of liquid, or half of a 60^3 box
+        if (g.NP > 3000000) return VFS_OK;
+        long long nb[kRes3dShapes], most = 0, all = 0;
+        for (int q = 0; q < kRes3dShapes; ++q) {
+            int x, y, z;
+            res3d_lattice(g, q, x, y, z);
+            nb[q] = (long long)x * y * z;
+            most = std::max(most, nb[q]);
+            all += nb[q];
+        }
+        const long long part = 4 * kRes3dMost * 16, lists = kRes3dShapes * kRes3dMost;
+        ctx->res_msg_words = res3d_words();
+        // words, messages, then lists, ranks and flags
+        const int rc = alloc(part + ctx->res_msg_words + (lists + all + most + 1) / 2);
+        if (rc || !ctx->res_part) return rc;
+        ctx->res_msg = ctx->res_part + part;
+        ctx->res_lists = (int*)(ctx->res_msg + ctx->res_msg_words);
+        ctx->res_rank[0] = ctx->res_lists + lists;
+        for (int q = 1; q < kRes3dShapes; ++q) ctx->res_rank[q] = ctx->res_rank[q - 1] + nb[q - 1];
+        ctx->res_flags = ctx->res_rank[kRes3dShapes - 1] + nb[kRes3dShapes - 1];
+        return VFS_OK;
+    }
+    // at most 256 tiles of 62 x 64 anchors, all of them active; a grid of more
+    // than twice as many is not expected to fit
+    if (g.NP > 2LL * kResMost * 62 * 64) return VFS_OK;
+    int ltx, lty;
+    res2d_lattice(g, ltx, lty);
+    for (int q = 0; q < kResShapes; ++q)
+        ctx->res_msg_words = std::max(ctx->res_msg_words, res2d_words(g, q));
+    // words, messages, partial sums, then lists and flags
+    const long long part = 2 * kResMost * 16, lists = kResShapes * kResMost;
+    const long long t64 = res2d_tiles64(g), tl = (long long)ltx * lty;
+    const int rc = alloc(part + ctx->res_msg_words + t64 + (lists + t64 + tl + t64 + 1) / 2);
+    if (rc || !ctx->res_part) return rc;
+    ctx->res_msg = ctx->res_part + part;
+    ctx->res_part64 = (double*)(ctx->res_msg + ctx->res_msg_words);
+    ctx->res_lists = (int*)(ctx->res_part64 + t64);
+    ctx->res_list64 = ctx->res_lists + lists;
+    ctx->res_flags = ctx->res_list64 + t64;
+    return VFS_OK;
+}
+
 int fail_global(int code, const std::string& msg) { return fail(nullptr, code, msg); }
 
 Geo make_geo(int dim, int nx, int ny, int nz, double h) {
@@ -1108,17 +1171,6 @@ int vfs_create(vfs_ctx** out, int dim, int nx, int ny, int nz, double h, const d
         vfs_destroy(ctx);                            \
         return fail(nullptr, rc, m);                 \
     }
-// the resident solve's memory; without it the context keeps to launched iterations
-#define RESIDENT(n)                                                   \
-    if ((rc = dalloc(ctx, &ctx->res_part, (n))) == VFS_ENOMEM) {      \
-        (void)hipGetLastError();                                      \
-        ctx->err.clear();                                             \
-        rc = VFS_OK;                                                  \
-    } else if (rc != VFS_OK) {                                        \
-        const std::string m = ctx->err;                               \
-        vfs_destroy(ctx);                                             \
-        return fail(nullptr, rc, m);                                  \
-    }
     ALLOC(ctx->phi_l, node_count(g));
     ALLOC(ctx->phi_s, node_count(g));
     ALLOC(ctx->rho, NP);
@@ -1179,55 +1231,17 @@ int vfs_create(vfs_ctx** out, int dim, int nx, int ny, int nz, double h, const d
         ALLOC(ctx->ftile_flags, nf);
         ALLOC(ctx->ftile_list, nf);
         ALLOC(ctx->rowbits, row_bytes(g));
-        // the resident solve holds at most 256 or 512 bricks; on grids up to about
-        // 130^3 that can be a thin or small body of liquid, or half of a 60^3 box
-        if (NP <= 3000000) {
-            long long nb[kRes3dShapes], most = 0, all = 0;
-            for (int q = 0; q < kRes3dShapes; ++q) {
-                int x, y, z;
-                res3d_lattice(g, q, x, y, z);
-                nb[q] = (long long)x * y * z;
-                most = std::max(most, nb[q]);
-                all += nb[q];
-            }
-            const long long part = 4 * kRes3dMost * 16, lists = kRes3dShapes * kRes3dMost;
-            ctx->res_msg_words = res3d_words();
-            // one allocation: words, messages, then lists, ranks and flags
-            RESIDENT(part + ctx->res_msg_words + (lists + all + most + 1) / 2);
-            if (ctx->res_part) {
-                ctx->res_msg = ctx->res_part + part;
-                ctx->res_lists = (int*)(ctx->res_msg + ctx->res_msg_words);
-                ctx->res_rank[0] = ctx->res_lists + lists;
-                for (int q = 1; q < kRes3dShapes; ++q) ctx->res_rank[q] = ctx->res_rank[q - 1] + nb[q - 1];
-                ctx->res_flags = ctx->res_rank[kRes3dShapes - 1] + nb[kRes3dShapes - 1];
-            }
-        }
     } else {
         ALLOC(ctx->tile_flags, nt2);
         ALLOC(ctx->tile_list, nt2);
         ALLOC(ctx->tile_count, 8);
-        // the resident solve holds at most 256 tiles of 62 x 64 anchors, all of
-        // them active; a grid of more than twice as many is not expected to fit
-        if (NP <= 2LL * kResMost * 62 * 64) {
-            int ltx, lty;
-            res2d_lattice(g, ltx, lty);
-            for (int q = 0; q < kResShapes; ++q)
-                ctx->res_msg_words = std::max(ctx->res_msg_words, res2d_words(g, q));
-            // one allocation: words, messages, partial sums, then lists and flags
-            const long long part = 2 * kResMost * 16, lists = kResShapes * kResMost;
-            const long long t64 = res2d_tiles64(g), tl = (long long)ltx * lty;
-            RESIDENT(part + ctx->res_msg_words + t64 + (lists + t64 + tl + t64 + 1) / 2);
-            if (ctx->res_part) {
-                ctx->res_msg = ctx->res_part + part;
-                ctx->res_part64 = (double*)(ctx->res_msg + ctx->res_msg_words);
-                ctx->res_lists = (int*)(ctx->res_part64 + t64);
-                ctx->res_list64 = ctx->res_lists + lists;
-                ctx->res_flags = ctx->res_list64 + t64;
-            }
-        }
     }
 #undef ALLOC
-#undef RESIDENT
+    if ((rc = res_alloc(ctx)) != VFS_OK) {
+        const std::string m = ctx->err;
+        vfs_destroy(ctx);
+        return fail(nullptr, rc, m);
+    }
     if (hipHostMalloc((void**)&ctx->sc_host, 4 * sizeof(Scalars), hipHostMallocDefault) !=
             hipSuccess ||
         hipHostMalloc((void**)&ctx->flag_host, 8 * sizeof(int), hipHostMallocDefault) !=
@@ -1468,7 +1482,7 @@ int vfs_set_solver(vfs_ctx* ctx, int precond, int precision, double rel_tol, int
     if (!(rel_tol > 0.0) || !(rel_tol < 1.0)) return fail(ctx, VFS_EINVAL, "rel_tol must be in (0,1)");
     if (max_iter < 1) return fail(ctx, VFS_EINVAL, "max_iter must be >= 1");
     if (!(w_min >= 0.0) || !(w_min < 0.5)) return fail(ctx, VFS_EINVAL, "w_min must be in [0,0.5)");
-    if (precond == VFS_PRECOND_SCHWARZ && !ctx->bricks) {
+    if (precond == VFS_PRECOND_SCHWARZ && !ctx->bricks && !(ctx->forms & VFS_FORM_NO_MEMORY)) {
         // without room for the bricks' corrections they are added class by class
         long long bricks, values;
         schwarz_space(ctx->g, &bricks, &values);
@@ -1487,6 +1501,30 @@ int vfs_set_solver(vfs_ctx* ctx, int precond, int precision, double rel_tol, int
     if (w_min != ctx->w_min) ctx->assembled = false;
     ctx->w_min = w_min;
     ctx->stats.precision = precision;
+    return VFS_OK;
+}
+
+int vfs_set_forms(vfs_ctx* ctx, int forms) {
+    if (!ctx) return VFS_EINVAL;
+    if (forms & ~(VFS_FORM_RESIDENT | VFS_FORM_GIVE_UP | VFS_FORM_NO_MEMORY))
+        return fail(ctx, VFS_EINVAL, "unknown form");
+    ctx->forms = forms;
+    if (forms & VFS_FORM_RESIDENT)
+        return ctx->res_part || (forms & VFS_FORM_NO_MEMORY) ? VFS_OK : res_alloc(ctx);
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    for (void* p : {(void*)ctx->res_part, (void*)ctx->res_stream})
+        if (p) (void)hipFree(p);
+    ctx->res_part = nullptr;
+    ctx->res_stream = nullptr;
+    ctx->res_stamp = 0;   // the next memory is zero
+    return VFS_OK;
+}
+
+int vfs_get_forms(vfs_ctx* ctx, int* forms, int* resident, int* give_ups) {
+    if (!ctx) return VFS_EINVAL;
+    if (forms) *forms = ctx->forms;
+    if (resident) *resident = ctx->res_ran;
+    if (give_ups) *give_ups = ctx->res_give_ups;
     return VFS_OK;
 }
 

@@ -116,8 +116,8 @@ void launch_batch_tile_flags(const BProb* prob, const int* full_prob, int nfull,
                              int* flags, hipStream_t s);
 void launch_batch_reset_ctl(BatchCtl* ctl, hipStream_t s);
 // zero solution, fresh state and start time of every problem, abort flag and
-// beats cleared
-void launch_batch_resident_start(const BatchArgs& A, unsigned* beats, hipStream_t s);
+// beats cleared (give_up: the flag is raised, so that the launch is given up)
+void launch_batch_resident_start(const BatchArgs& A, unsigned* beats, bool give_up, hipStream_t s);
 // every problem's whole mixed solve (A.prob, A.state, A.ctl, tolerance and limits)
 void launch_batch_resident(int shape, const BatchArgs& A, const BResProb* rp, const BResWg* wg,
                            const int* list, unsigned* beats, int grid, hipStream_t s);

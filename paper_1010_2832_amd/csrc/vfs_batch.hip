@@ -57,6 +57,8 @@ struct vfs_batch {
     unsigned* d_beats = nullptr;
     int res_shape = -1, graph_shape = -1, res_groups = 0;
     bool res_off = false;
+    int forms = VFS_FORM_RESIDENT;
+    int res_ran = -1, res_give_ups = 0;   // shape of the last step, launches given up
     // graph of the whole solve
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
@@ -163,6 +165,18 @@ bool all_assembled(const vfs_batch* b) {
     return true;
 }
 
+void drop_graph(vfs_batch* b) {
+    if (b->gexec) {
+        (void)hipGraphExecDestroy(b->gexec);
+        b->gexec = nullptr;
+    }
+    if (b->graph) {
+        (void)hipGraphDestroy(b->graph);
+        b->graph = nullptr;
+    }
+    b->graph_ok = false;
+}
+
 // (re)build the tile list of every problem for the current tile variant; the
 // live items are all tiles until the next assembly compacts them
 int build_items(vfs_batch* b) {
@@ -235,15 +249,7 @@ int build_items(vfs_batch* b) {
     const int use = std::max(1, std::min(b->blocks_per_cu, bpc));
     b->bpc_used = use;
     b->grid = std::max(1, std::min(b->ncu * use, b->nfull));
-    if (b->gexec) {
-        (void)hipGraphExecDestroy(b->gexec);
-        b->gexec = nullptr;
-    }
-    if (b->graph) {
-        (void)hipGraphDestroy(b->graph);
-        b->graph = nullptr;
-    }
-    b->graph_ok = false;
+    drop_graph(b);
     return VFS_OK;
 }
 
@@ -293,7 +299,7 @@ bool res_pack(const std::vector<int>& order, const std::vector<int>& w, const st
 // side, small ones shorten the longest.
 int plan_resident(vfs_batch* b) {
     b->res_shape = -1;
-    if (b->res_off) return VFS_OK;
+    if (b->res_off || !(b->forms & VFS_FORM_RESIDENT)) return VFS_OK;
     const int most = res_most();
     const double cost[kBResShapes] = {2.7, 3.2, 4.4};
     std::vector<ResGroup> best, trial;
@@ -384,7 +390,7 @@ int plan_resident(vfs_batch* b) {
 void enqueue_solve(vfs_batch* b, hipStream_t s) {
     if (b->res_shape >= 0) {
         const BatchArgs A = args(b, 0);
-        launch_batch_resident_start(A, b->d_beats, s);
+        launch_batch_resident_start(A, b->d_beats, (b->forms & VFS_FORM_GIVE_UP) != 0, s);
         launch_batch_resident(b->res_shape, A, (const BResProb*)b->d_res, res_wgs(b->d_res, b->n),
                               res_list(b->d_res, b->n), b->d_beats, res_most(), s);
         return;
@@ -400,15 +406,7 @@ void enqueue_solve(vfs_batch* b, hipStream_t s) {
 
 int ensure_graph(vfs_batch* b) {
     if (b->graph_ok && b->graph_shape == b->res_shape) return VFS_OK;
-    if (b->gexec) {
-        (void)hipGraphExecDestroy(b->gexec);
-        b->gexec = nullptr;
-    }
-    if (b->graph) {
-        (void)hipGraphDestroy(b->graph);
-        b->graph = nullptr;
-    }
-    b->graph_ok = false;
+    drop_graph(b);
     BCHK(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
     enqueue_solve(b, b->stream);
     hipGraph_t g = nullptr;
@@ -448,6 +446,7 @@ int solve_all(vfs_batch* b, bool use_graph) {
         if (b->h_ctl->abort) {   // again, by the persistent kernel
             b->res_off = true;
             b->res_shape = -1;
+            ++b->res_give_ups;
             one.unlock();
             return solve_all(b, use_graph);
         }
@@ -563,15 +562,7 @@ int vfs_batch_set_stream(vfs_batch* b, void* stream) {
     if (!b) return VFS_EINVAL;
     b->stream = stream ? (hipStream_t)stream : b->own_stream;
     for (auto* c : b->ctx) c->stream = b->stream;
-    if (b->gexec) {
-        (void)hipGraphExecDestroy(b->gexec);
-        b->gexec = nullptr;
-    }
-    if (b->graph) {
-        (void)hipGraphDestroy(b->graph);
-        b->graph = nullptr;
-    }
-    b->graph_ok = false;
+    drop_graph(b);
     return VFS_OK;
 }
 
@@ -601,15 +592,7 @@ int vfs_batch_set_solver(vfs_batch* b, double rel_tol, int max_iter, double w_mi
     b->tol = rel_tol;
     b->max_iter = max_iter;
     b->max_iter_pass = std::min(max_iter, 50000);
-    if (b->gexec) {
-        (void)hipGraphExecDestroy(b->gexec);
-        b->gexec = nullptr;
-    }
-    if (b->graph) {
-        (void)hipGraphDestroy(b->graph);
-        b->graph = nullptr;
-    }
-    b->graph_ok = false;
+    drop_graph(b);
     return VFS_OK;
 }
 
@@ -646,6 +629,7 @@ int vfs_batch_step(vfs_batch* b, double dt) {
     // stats
     vfs_batch_stats& S = b->stats;
     S = vfs_batch_stats{};
+    b->res_ran = b->res_shape;
     S.n_problems = b->n;
     S.variant = b->variant;
     S.blocks_per_cu = b->bpc_used;
@@ -726,6 +710,23 @@ int vfs_batch_get_problem(vfs_batch* b, int i, int* iterations, int* passes,
 int vfs_batch_get_stats(vfs_batch* b, vfs_batch_stats* out) {
     if (!b || !out) return VFS_EINVAL;
     *out = b->stats;
+    return VFS_OK;
+}
+
+int vfs_batch_set_forms(vfs_batch* b, int forms) {
+    if (!b) return VFS_EINVAL;
+    if (forms & ~(VFS_FORM_RESIDENT | VFS_FORM_GIVE_UP | VFS_FORM_NO_MEMORY))
+        return bfail(b, VFS_EINVAL, "unknown form");
+    b->forms = forms;
+    drop_graph(b);   // it holds whether to give up
+    return VFS_OK;
+}
+
+int vfs_batch_get_forms(vfs_batch* b, int* forms, int* resident, int* give_ups) {
+    if (!b) return VFS_EINVAL;
+    if (forms) *forms = b->forms;
+    if (resident) *resident = b->res_ran;
+    if (give_ups) *give_ups = b->res_give_ups;
     return VFS_OK;
 }
 

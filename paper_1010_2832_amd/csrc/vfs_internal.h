@@ -276,7 +276,7 @@ struct vfs_ctx {
     // resident CG: exchange buffers, tile lists by shape and the stamp the next
     // solve starts from (null buffers: the grid is too large for it); res_off
     // is set when a wait was given up and keeps this context to the launched
-    // iteration
+    // iteration; res_ran: shape of the last solve's runs (-1: launched)
     vfs::LLWordBuf res_part = nullptr, res_msg = nullptr;
     long long res_msg_words = 0;
     int* res_flags = nullptr;
@@ -289,6 +289,8 @@ struct vfs_ctx {
     int* res_rank[vfs::kRes3dShapes] = {};   // 3D: workgroup of every brick
     unsigned res_stamp = 0;
     bool res_off = false;
+    int forms = VFS_FORM_RESIDENT;
+    int res_ran = -1, res_give_ups = 0;
     // 3D: work tiles of the fused iteration holding an active tile, and one
     // byte per kRow3X-anchor row (x part, y, z) with bit s set if sample slice
     // s has an active sample in the row
@@ -327,6 +329,8 @@ namespace vfs {
 // and the lock held while one runs
 int res_most();
 std::mutex& res_mutex();
+// memory for a context's resident solves (none where it cannot be had)
+int res_alloc(vfs_ctx* ctx);
 
 // error message of a call without a context (read by vfs_last_error(NULL))
 int fail_global(int code, const std::string& msg);

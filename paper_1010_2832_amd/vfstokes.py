@@ -27,6 +27,7 @@ VFS_SET_CELL, VFS_SET_FACE_X, VFS_SET_FACE_Y, VFS_SET_FACE_Z = 0, 1, 2, 3
 VFS_SET_NODE = VFS_SET_EDGE_Z = 4
 VFS_SET_EDGE_Y, VFS_SET_EDGE_X = 5, 6
 VFS_WEIGHT_LIQUID, VFS_WEIGHT_FLUID = 0, 1
+VFS_FORM_RESIDENT, VFS_FORM_GIVE_UP, VFS_FORM_NO_MEMORY = 1, 2, 4
 
 _CODES = {0: "VFS_OK", -1: "VFS_EINVAL", -2: "VFS_ENOMEM", -3: "VFS_EHIP", -4: "VFS_ENOTCONV",
           -5: "VFS_EBREAKDOWN", -6: "VFS_ESTATE"}
@@ -102,6 +103,8 @@ _SIGS = {
     "vfs_get_level_set": ([_P, _P], _I),
     "vfs_set_warm_start": ([_P, _I], _I),
     "vfs_set_solver": ([_P, _I, _I, _D, _I, _D], _I),
+    "vfs_set_forms": ([_P, _I], _I),
+    "vfs_get_forms": ([_P, ctypes.POINTER(_I), ctypes.POINTER(_I), ctypes.POINTER(_I)], _I),
     "vfs_step": ([_P, _D], _I),
     "vfs_assemble": ([_P, _D], _I),
     "vfs_apply": ([_P, _P, _P], _I),
@@ -135,6 +138,8 @@ _SIGS = {
     "vfs_batch_get_problem": ([_P, _I, ctypes.POINTER(_I), ctypes.POINTER(_I), ctypes.POINTER(_D),
                                ctypes.POINTER(_D), ctypes.POINTER(ctypes.c_int64)], _I),
     "vfs_batch_get_stats": ([_P, ctypes.POINTER(vfs_batch_stats)], _I),
+    "vfs_batch_set_forms": ([_P, _I], _I),
+    "vfs_batch_get_forms": ([_P, ctypes.POINTER(_I), ctypes.POINTER(_I), ctypes.POINTER(_I)], _I),
     "vfs_unet_last_error": ([_P], ctypes.c_char_p),
     "vfs_unet_param_count": ([], ctypes.c_int64),
     "vfs_unet_create": ([ctypes.POINTER(_P)], _I),
@@ -375,6 +380,14 @@ class Context:
                                                      max_iter, w_min))
         self._solver = (precond, precision, rel_tol, max_iter, w_min)
         return rc
+
+    def vfs_set_forms(self, forms=VFS_FORM_RESIDENT):
+        return _check(self.handle, _lib.vfs_set_forms(self.handle, forms))
+
+    def vfs_get_forms(self):
+        f, r, g = _I(), _I(), _I()
+        _check(self.handle, _lib.vfs_get_forms(self.handle, ctypes.byref(f), ctypes.byref(r), ctypes.byref(g)))
+        return dict(forms=f.value, resident=r.value, give_ups=g.value)
 
     # work ------------------------------------------------------------------
     def vfs_step(self, dt, allow_unconverged=False):
@@ -623,6 +636,15 @@ class Batch:
         st = vfs_batch_stats()
         _bcheck(self.handle, _lib.vfs_batch_get_stats(self.handle, ctypes.byref(st)))
         return st.as_dict()
+
+    def vfs_batch_set_forms(self, forms=VFS_FORM_RESIDENT):
+        return _bcheck(self.handle, _lib.vfs_batch_set_forms(self.handle, forms))
+
+    def vfs_batch_get_forms(self):
+        f, r, g = _I(), _I(), _I()
+        _bcheck(self.handle, _lib.vfs_batch_get_forms(self.handle, ctypes.byref(f), ctypes.byref(r),
+                                                      ctypes.byref(g)))
+        return dict(forms=f.value, resident=r.value, give_ups=g.value)
 
 
 def batch_from_cases(case_list, tol=1e-6, max_iter=200000, w_min=1e-3):
