@@ -32,8 +32,9 @@ int res_most() {
     return c;
 }
 
-// One resident solve at a time on a device: two of them could each hold half
-// of the chip and wait for the other half.
+// One kernel at a time on a device whose workgroups wait for each other, resident
+// solve or persistent batch: two of them could each hold half of the chip and wait
+// for the other half.
 std::mutex& res_mutex() {
     static std::mutex m[16];
     int dev = 0;

@@ -428,10 +428,8 @@ int read_state(vfs_batch* b) {
     return VFS_OK;
 }
 
-// solve phase of a step on assembled problems (one graph launch); returns status
-int solve_all(vfs_batch* b, bool use_graph) {
-    std::unique_lock<std::mutex> one(res_mutex(), std::defer_lock);
-    if (b->res_shape >= 0) one.lock();
+// one solve of the assembled problems in the form res_shape names
+int solve_once(vfs_batch* b, bool use_graph) {
     if (use_graph) {
         int rc = ensure_graph(b);
         if (rc) return rc;
@@ -440,19 +438,25 @@ int solve_all(vfs_batch* b, bool use_graph) {
         enqueue_solve(b, b->stream);
     }
     BCHK(hipGetLastError());
-    int rc = read_state(b);
+    return read_state(b);
+}
+
+// solve phase of a step on assembled problems (one graph launch); returns status.
+// Either form's workgroups wait for each other: the lock is held until the step
+// is solved, also when a resident launch is given up.
+int solve_all(vfs_batch* b, bool use_graph) {
+    std::lock_guard<std::mutex> one(res_mutex());
+    int rc = solve_once(b, use_graph);
+    if (!rc && b->res_shape >= 0 && b->h_ctl->abort) {   // again, by the persistent kernel
+        b->res_off = true;
+        b->res_shape = -1;
+        ++b->res_give_ups;
+        rc = solve_once(b, use_graph);
+    }
     if (rc) return rc;
-    if (b->res_shape >= 0) {
-        if (b->h_ctl->abort) {   // again, by the persistent kernel
-            b->res_off = true;
-            b->res_shape = -1;
-            ++b->res_give_ups;
-            one.unlock();
-            return solve_all(b, use_graph);
-        }
+    if (b->res_shape >= 0)
         for (int p = 0; p < b->n; ++p)
             if (b->h_state[p].stamp) b->ctx[p]->res_stamp = b->h_state[p].stamp + 4u;
-    }
     int status = VFS_OK;
     for (int p = 0; p < b->n; ++p)
         if (b->h_state[p].rel > b->tol) status = VFS_ENOTCONV;
@@ -750,6 +754,7 @@ int vfs_batch_time_variant(vfs_batch* b, int variant, int blocks_per_cu, int ite
     b->max_iter_pass = iterations;
     b->max_passes = 1;
     hipStream_t s = b->stream;
+    std::unique_lock<std::mutex> one(res_mutex());
     const BatchArgs A0 = args(b, 1);
     launch_batch_zero(A0, s);
     launch_batch_resid(b->variant, A0, b->grid, s);
@@ -761,6 +766,7 @@ int vfs_batch_time_variant(vfs_batch* b, int variant, int blocks_per_cu, int ite
     BCHK(hipEventRecord(b->ev[1], s));
     BCHK(hipGetLastError());
     BCHK(hipEventSynchronize(b->ev[1]));
+    one.unlock();
     b->max_iter_pass = mip;
     b->max_passes = mp;
     rc = read_state(b);

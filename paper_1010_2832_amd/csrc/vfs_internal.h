@@ -326,7 +326,7 @@ struct vfs_ctx {
 namespace vfs {
 
 // resident solves (vfs_api.hip): the workgroups one may have on this device,
-// and the lock held while one runs
+// and the lock held while one, or a persistent batch, runs
 int res_most();
 std::mutex& res_mutex();
 // memory for a context's resident solves (none where it cannot be had)
