@@ -233,8 +233,8 @@ int vfs_set_solver(vfs_ctx* ctx, int precond, int precision, double rel_tol,
  * whose workgroups wait for each other; without it every iteration is launched
  * and the memory that such runs need is given back.  Where the workgroups
  * cannot all run (another process or stream holds compute units for over a
- * second) the run is given up and done again by launched iterations.  Both
- * forms meet the tolerance; VFS_MIXED iterates are the same bits, VFS_FP64 ones
+ * second) the run is given up and done again by launched iterations, and the
+ * solves of the next 4 s (then 8, 16, ...) are launched too.  Both forms meet the tolerance; VFS_MIXED iterates are the same bits, VFS_FP64 ones
  * agree to rounding.
  * GIVE_UP and NO_MEMORY are for tests: every resident run is given up, and no
  * memory is found beyond that of vfs_create (a preconditioner or resident run

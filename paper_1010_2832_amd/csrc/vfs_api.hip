@@ -289,7 +289,6 @@ int run_chunks(vfs_ctx* ctx, Vecs<T>& v, bool set_bb, Scalars* out) {
 // and what more workgroups cost the exchange (1.4 us a round for 32 of them,
 // 2.3 us for 256) is less than a doubled tile does.
 int res2d_shape(const vfs_ctx* ctx, int word) {
-    if (!ctx->res_part || ctx->res_off) return -1;
     const int most = res_most();
     for (int q = 0; q < (word == 4 ? kResShapes : kResShapes - 1); ++q)
         if (ctx->res_count[q] > 0 && ctx->res_count[q] <= most) return q;
@@ -299,7 +298,6 @@ int res2d_shape(const vfs_ctx* ctx, int word) {
 // Brick shape of the resident 3D solve, or -1: small bricks, one to a compute
 // unit; more of them, in FP32 twice as large, in FP64 two to a unit.
 int res3d_shape(vfs_ctx* ctx, int word) {
-    if (!ctx->res_part || ctx->res_off) return -1;
     const int most = res_most();
     auto fits = [&](int q, int n) { return ctx->res_count[q] > 0 && ctx->res_count[q] <= n; };
     if (fits(0, most)) return 0;
@@ -318,17 +316,18 @@ int res3d_shape(vfs_ctx* ctx, int word) {
 }
 
 int res_shape(vfs_ctx* ctx, int word) {
+    if (!ctx->res_part || ctx->res_pause.on()) return -1;
     return ctx->g.dim == 2 ? res2d_shape(ctx, word) : res3d_shape(ctx, word);
 }
 
 // A whole Jacobi-PCG run on the residual in v.r, added to v.x, in one resident
-// kernel.  VFS_OK with *gave_up set when its workgroups could not all run (the
-// context then keeps to the launched iteration; v.r is untouched, v.x void).
+// kernel.  VFS_OK with *gave_up set when its workgroups could not all run (v.r is
+// untouched, v.x void; the solve goes on by launches).
 template <typename T>
 int run_resident(vfs_ctx* ctx, int shape, Vecs<T>& v, bool set_bb, int max_iter, Scalars* out,
                  bool* gave_up) {
     hipStream_t s = ctx->stream;
-    if (ctx->res_stamp > 0xfffffff0u - (unsigned)max_iter - 8u) {   // stamps would wrap
+    if (ctx->res_stamp > 0xfffffff0u - (unsigned)max_iter - 8u) {   // stamps would wrap, or are unknown
         const size_t part = (ctx->g.dim == 2 ? 2 * kResMost : 4 * kRes3dMost) * 16;
         HIPCHK(hipMemsetAsync(ctx->res_part, 0, part * sizeof(*ctx->res_part), s));
         HIPCHK(hipMemsetAsync(ctx->res_msg, 0, ctx->res_msg_words * sizeof(*ctx->res_msg), s));
@@ -359,12 +358,14 @@ int run_resident(vfs_ctx* ctx, int shape, Vecs<T>& v, bool set_bb, int max_iter,
     if (rc) return rc;
     *gave_up = out->aborted != 0 || out->done == 0;
     if (*gave_up) {
-        ctx->res_off = true;
+        ctx->res_pause.gave_up();
+        ctx->res_stamp = 0xffffffffu;   // words of unknown stamps are about: clear them
         ctx->res_ran = -1;
         ++ctx->res_give_ups;
         return VFS_OK;
     }
     ctx->res_stamp += (unsigned)out->iter + 4u;
+    ctx->res_pause.ran();
     ctx->res_ran = shape;
     if (ctx->prof) {   // average over the iterations of the run
         ctx->prof_apply_ms += elapsed(ctx->pev[0], ctx->pev[1]) / std::max(1, out->iter + 1);
@@ -548,12 +549,12 @@ int zero_dirs(vfs_ctx* ctx, bool f32) {
 }
 
 // FP64 solve of A x = b (padded device vectors); fills stats.
-int solve_fp64(vfs_ctx* ctx, const double* b, double* x) {
+int solve_fp64(vfs_ctx* ctx, const double* b, double* x, bool launched = false) {
     const Geo& g = ctx->g;
     const Parts P = parts(ctx);
     Vecs<double> v{x, ctx->r, ctx->p0, ctx->p1, ctx->q, nullptr, ctx->a, ctx->c, ctx->K,
                    ctx->dinv};
-    const int shape = res_shape(ctx, 8);
+    const int shape = launched ? -1 : res_shape(ctx, 8);
     if (shape < 0)
         if (int rc0 = zero_dirs(ctx, false)) return rc0;
     auto run = [&](bool set_bb, int most, Scalars* out, bool* gave_up) {
@@ -568,7 +569,7 @@ int solve_fp64(vfs_ctx* ctx, const double* b, double* x) {
     bool gave_up = false;
     int rc = run(true, ctx->max_iter, &s, &gave_up);
     if (rc) return rc;
-    if (gave_up) return solve_fp64(ctx, b, x);   // from the start, by launches
+    if (gave_up) return solve_fp64(ctx, b, x, true);   // from the start, by launches
     int total = s.iter, outer = 0, status = VFS_OK;
     const double bb = s.bb;
     ctx->stats.rel_residual_start = bb > 0.0 ? 1.0 : 0.0;
@@ -593,7 +594,7 @@ int solve_fp64(vfs_ctx* ctx, const double* b, double* x) {
         HIPCHK(hipGetLastError());
         rc = run(false, ctx->max_iter - total, &s, &gave_up);
         if (rc) return rc;
-        if (gave_up) return solve_fp64(ctx, b, x);
+        if (gave_up) return solve_fp64(ctx, b, x, true);
         total += s.iter;
     }
     ctx->stats.iterations = total;
@@ -622,6 +623,7 @@ int solve_mixed(vfs_ctx* ctx, const double* b, double* x) {
         if (int rc0 = net_prepare_ctx(ctx->net, ctx)) return fail(ctx, rc0, ctx->net->err);
     }
     int fallbacks = 0;
+    bool launched = false;   // a resident run of this solve was given up
     // warm start: keep the last solution on the samples that are still active
     const bool warm = ctx->warm_start && ctx->have_x && x == ctx->x;
     if (warm)
@@ -663,10 +665,11 @@ int solve_mixed(vfs_ctx* ctx, const double* b, double* x) {
         if (learned) {
             rc = run_chunks_fcg(ctx, v, true, &s);
         } else {
-            const int shape = res_shape(ctx, 4);
+            const int shape = launched ? -1 : res_shape(ctx, 4);
             if (shape >= 0)
                 rc = run_resident<float>(ctx, shape, v, true, ctx->max_iter - total, &s, &gave_up);
             if (!rc && gave_up) {   // again by launches, from the same residual
+                launched = true;
                 launch_cg_init<float>(g, ctx->r32, ctx->x32, ctx->r32, ctx->dinv32, nullptr, tol_in,
                                       ctx->max_iter - total, ctx->sc, P.B, ctx->stream);
                 HIPCHK(hipGetLastError());

@@ -51,12 +51,12 @@ struct vfs_batch {
     BatchCtl* h_ctl = nullptr;   // pinned
     // resident solve: device arrays (problems, workgroups, lists), their staging
     // copy, the tile shape of this step (-1: the persistent kernel) and the one
-    // the captured graph has; res_off: a resident solve was given up
+    // the captured graph has
     char* d_res = nullptr;
     char* h_res = nullptr;
     unsigned* d_beats = nullptr;
     int res_shape = -1, graph_shape = -1, res_groups = 0;
-    bool res_off = false;
+    ResPause res_pause;
     int forms = VFS_FORM_RESIDENT;
     int res_ran = -1, res_give_ups = 0;   // shape of the last step, launches given up
     // graph of the whole solve
@@ -299,7 +299,7 @@ bool res_pack(const std::vector<int>& order, const std::vector<int>& w, const st
 // side, small ones shorten the longest.
 int plan_resident(vfs_batch* b) {
     b->res_shape = -1;
-    if (b->res_off || !(b->forms & VFS_FORM_RESIDENT)) return VFS_OK;
+    if (b->res_pause.on() || !(b->forms & VFS_FORM_RESIDENT)) return VFS_OK;
     const int most = res_most();
     const double cost[kBResShapes] = {2.7, 3.2, 4.4};
     std::vector<ResGroup> best, trial;
@@ -352,7 +352,7 @@ int plan_resident(vfs_batch* b) {
     int* list = res_list(b->h_res, n);
     for (int p = 0; p < n; ++p) {
         vfs_ctx* c = b->ctx[p];
-        if (c->res_stamp > 0x7fffffffu) {   // far from wrapping within a solve
+        if (c->res_part && c->res_stamp > 0x7fffffffu) {   // far from wrapping within a solve
             BCHK(hipMemsetAsync(c->res_part, 0, 2 * kResMost * 16 * sizeof(*c->res_part), b->stream));
             BCHK(hipMemsetAsync(c->res_msg, 0, c->res_msg_words * sizeof(*c->res_msg), b->stream));
             c->res_stamp = 0;
@@ -448,15 +448,18 @@ int solve_all(vfs_batch* b, bool use_graph) {
     std::lock_guard<std::mutex> one(res_mutex());
     int rc = solve_once(b, use_graph);
     if (!rc && b->res_shape >= 0 && b->h_ctl->abort) {   // again, by the persistent kernel
-        b->res_off = true;
+        b->res_pause.gave_up();
         b->res_shape = -1;
         ++b->res_give_ups;
+        for (auto* c : b->ctx) c->res_stamp = 0xffffffffu;   // unknown: the next plan clears the words
         rc = solve_once(b, use_graph);
     }
     if (rc) return rc;
-    if (b->res_shape >= 0)
+    if (b->res_shape >= 0) {
+        b->res_pause.ran();
         for (int p = 0; p < b->n; ++p)
             if (b->h_state[p].stamp) b->ctx[p]->res_stamp = b->h_state[p].stamp + 4u;
+    }
     int status = VFS_OK;
     for (int p = 0; p < b->n; ++p)
         if (b->h_state[p].rel > b->tol) status = VFS_ENOTCONV;

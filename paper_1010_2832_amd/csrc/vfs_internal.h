@@ -19,6 +19,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <chrono>
 #include <mutex>
 #include <string>
 
@@ -29,6 +30,22 @@ namespace vfs {
 // Words through which the workgroups of a resident solve exchange values
 // (vfs_resident.h), and its tile shapes and largest number of workgroups.
 using LLWordBuf = unsigned long long*;
+
+// After a resident run was given up none is tried for 4 s, then 8, 16, ...: what
+// held compute units may have gone, and a try costs the deadline of a wait (1 s).
+// One that runs through clears it.
+struct ResPause {
+    double until = 0.0, length = 0.0;   // s
+    static double now() {
+        return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
+    }
+    bool on() const { return length > 0.0 && now() < until; }
+    void gave_up() {
+        length = length > 0.0 ? 2.0 * length : 4.0;
+        until = now() + length;
+    }
+    void ran() { length = 0.0; }
+};
 constexpr int kResShapes = 4;
 constexpr int kResMost = 256;
 constexpr int kRes3dShapes = 2, kRes3dMost = 512;   // 3D: two workgroups may share a unit
@@ -274,9 +291,8 @@ struct vfs_ctx {
     vfs::Tiles tiles{nullptr, 0, 0, 0, 0};
     int tiles2d = 0;                 // 2D: active tiles of the fused CG (in tile_list)
     // resident CG: exchange buffers, tile lists by shape and the stamp the next
-    // solve starts from (null buffers: the grid is too large for it); res_off
-    // is set when a wait was given up and keeps this context to the launched
-    // iteration; res_ran: shape of the last solve's runs (-1: launched)
+    // solve starts from (null buffers: the grid is too large for it); res_ran:
+    // shape of the last solve's runs (-1: launched)
     vfs::LLWordBuf res_part = nullptr, res_msg = nullptr;
     long long res_msg_words = 0;
     int* res_flags = nullptr;
@@ -288,7 +304,7 @@ struct vfs_ctx {
     double* res_stream = nullptr;   // 3D FP64, two bricks to a unit: their fields
     int* res_rank[vfs::kRes3dShapes] = {};   // 3D: workgroup of every brick
     unsigned res_stamp = 0;
-    bool res_off = false;
+    vfs::ResPause res_pause;
     int forms = VFS_FORM_RESIDENT;
     int res_ran = -1, res_give_ups = 0;
     // 3D: work tiles of the fused iteration holding an active tile, and one

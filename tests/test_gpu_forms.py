@@ -211,3 +211,41 @@ def test_batch_given_up_runs_in_the_persistent_kernel():
         b.close()
     for (i0, x0), (i1, x1) in zip(out[0], out[1]):
         assert i0 == i1 and np.array_equal(x0, x1)
+
+
+def test_resident_solves_come_back_after_one_is_given_up():
+    """Whatever held the compute units may have gone: after a pause of 4 s the
+    resident form is tried again, from cleared words."""
+    import time
+    solves = []
+    for name in ("2d_fp64", "3d_8"):
+        make, shape, precision = CASES[name]
+        ctx = gpu_run(make(), precision=precision, tol=1e-8, step=False)
+        b = ctx.vfs_get_rhs()
+        x = ctx.vfs_solve(b)
+        assert ctx.vfs_get_forms()["resident"] == shape
+        ctx.vfs_set_forms(RESIDENT | GIVE_UP)
+        ctx.vfs_solve(b)
+        ctx.vfs_set_forms(RESIDENT)
+        ctx.vfs_solve(b)
+        assert ctx.vfs_get_forms() == dict(forms=RESIDENT, resident=-1, give_ups=1)
+        solves.append((ctx, b, x, shape))
+    probs = _batch_problems()
+    batch = _batch(probs, RESIDENT | GIVE_UP)
+    batch.vfs_batch_set_forms(RESIDENT)
+    for i, c in enumerate(probs):
+        batch.vfs_batch_set_problem(i, c)
+    batch.vfs_batch_step(probs[0]["dt"])
+    assert batch.vfs_batch_get_forms() == dict(forms=RESIDENT, resident=-1, give_ups=1)
+    want = [batch.vfs_batch_get_solution(i) for i in range(len(probs))]
+    time.sleep(4.5)
+    for ctx, b, x, shape in solves:
+        assert np.array_equal(ctx.vfs_solve(b), x)
+        assert ctx.vfs_get_forms() == dict(forms=RESIDENT, resident=shape, give_ups=1)
+    for i, c in enumerate(probs):
+        batch.vfs_batch_set_problem(i, c)
+    batch.vfs_batch_step(probs[0]["dt"])
+    assert batch.vfs_batch_get_forms() == dict(forms=RESIDENT, resident=0, give_ups=1)
+    for i, x in enumerate(want):
+        assert np.array_equal(batch.vfs_batch_get_solution(i), x)
+    batch.close()
