@@ -4,6 +4,7 @@
 // this library on the context's stream.
 #include <algorithm>
 #include <cmath>
+#include <condition_variable>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -32,15 +33,44 @@ int res_most() {
     return c;
 }
 
-// One kernel at a time on a device whose workgroups wait for each other, resident
-// solve or persistent batch: two of them could each hold half of the chip and wait
-// for the other half.
-std::mutex& res_mutex() {
-    static std::mutex m[16];
+// Kernels whose workgroups wait for each other, resident solves and persistent
+// batches, may together hold no more workgroups than the chip has units: two of
+// them could else each hold half of what they need and wait for the rest.  Small
+// solves run side by side: a 96^2 FP64 solve in each of two or four host threads
+// takes 3.9 or 4.0 ms (7.0 or 14.1 with one solve at a time, 3.6 alone).  Who comes
+// first goes first, so that a large solve is not passed over for ever.
+struct ResGate {
+    std::mutex m;
+    std::condition_variable changed;
+    unsigned long long next = 0, serving = 0;
+    int used = 0;
+};
+
+ResPlace::ResPlace(int n) : units(n) {
+    static ResGate gates[16];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    return m[dev & 15];
+    gate = &gates[dev & 15];
+    const int most = res_most();
+    std::unique_lock<std::mutex> l(gate->m);
+    const unsigned long long ticket = gate->next++;
+    gate->changed.wait(l, [&] {
+        return gate->serving == ticket && (gate->used == 0 || gate->used + units <= most);
+    });
+    ++gate->serving;
+    gate->used += units;
+    gate->changed.notify_all();
 }
+
+ResPlace::~ResPlace() {
+    std::lock_guard<std::mutex> l(gate->m);
+    gate->used -= units;
+    gate->changed.notify_all();
+}
+
+// Workgroups are dealt to the 8 XCDs in turn, whatever runs there: a kernel takes
+// up to ceil(n / 8) units of each.
+int res_units(int n) { return std::min(res_most(), (n + 7) / 8 * 8); }
 
 }  // namespace vfs
 
@@ -334,7 +364,9 @@ int run_resident(vfs_ctx* ctx, int shape, Vecs<T>& v, bool set_bb, int max_iter,
         ctx->res_stamp = 0;
     }
     if (ctx->forms & VFS_FORM_GIVE_UP) HIPCHK(hipMemsetAsync(&ctx->sc->aborted, 1, sizeof(int), s));
-    std::lock_guard<std::mutex> one(res_mutex());
+    const bool pairs = ctx->g.dim == 3 && shape == 2;   // two workgroups to a unit
+    const int W = ctx->g.dim == 2 ? ctx->res_count[shape] : ctx->res_count[shape == 1 ? 1 : 0];
+    const ResPlace place(pairs ? res_most() : res_units(W));
     if (ctx->prof) HIPCHK(hipEventRecord(ctx->pev[0], s));
     if (ctx->g.dim == 2) {
         const int* list = ctx->res_lists + shape * kResMost;

@@ -442,10 +442,10 @@ int solve_once(vfs_batch* b, bool use_graph) {
 }
 
 // solve phase of a step on assembled problems (one graph launch); returns status.
-// Either form's workgroups wait for each other: the lock is held until the step
-// is solved, also when a resident launch is given up.
+// Either form's workgroups wait for each other and fill the chip: the place is held
+// until the step is solved, also when a resident launch is given up.
 int solve_all(vfs_batch* b, bool use_graph) {
-    std::lock_guard<std::mutex> one(res_mutex());
+    const ResPlace place(res_most());
     int rc = solve_once(b, use_graph);
     if (!rc && b->res_shape >= 0 && b->h_ctl->abort) {   // again, by the persistent kernel
         b->res_pause.gave_up();
@@ -757,19 +757,20 @@ int vfs_batch_time_variant(vfs_batch* b, int variant, int blocks_per_cu, int ite
     b->max_iter_pass = iterations;
     b->max_passes = 1;
     hipStream_t s = b->stream;
-    std::unique_lock<std::mutex> one(res_mutex());
-    const BatchArgs A0 = args(b, 1);
-    launch_batch_zero(A0, s);
-    launch_batch_resid(b->variant, A0, b->grid, s);
-    launch_batch_finalize(A0, s);
-    const BatchArgs A = args(b, 0);
-    launch_batch_reset_ctl(b->d_ctl, s);
-    BCHK(hipEventRecord(b->ev[0], s));
-    launch_batch_pcg(b->variant, A, b->grid, s);
-    BCHK(hipEventRecord(b->ev[1], s));
-    BCHK(hipGetLastError());
-    BCHK(hipEventSynchronize(b->ev[1]));
-    one.unlock();
+    {
+        const ResPlace place(res_most());
+        const BatchArgs A0 = args(b, 1);
+        launch_batch_zero(A0, s);
+        launch_batch_resid(b->variant, A0, b->grid, s);
+        launch_batch_finalize(A0, s);
+        const BatchArgs A = args(b, 0);
+        launch_batch_reset_ctl(b->d_ctl, s);
+        BCHK(hipEventRecord(b->ev[0], s));
+        launch_batch_pcg(b->variant, A, b->grid, s);
+        BCHK(hipEventRecord(b->ev[1], s));
+        BCHK(hipGetLastError());
+        BCHK(hipEventSynchronize(b->ev[1]));
+    }
     b->max_iter_pass = mip;
     b->max_passes = mp;
     rc = read_state(b);

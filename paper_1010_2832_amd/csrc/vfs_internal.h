@@ -20,7 +20,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <chrono>
-#include <mutex>
 #include <string>
 
 #include "../../include/vfstokes.h"
@@ -341,10 +340,23 @@ struct vfs_ctx {
 
 namespace vfs {
 
-// resident solves (vfs_api.hip): the workgroups one may have on this device,
-// and the lock held while one, or a persistent batch, runs
+// resident solves (vfs_api.hip): the workgroups one may have on this device
 int res_most();
-std::mutex& res_mutex();
+// A place on the current device for a kernel whose workgroups wait for each other,
+// held while it runs: waits until `units` compute units are free of such kernels.
+class ResPlace {
+  public:
+    explicit ResPlace(int units);
+    ~ResPlace();
+    ResPlace(const ResPlace&) = delete;
+    ResPlace& operator=(const ResPlace&) = delete;
+
+  private:
+    struct ResGate* gate;
+    int units;
+};
+// the units n workgroups need, one to a unit, wherever else others run
+int res_units(int n);
 // memory for a context's resident solves (none where it cannot be had)
 int res_alloc(vfs_ctx* ctx);
 

@@ -85,3 +85,33 @@ def test_persistent_batch_and_resident_solve_wait_for_each_other():
     assert give_ups == 0
     assert rc in (V.VFS_OK, V.VFS_ENOTCONV), rc
     batch.close()
+
+
+def test_small_solves_run_side_by_side():
+    """Two host threads with a small context each: the solves overlap (measured
+    0.54 of the time in turn, 0.97 with one solve at a time on the device), and
+    each gives the bits it gives alone.  A third thread's solve of the whole chip
+    gets its turn between them."""
+    ctxs = [_on_stream(gpu_run(cases.drop2d(96, 3 + q), tol=1e-10, step=False)) for q in range(2)]
+    rhs = [c.vfs_get_rhs() for c in ctxs]
+    want = [c.vfs_solve(b) for c, b in zip(ctxs, rhs)]
+    count = 40
+
+    def solves(q):
+        return all(np.array_equal(ctxs[q].vfs_solve(rhs[q]), want[q]) for _ in range(count))
+    t = time.time()
+    assert solves(0) and solves(1)
+    in_turn = time.time() - t
+    t = time.time()
+    assert _together(lambda: solves(0), lambda: solves(1)) == [True, True]
+    together = time.time() - t
+    _banner(f"in turn {in_turn:.3f} s, together {together:.3f} s")
+    assert together < 0.8 * in_turn
+    big = _on_stream(gpu_run(cases.drop2d(640, 11), tol=1e-6, step=False))
+    b = big.vfs_get_rhs()
+    x = big.vfs_solve(b)
+    out = _together(lambda: solves(0), lambda: solves(1), lambda: np.array_equal(big.vfs_solve(b), x))
+    assert out == [True, True, True]
+    for c in ctxs + [big]:
+        f = c.vfs_get_forms()
+        assert f["resident"] >= 0 and f["give_ups"] == 0
