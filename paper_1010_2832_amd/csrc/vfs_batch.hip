@@ -259,6 +259,23 @@ size_t res_bytes(int n) {
 BResWg* res_wgs(char* base, int n) { return (BResWg*)(base + sizeof(BResProb) * n); }
 int* res_list(char* base, int n) { return (int*)(res_wgs(base, n) + kResMost); }
 
+// Memory of the resident solve's plan, all of it or (false) none.
+bool res_buffers(vfs_batch* b) {
+    void *dev = nullptr, *host = nullptr, *beats = nullptr;
+    if (!(b->forms & VFS_FORM_NO_MEMORY) && hipMalloc(&dev, res_bytes(b->n)) == hipSuccess &&
+        hipHostMalloc(&host, res_bytes(b->n), hipHostMallocDefault) == hipSuccess &&
+        hipMalloc(&beats, sizeof(unsigned) * kResMost) == hipSuccess) {
+        b->d_res = (char*)dev;
+        b->h_res = (char*)host;
+        b->d_beats = (unsigned*)beats;
+        return true;
+    }
+    (void)hipGetLastError();
+    if (dev) (void)hipFree(dev);
+    if (host) (void)hipHostFree(host);
+    return false;
+}
+
 // Groups of workgroups for problems of widths w (tiles) and lengths t (expected
 // times): widest first, each problem goes to the narrowest group that still
 // has the time before `deadline`, or opens a group of its own width.  False if
@@ -342,10 +359,9 @@ int plan_resident(vfs_batch* b) {
     }
     if (b->res_shape < 0) return VFS_OK;
     const int n = b->n, q = b->res_shape;
-    if (!b->d_res) {
-        BCHK(hipMalloc((void**)&b->d_res, res_bytes(n)));
-        BCHK(hipHostMalloc((void**)&b->h_res, res_bytes(n), hipHostMallocDefault));
-        BCHK(hipMalloc((void**)&b->d_beats, sizeof(unsigned) * kResMost));
+    if (!b->d_res && !res_buffers(b)) {   // the persistent kernel needs none of it
+        b->res_shape = -1;
+        return VFS_OK;
     }
     BResProb* rp = (BResProb*)b->h_res;
     BResWg* wg = res_wgs(b->h_res, n);

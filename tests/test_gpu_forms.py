@@ -249,3 +249,20 @@ def test_resident_solves_come_back_after_one_is_given_up():
     for i, x in enumerate(want):
         assert np.array_equal(batch.vfs_batch_get_solution(i), x)
     batch.close()
+
+
+def test_batch_without_memory_for_its_plan():
+    """A resident step needs memory of its own; where there is none the persistent
+    kernel, which needs none of it, solves, and a later step tries again."""
+    probs = _batch_problems()
+    b = _batch(probs, RESIDENT | NO_MEMORY)
+    assert b.vfs_batch_get_forms()["resident"] == -1
+    want = [b.vfs_batch_get_solution(i) for i in range(len(probs))]
+    b.vfs_batch_set_forms(RESIDENT)
+    for i, c in enumerate(probs):
+        b.vfs_batch_set_problem(i, c)
+    b.vfs_batch_step(probs[0]["dt"])
+    assert b.vfs_batch_get_forms()["resident"] == 0
+    for i, x in enumerate(want):
+        assert np.array_equal(b.vfs_batch_get_solution(i), x)
+    b.close()
