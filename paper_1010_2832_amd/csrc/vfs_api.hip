@@ -137,23 +137,29 @@ int check_stage(vfs_ctx* ctx, const double* v, long long n, int positive, const 
     return VFS_OK;
 }
 
-// Whether kernels may use the caller's memory as it is: device memory of the
-// current GPU, aligned to its elements.  Other memory goes through the staging
-// array.
-bool direct(const double* user) {
+// Whether kernels may use the caller's n values as they are: device memory of the
+// current GPU, aligned to its elements, and all of it in one allocation.  Other
+// memory goes through the staging array by a copy, which refuses an array that
+// ends before its last value.
+bool direct(const double* user, long long n) {
     if (!user || (uintptr_t)user % sizeof(double)) return false;
     hipPointerAttribute_t at{};
-    if (hipPointerGetAttributes(&at, user) != hipSuccess) {
+    int dev = -1;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, user) != hipSuccess || at.type != hipMemoryTypeDevice ||
+        hipGetDevice(&dev) != hipSuccess || at.device != dev ||
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)user) != hipSuccess) {
         (void)hipGetLastError();   // host memory that HIP does not know
         return false;
     }
-    int dev = -1;
-    return hipGetDevice(&dev) == hipSuccess && at.type == hipMemoryTypeDevice && at.device == dev;
+    return (size_t)((const char*)user - (const char*)base) + (size_t)n * sizeof(double) <= size;
 }
 
-bool direct(const double* const* user, int count) {
+// arrays of weight sets
+bool direct(const Geo& g, int count, const int* sets, const double* const* users) {
     for (int q = 0; q < count; ++q)
-        if (!direct(user[q])) return false;
+        if (!direct(users[q], set_count(g, sets[q]))) return false;
     return true;
 }
 
@@ -182,7 +188,7 @@ int taken(vfs_ctx* ctx, int* first_bad) {
 // An array with a bad value changes neither its slice nor a later one.
 int put_sets(vfs_ctx* ctx, int count, const int* sets, const double* const* users, double* const* dsts,
              int positive, const char* what) {
-    if (direct(users, count)) {
+    if (direct(ctx->g, count, sets, users)) {
         SliceMap m{};
         for (int q = 0; q < count; ++q) map_slice(m, ctx->g, sets[q], users[q], dsts[q]);
         launch_take(ctx->g, m, TakeMode::check, positive, ctx->flag, ctx->flag_host, ctx->stream);
@@ -212,7 +218,7 @@ int put_set(vfs_ctx* ctx, int set, const double* user, double* dst, int positive
 
 // padded device slices -> user (host or device) compact arrays
 int get_sets(vfs_ctx* ctx, int count, const int* sets, const double* const* srcs, double* const* users) {
-    if (direct(users, count)) {
+    if (direct(ctx->g, count, sets, users)) {
         SliceMap m{};
         for (int q = 0; q < count; ++q) map_slice(m, ctx->g, sets[q], users[q], srcs[q]);
         launch_give(ctx->g, m, ctx->stream);
@@ -986,7 +992,7 @@ int pack_samples(vfs_ctx* ctx, const double* user, double* dst, double* active =
         users[s] = user + off;
         off += set_count(g, sets[s]);
     }
-    if (direct(user)) {
+    if (direct(user, off)) {
         SliceMap m{};
         for (int s = 0; s < g.nsamp(); ++s) map_slice(m, g, sets[s], users[s], dst + s * g.NP);
         m.mask = active ? ctx->a : nullptr;
@@ -1317,7 +1323,7 @@ int vfs_set_level_sets(vfs_ctx* ctx, const double* phi_liquid, const double* phi
     if (!ctx) return VFS_EINVAL;
     if (!phi_liquid) return fail(ctx, VFS_EINVAL, "phi_liquid is NULL");
     const long long n = node_count(ctx->g);
-    if (direct(phi_liquid) && (!phi_solid || direct(phi_solid))) {
+    if (direct(phi_liquid, n) && (!phi_solid || direct(phi_solid, n))) {
         // a bad liquid level set keeps the solid one from being taken
         const double* from[2] = {phi_liquid, phi_solid};
         double* to[2] = {ctx->phi_l, ctx->phi_s};

@@ -103,3 +103,29 @@ def test_a_bad_value_changes_neither_its_array_nor_a_later_one(name, put):
     fresh.vfs_step(case["dt"])
     for q, r in zip(ctx.vfs_get_velocity(), fresh.vfs_get_velocity()):
         assert np.array_equal(q, r)
+
+
+def test_device_arrays_that_end_early_are_refused():
+    """An array that ends before its last value is refused, as the copies that took
+    it did, and not read or written past its end.  (The values missing here lie in
+    the same page of memory.)"""
+    from paper_1010_2832_amd import vfstokes as V
+    case = cases.drop2d(16, 3)
+    ctx = gpu_run(case, step=False)
+    hip = V._lib   # its HIP runtime
+    short = ctypes.c_void_p()
+    assert hip.hipMalloc(ctypes.byref(short), ctypes.c_size_t(1024)) == 0
+    try:
+        zero = np.zeros(128)
+        assert hip.hipMemcpy(short, ctypes.c_void_p(zero.ctypes.data), ctypes.c_size_t(1024), 1) == 0
+        old = ctx.vfs_get_pressure(), ctx.vfs_get_velocity()
+        assert V._lib.vfs_set_density(ctx.handle, short) == V.VFS_EHIP
+        assert V._lib.vfs_set_velocity(ctx.handle, short, short, None) == V.VFS_EHIP
+        assert V._lib.vfs_set_level_sets(ctx.handle, short, None) == V.VFS_EHIP
+        assert V._lib.vfs_get_pressure(ctx.handle, short) == V.VFS_EHIP
+        assert V._lib.vfs_get_rhs(ctx.handle, short) == V.VFS_EHIP
+        assert V._lib.vfs_apply(ctx.handle, short, short) == V.VFS_EHIP
+        for a, b in zip(old[1], ctx.vfs_get_velocity()):
+            assert np.array_equal(a, b)
+    finally:
+        assert hip.hipFree(short) == 0
