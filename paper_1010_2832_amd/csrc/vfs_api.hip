@@ -163,6 +163,16 @@ bool direct(const Geo& g, int count, const int* sets, const double* const* users
     return true;
 }
 
+// Outputs of which two share memory are written one after the other, the last one
+// last, and not by one launch.
+bool apart(const Geo& g, int count, const int* sets, double* const* users) {
+    for (int q = 0; q < count; ++q)
+        for (int p = 0; p < q; ++p)
+            if (users[p] < users[q] + set_count(g, sets[q]) && users[q] < users[p] + set_count(g, sets[p]))
+                return false;
+    return true;
+}
+
 void map_slice(SliceMap& m, const Geo& g, int set, const double* user, const double* pad) {
     const int q = m.count++;
     m.user[q] = const_cast<double*>(user);
@@ -218,7 +228,7 @@ int put_set(vfs_ctx* ctx, int set, const double* user, double* dst, int positive
 
 // padded device slices -> user (host or device) compact arrays
 int get_sets(vfs_ctx* ctx, int count, const int* sets, const double* const* srcs, double* const* users) {
-    if (direct(ctx->g, count, sets, users)) {
+    if (apart(ctx->g, count, sets, users) && direct(ctx->g, count, sets, users)) {
         SliceMap m{};
         for (int q = 0; q < count; ++q) map_slice(m, ctx->g, sets[q], users[q], srcs[q]);
         launch_give(ctx->g, m, ctx->stream);

@@ -129,3 +129,24 @@ def test_device_arrays_that_end_early_are_refused():
             assert np.array_equal(a, b)
     finally:
         assert hip.hipFree(short) == 0
+
+
+def test_outputs_that_share_memory_hold_the_last_one():
+    """One device array given for several components of the velocity holds the last
+    component's values, as with host arrays; so do parts that overlap."""
+    import torch
+    from paper_1010_2832_amd import vfstokes as V
+    case = cases.crop(cases.pool3d(40, 9), (0, 0, 0), (40, 31, 37))
+    ctx = gpu_run(case, step=False)
+    u = [q.ravel(order="F") for q in ctx.vfs_get_velocity()]
+    for shift in (0, 1000):
+        host = np.full(max(q.size for q in u) + 2 * shift, np.nan)
+        dev = _dev(host)
+        for buf, p in ((host, host.ctypes.data), (dev, dev.data_ptr())):
+            ptr = [ctypes.c_void_p(p + 8 * shift * a) for a in range(3)]
+            assert V._lib.vfs_get_velocity(ctx.handle, *ptr) == 0
+        want = np.full_like(host, np.nan)
+        for a in range(3):
+            want[shift * a:shift * a + u[a].size] = u[a]
+        assert np.array_equal(host, want, equal_nan=True)
+        assert np.array_equal(dev.cpu().numpy(), want, equal_nan=True)
