@@ -304,7 +304,9 @@ int vfs_get_sizes(const vfs_ctx* ctx, int64_t* n_samples, int64_t* n_faces);
  * Work is queued on hip_stream (NULL = the null stream) and the call returns
  * without synchronising; NaN/Inf in phi_liquid are not checked.  One kernel
  * reads the level set and writes out, with no work space: calls on one GPU may
- * overlap (different streams or threads).  Grids whose fractions and weights,
+ * overlap (different streams or threads).  Where out shares memory with
+ * phi_liquid the weights pass through one 12 MiB array per GPU, held until the
+ * process ends: such calls must be serialised by the caller.  Grids whose fractions and weights,
  * (16 (nx ny [nz]) + 2 nsets NP) doubles in 3D and (8 nx ny + 2 nsets NP) in 2D,
  * NP the padded grid size of the conventions above, are over 96 MiB return
  * VFS_EINVAL: square 2D grids up to 882^2 and cubic 3D grids up to 69^3 pass.

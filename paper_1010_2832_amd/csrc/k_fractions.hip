@@ -361,7 +361,12 @@ __global__ __launch_bounds__(256) void k_weights(Geo g, const double* __restrict
 // volumes of one set share no sub-cell: a lane computes one, and the 2^d lanes of
 // a sample add theirs in pairs along x, y and z.  3.4 us at 64^2, where the
 // launches of filling, sub-cell, weight and unpack kernels took 18.
-template <int DIM>
+//
+// KEEP: out may lie over phi, so the weights are kept in an array of the library's
+// until all of phi is read (k_kept_out then copies them).
+__device__ double kept[kMostSetValues];
+
+template <int DIM, bool KEEP>
 __global__ __launch_bounds__(256) void k_weights_set(Geo g, int n0, int n1, int n2, int sx, int sy, int sz,
                                                      const double* __restrict__ phi, double w_min,
                                                      double* __restrict__ out) {
@@ -386,7 +391,12 @@ __global__ __launch_bounds__(256) void k_weights_set(Geo g, int n0, int n1, int 
     f = f + __shfl_xor(f, 1);
     f = f + __shfl_xor(f, 2);
     if constexpr (DIM == 3) f = f + __shfl_xor(f, 4);
-    if (q == 0) out[e] = snap(f * (DIM == 2 ? 0.25 : 0.125), w_min);
+    if (q == 0) (KEEP ? kept : out)[e] = snap(f * (DIM == 2 ? 0.25 : 0.125), w_min);
+}
+
+__global__ __launch_bounds__(256) void k_kept_out(long long n, double* __restrict__ out) {
+    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n) out[t] = kept[t];
 }
 
 __global__ void k_fill(double* __restrict__ d, long long n, double v) {
@@ -425,12 +435,18 @@ void launch_weights_set(const Geo& g, int set, const double* phi_l, double w_min
     const long long n = (long long)shp[0] * shp[1] * (g.dim == 3 ? shp[2] : 1);
     const int sx = shp[0] == g.nx, sy = shp[1] == g.ny, sz = g.dim == 3 ? shp[2] == g.nz : 1;
     const unsigned nb = (unsigned)((n * (1 << g.dim) + 255) / 256);
+    const long long nodes = (long long)(g.nx + 1) * (g.ny + 1) * (g.dim == 3 ? g.nz + 1 : 1);
+    const bool keep = out < phi_l + nodes && phi_l < out + n;
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nb), dim3(256), 0, s, g, shp[0], shp[1], g.dim == 3 ? shp[2] : 1, sx,
+                           sy, sz, phi_l, w_min, out);
+    };
     if (g.dim == 2)
-        hipLaunchKernelGGL(k_weights_set<2>, dim3(nb), dim3(256), 0, s, g, shp[0], shp[1], 1, sx, sy, sz,
-                           phi_l, w_min, out);
+        keep ? launch(k_weights_set<2, true>) : launch(k_weights_set<2, false>);
     else
-        hipLaunchKernelGGL(k_weights_set<3>, dim3(nb), dim3(256), 0, s, g, shp[0], shp[1], shp[2], sx, sy,
-                           sz, phi_l, w_min, out);
+        keep ? launch(k_weights_set<3, true>) : launch(k_weights_set<3, false>);
+    if (keep)
+        hipLaunchKernelGGL(k_kept_out, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, out);
 }
 
 }  // namespace vfs

@@ -370,7 +370,9 @@ void launch_fill(double* dst, long long n, double v, hipStream_t s);
 // no solid)
 void launch_weights(const Geo& g, const double* phi_l, const double* phi_s, double w_min,
                     double* WL, double* WF, hipStream_t s);
-// liquid weights of one set (numbered as stored) to a compact array
+// liquid weights of one set (numbered as stored) to a compact array of at most
+// kMostSetValues; it may lie over phi_l, but such launches must not run at a time
+constexpr long long kMostSetValues = 1572864;
 void launch_weights_set(const Geo& g, int set, const double* phi_l, double w_min, double* out,
                         hipStream_t s);
 // 2D assembly (k_assemble2d.hip)

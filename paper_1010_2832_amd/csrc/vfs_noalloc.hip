@@ -1,7 +1,7 @@
 // Allocation-free entry point: the liquid volume fractions W_L of one sample
 // set (Section 5, Figs. 3-4) straight from a nodal liquid level set, with no
 // context, no device allocation and no work space: one kernel from the level set
-// to the caller's array (filling, sub-cell, weight and unpack kernels over a work
+// to the caller's array, by way of a static one where the two overlap (filling, sub-cell, weight and unpack kernels over a work
 // array took 20 us at 64^2).  The operation order is that of vfs_assemble, so
 // the result is bit-identical to vfs_get_weights(ctx, set, VFS_WEIGHT_LIQUID,
 // out) on a context assembled from the same level set.
@@ -16,6 +16,9 @@ namespace {
 
 // the grids this call takes, by the bytes of their sub-cell fractions and weights
 constexpr long long kMostBytes = 96LL * 1024 * 1024;
+// they hold at least 8 (2D: two materials of four sets) arrays of NP values, and a
+// set has fewer values than NP
+static_assert(kMostSetValues >= kMostBytes / 8 / 8, "the largest set");
 
 // errors are reported through vfs_last_error(NULL)
 int nfail(int code, const std::string& m) { return fail_global(code, m); }
