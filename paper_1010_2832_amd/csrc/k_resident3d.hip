@@ -76,7 +76,7 @@ struct Res3dArgs {
     int nbx, nby;      // bricks of the lattice along x and y
     double* buf;       // streamed fields of every workgroup, or null
     LLWord* part;
-    LLWord* msg;       // [2][kRes3dMost][message]
+    LLWord* msg;       // [2][workgroups][message]
     unsigned stamp;
     int set_bb;
     int pair;          // the launched iteration would run two threads an anchor
@@ -392,7 +392,7 @@ __global__ __launch_bounds__((Brick<BX, BY, BZ>::NT), (PER * Brick<BX, BY, BZ>::
             const unsigned want = S.stamp + (unsigned)k;
             double tot[5];
             if (W > 1) {
-                const LLWord* msg = S.msg + (long long)(want & 1) * kRes3dMost * B::values * LW;
+                const LLWord* msg = S.msg + (long long)(want & 1) * W * B::values * LW;
                 const LLWord* pw = S.part + (long long)(want & 1) * kRes3dMost * 16 + 2 * min(tt & 7, 4);
                 LLWord* const all = S.part + (2 + (want & 1)) * (long long)kRes3dMost * 16;
                 const int np = (W + PS - 1) / PS;
@@ -587,7 +587,7 @@ __global__ __launch_bounds__((Brick<BX, BY, BZ>::NT), (PER * Brick<BX, BY, BZ>::
         // A p at the own anchors
         renew();
         const unsigned stamp = S.stamp + (unsigned)k + 1u;
-        LLWord* out = S.msg + ((long long)(stamp & 1) * kRes3dMost + me) * B::values * LW;
+        LLWord* out = S.msg + ((long long)(stamp & 1) * W + me) * B::values * LW;
 #pragma unroll
         for (int n = 0; n < RPT; ++n) {
             const int x = lx(n), y = ly(n), z = lz(n);
@@ -754,10 +754,15 @@ void res3d_lattice(const Geo& g, int shape, int& nbx, int& nby, int& nbz) {
     nbz = g.nz / b.bz + 1;
 }
 
-// words of the messages of the most workgroups, both parities; FP64 for the
-// first shape, FP32 for the second
-long long res3d_words() {
-    return std::max(2LL * kRes3dMost * Brick<8, 8, 8>::values * 2, 2LL * kRes3dMost * Brick<16, 8, 8>::values);
+// words of the messages of the most workgroups a grid can need, both parities; FP64
+// for the first shape, FP32 for the second
+long long res3d_words(const Geo& g) {
+    auto bricks = [&](int shape) {
+        int x, y, z;
+        res3d_lattice(g, shape, x, y, z);
+        return std::min((long long)x * y * z, (long long)kRes3dMost);
+    };
+    return std::max(2 * bricks(0) * Brick<8, 8, 8>::values * 2, 2 * bricks(1) * Brick<16, 8, 8>::values);
 }
 
 // values of the streamed fields of n bricks

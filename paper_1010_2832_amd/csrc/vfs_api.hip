@@ -1084,7 +1084,7 @@ int res_alloc(vfs_ctx* ctx) {
             all += nb[q];
         }
         const long long part = 4 * kRes3dMost * 16, lists = kRes3dShapes * kRes3dMost;
-        ctx->res_msg_words = res3d_words();
+        ctx->res_msg_words = res3d_words(g);
         // words, messages, then lists, ranks and flags
         const int rc = alloc(part + ctx->res_msg_words + (lists + all + most + 1) / 2);
         if (rc || !ctx->res_part) return rc;
@@ -1545,6 +1545,10 @@ int vfs_set_solver(vfs_ctx* ctx, int precond, int precision, double rel_tol, int
             ctx->bricks = nullptr;
             (void)hipGetLastError();
         }
+    } else if (precond != VFS_PRECOND_SCHWARZ && ctx->bricks) {   // its memory is given back
+        HIPCHK(hipStreamSynchronize(ctx->stream));
+        (void)hipFree(ctx->bricks);
+        ctx->bricks = nullptr;
     }
     ctx->precond = precond;
     ctx->precision = precision;

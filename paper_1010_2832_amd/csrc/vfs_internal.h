@@ -546,7 +546,7 @@ void launch_resident2d(const Geo& g, int shape, const int* tiles, int count, con
 // FP64: two to a compute unit) or, in FP32, 16 x 8 x 8 anchors (shape 1); e = a D^-1 (FP64: D^-1); pair and fold: what the
 // launched iteration would do (its Tiles::split, its folded column)
 void res3d_lattice(const Geo& g, int shape, int& nbx, int& nby, int& nbz);
-long long res3d_words();
+long long res3d_words(const Geo& g);
 bool res3d_two();                  // shape 2 fits
 long long res3d_stream(int n);     // its buffer, in doubles, for n bricks
 void launch_res3d_lists(const Geo& g, int shape, const double* a, const int* tile_flags, int* flags,

@@ -1,10 +1,11 @@
 // Allocation-free entry point: the liquid volume fractions W_L of one sample
 // set (Section 5, Figs. 3-4) straight from a nodal liquid level set, with no
 // context, no device allocation and no work space: one kernel from the level set
-// to the caller's array, by way of a static one where the two overlap (filling, sub-cell, weight and unpack kernels over a work
-// array took 20 us at 64^2).  The operation order is that of vfs_assemble, so
-// the result is bit-identical to vfs_get_weights(ctx, set, VFS_WEIGHT_LIQUID,
-// out) on a context assembled from the same level set.
+// to the caller's array, by way of a static one where the two overlap (filling,
+// sub-cell, weight and unpack kernels over a work array took 20 us at 64^2).  The
+// operation order is that of vfs_assemble, so the result is bit-identical to
+// vfs_get_weights(ctx, set, VFS_WEIGHT_LIQUID, out) on a context assembled from
+// the same level set.
 #include <cmath>
 #include <string>
 

@@ -266,3 +266,35 @@ def test_batch_without_memory_for_its_plan():
     for i, x in enumerate(want):
         assert np.array_equal(b.vfs_batch_get_solution(i), x)
     b.close()
+
+
+def _used():
+    import torch
+    torch.cuda.synchronize()
+    free, total = torch.cuda.mem_get_info()
+    return total - free
+
+
+def test_memory_of_small_contexts_and_of_a_preconditioner_no_longer_set():
+    """A small 3D context holds exchange words for the bricks it can have (it held
+    38 MB for 512 of them), and the Schwarz corrections are held only while that
+    preconditioner is set."""
+    from paper_1010_2832_amd import vfstokes as V
+    V.Context(3, (8, 8, 8), 0.1).close()     # the library's own first allocations
+    before = _used()
+    ctxs = [V.Context(3, (8, 8, 8), 0.1) for _ in range(20)]
+    small = (_used() - before) / len(ctxs) / 1e6
+    for c in ctxs:
+        c.close()
+    ctx = V.Context(3, (96, 96, 96), 0.01)
+    before = _used()
+    ctx.vfs_set_solver(V.VFS_PRECOND_SCHWARZ, V.VFS_FP64, 1e-6, 100, 1e-3)
+    held = (_used() - before) / 1e6
+    ctx.vfs_set_solver(V.VFS_PRECOND_JACOBI, V.VFS_FP64, 1e-6, 100, 1e-3)
+    left = (_used() - before) / 1e6
+    ctx.vfs_set_solver(V.VFS_PRECOND_SCHWARZ, V.VFS_FP64, 1e-6, 100, 1e-3)
+    again = (_used() - before) / 1e6
+    ctx.close()
+    _banner(f"MB: {small:.1f} a small context, corrections {held:.0f}, {left:.0f} after, {again:.0f} again")
+    assert small < 20
+    assert 160 < held < 200 and left < 8 and abs(again - held) < 8
