@@ -15,7 +15,7 @@
 // R, Q and the halo's R in registers and stream the rest (a, D^-1, c, K, x) from
 // rows of their own.  Of those up to 512 workgroups the first adds the sums and
 // writes each of the others its own line: 474 workgroups reading 474 lines, or all
-// one line, slowed everything else (88 x 56 x 72: 100 and 330 ms a step, now 50).
+// one line, slowed everything else (88 x 56 x 72: 100 and 330 ms a step, now 36 to 42).
 // a p lies in LDS, c, K and 1 / a too, where the registers would spill, and
 // addresses are renewed in every iteration (hoisted by the compiler they were
 // spilled, and 64^3 took 17.9 us an iteration).  Measured, us an iteration,

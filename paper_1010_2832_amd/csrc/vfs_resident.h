@@ -2,18 +2,20 @@
 // the chip for a whole solve and trade values through memory once per CG
 // iteration, without a launch, a fence or a barrier.
 //
-// Every value travels as 8-byte words of 32 bits of payload and a 32-bit
-// stamp, stored and polled with relaxed agent-scope atomics (which bypass the
-// caches that are not shared), so a word that shows the expected stamp is the
-// value itself: one trip through memory carries data and arrival.  All
-// participants reading ten words of each other took 1.4 us a round for 32
+// The words are those of low-latency collectives, which send a flag with every
+// few bytes of data: every value travels as 8-byte words of 32 bits of payload
+// and a 32-bit stamp, stored and polled with relaxed agent-scope atomics (which
+// bypass the caches that are not shared), so a word that shows the expected
+// stamp is the value itself: one trip through memory carries data and arrival.
+// All participants reading ten words of each other took 1.4 us a round for 32
 // workgroups and 2.3 us for 256 (a grid barrier with release and acquire: 12
 // us for 256, because it writes back and invalidates the L2s).
 //
 // Two slots by iteration parity suffice: a workgroup stores iteration k + 1
 // only after it has read the partial sums of iteration k from everybody, and
 // everybody stores those after reading all it needs of iteration k - 1.
-// Stamps grow over all solves of a context, so no slot has to be cleared.
+// Stamps grow over all solves of a context, so no slot has to be cleared but
+// after a solve that was given up.
 // Every wait ends: by arrival, by the abort flag of the solve, or by a
 // deadline, which sets that flag.
 #pragma once
